@@ -124,14 +124,13 @@ __device__ __forceinline__ void load_site_nt(const cx<T>* __restrict__ st, const
   }
 }
 
-// C^H without its factor 1/2:  2 a' = (a + b) + i (a - b),  2 b' = (a + b) - i (a - b)
-__device__ __forceinline__ void collide2_adj(cx<double> (&a)[5], cx<double> (&b)[5]) {
+// C^H times (1 - i), the adjoint of collide_r:  a' = a - i b,  b' = b - i a
+__device__ __forceinline__ void collide_r_adj(cx<double> (&a)[5], cx<double> (&b)[5]) {
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    const double sr = a[m].re + b[m].re, si = a[m].im + b[m].im;
-    const double dr = a[m].re - b[m].re, di = a[m].im - b[m].im;
-    a[m] = cx<double>{sr - di, si + dr};
-    b[m] = cx<double>{sr + di, si - dr};
+    const cx<double> x = a[m], y = b[m];
+    a[m] = cx<double>{x.re + y.im, x.im - y.re};
+    b[m] = cx<double>{y.re + x.im, y.im - x.re};
   }
 }
 
@@ -155,18 +154,19 @@ __device__ __forceinline__ cx<T> lane_move(cx<T> v) {
   return cx<T>{lane_move<Ctrl>(v.re), lane_move<Ctrl>(v.im)};
 }
 
-// I'_{x,q} with x along the lanes, in the operation order of iprime_site: C, q from x + 1, C,
-// q from x - 1, and its exact 1/4.  Q = 1: qubit b moves; Q = 0: qubit a.
+// 2 f I'_{x,q}, with x along the lanes, in the operation order of
+// iprime_site: C, q from x + 1, C, q from x - 1, and the collides' factor 2i
+// divided out (f = 1/2, or less where the state carries a factor of its own).  Q = 1: qubit b moves; Q = 0: qubit a.
 template <int Q, typename T>
-__device__ __forceinline__ void iprime_lanes(cx<T> (&a)[5], cx<T> (&b)[5]) {
-  collide2(a, b);
+__device__ __forceinline__ void iprime_lanes(cx<T> (&a)[5], cx<T> (&b)[5], T f) {
+  collide_r(a, b);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
     if (Q) b[m] = lane_move<kFromNextLane>(b[m]);
     else   a[m] = lane_move<kFromNextLane>(a[m]);
   }
-  collide2(a, b);
-  scale_quarter(a, b);
+  collide_r(a, b);
+  unphase_by(a, b, f);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
     if (Q) b[m] = lane_move<kFromPrevLane>(b[m]);
@@ -174,8 +174,8 @@ __device__ __forceinline__ void iprime_lanes(cx<T> (&a)[5], cx<T> (&b)[5]) {
   }
 }
 
-// lambda <- I'^H_{x,q} lambda with x along the lanes: q from x + 1, C^H, q from x - 1, C^H, 1/4
-// (the order of iprime_adj_site).  Q = 1: qubit b moves; Q = 0: qubit a.
+// lambda <- I'^H_{x,q} lambda with x along the lanes: q from x + 1, C^H, q from x - 1, C^H
+// (the order of iprime_adj_site), the factors of the two C^H divided out.  Q = 1: qubit b moves; Q = 0: qubit a.
 template <int Q>
 __device__ __forceinline__ void iprime_adj_lanes(cx<double> (&a)[5], cx<double> (&b)[5]) {
 #pragma unroll
@@ -183,26 +183,22 @@ __device__ __forceinline__ void iprime_adj_lanes(cx<double> (&a)[5], cx<double> 
     if (Q) b[m] = lane_move<kFromNextLane>(b[m]);
     else   a[m] = lane_move<kFromNextLane>(a[m]);
   }
-  collide2_adj(a, b);
+  collide_r_adj(a, b);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
     if (Q) b[m] = lane_move<kFromPrevLane>(b[m]);
     else   a[m] = lane_move<kFromPrevLane>(a[m]);
   }
-  collide2_adj(a, b);
-#pragma unroll
-  for (int m = 0; m < 5; ++m) {
-    a[m] = 0.25 * a[m];
-    b[m] = 0.25 * b[m];
-  }
+  collide_r_adj(a, b);
+  unphase_by(a, b, -0.5);
 }
 
 }  // namespace
 
 // (I' in)(x) for I'_{axis,q} = S_q C S_q^T C, from `in` at x-1, x, x+1, with the fused
 // kernels' operation order: c = C(in) at x-1, x, x+1;  t(y) = (c.nonq(y), c.q(y+1));
-// m(y) = C t(y) (two unscaled collides and an exact 1/4);  out.nonq(x) = m(x).nonq,
-// out.q(x) = m(x-1).q.
+// m(y) = C t(y) (two collides by collide_r, their exact factor 2i divided out at the end);
+// out.nonq(x) = m(x).nonq, out.q(x) = m(x-1).q.
 template <typename T>
 __device__ __forceinline__ void iprime_site(const cx<T>* __restrict__ in, const Site& r, int axis, int qb,
                                             cx<T> (&oa)[5], cx<T> (&ob)[5]) {
@@ -211,9 +207,9 @@ __device__ __forceinline__ void iprime_site(const cx<T>* __restrict__ in, const 
   load_site(in, r.d, sm, a0, b0);
   load_site(in, r.d, r.s, a1, b1);
   load_site(in, r.d, sp, a2, b2);
-  collide2(a0, b0);
-  collide2(a1, b1);
-  collide2(a2, b2);
+  collide_r(a0, b0);
+  collide_r(a1, b1);
+  collide_r(a2, b2);
   cx<T> ta[5], tb[5], ua[5], ub[5];
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
@@ -223,15 +219,14 @@ __device__ __forceinline__ void iprime_site(const cx<T>* __restrict__ in, const 
     ua[m] = sel(qb != 0, a0[m], a1[m]);
     ub[m] = sel(qb != 0, b1[m], b0[m]);
   }
-  collide2(ta, tb);
-  scale_quarter(ta, tb);
-  collide2(ua, ub);
-  scale_quarter(ua, ub);
+  collide_r(ta, tb);
+  collide_r(ua, ub);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
     oa[m] = sel(qb != 0, ta[m], ua[m]);   // moving qubit from m(x-1), the other from m(x)
     ob[m] = sel(qb != 0, ub[m], tb[m]);
   }
+  unphase_by(oa, ob, T(0.5));
 }
 
 // One link of the recorded forward chain that regenerates a checkpoint segment:
@@ -259,6 +254,7 @@ __global__ __launch_bounds__(kChunk) void k_chain(const cx<T>* __restrict__ in, 
     // the same per-site angle as the fused forward kernels: T(theta) T(V + mu)
     if (pot || mu != 0.0) potential<T, true>(a, b, ang, T(theta) * T((pot ? pot[r.d.psi_off / 5 + r.s] : 0.0) + mu));
     else potential(a, b, ang);
+    scale_by(a, b, T(1) / UScale<T>::value);
   }
   store_site(out, r.d, r.s, a, b);
 }
@@ -280,19 +276,15 @@ __device__ __forceinline__ void iprime_adj_site(const cx<double>* __restrict__ i
     va[m] = sel(qb != 0, a0[m], a1[m]);
     vb[m] = sel(qb != 0, b1[m], b0[m]);
   }
-  collide2_adj(wa, wb);
-  collide2_adj(va, vb);
+  collide_r_adj(wa, wb);
+  collide_r_adj(va, vb);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
     oa[m] = sel(qb != 0, wa[m], va[m]);
     ob[m] = sel(qb != 0, vb[m], wb[m]);
   }
-  collide2_adj(oa, ob);
-#pragma unroll
-  for (int m = 0; m < 5; ++m) {
-    oa[m] = 0.25 * oa[m];
-    ob[m] = 0.25 * ob[m];
-  }
+  collide_r_adj(oa, ob);
+  unphase_by(oa, ob, -0.5);
 }
 
 // lambda <- I'^H lambda, out of place.
@@ -608,16 +600,18 @@ __global__ __launch_bounds__(kChunk) void k_chain_x4(const cx<T>* __restrict__ i
     if (ext) potential<T, true>(a, b, ang, e);
     else potential(a, b, ang);
   };
-  iprime_lanes<1>(a, b);
+  constexpr T kAfterU = T(0.5) / UScale<T>::value;   // U leaves its factor to the I' after it
+  iprime_lanes<1>(a, b, T(0.5));
   link(r0);
-  iprime_lanes<1>(a, b);
+  iprime_lanes<1>(a, b, kAfterU);
   link(r1);
-  iprime_lanes<0>(a, b);
+  iprime_lanes<0>(a, b, kAfterU);
   link(r2);
   if (r3) {
-    iprime_lanes<0>(a, b);
+    iprime_lanes<0>(a, b, kAfterU);
     link(r3);
   }
+  scale_by(a, b, T(1) / UScale<T>::value);
   if (own) store_site(out, d, s, a, b);
 }
 

@@ -57,17 +57,17 @@ __device__ __forceinline__ cx<T> from_prev_lane(cx<T> v) {
   return cx<T>{dpp_move<kDppWaveShr1>(v.re), dpp_move<kDppWaveShr1>(v.im)};
 }
 
-// 4 I'_{x,q} = S_q (2C) S_q^T (2C) with lanes along x (the factor 1/4 is left to
+// 2i I'_{x,q}: S_q C S_q^T C by collide_r, with lanes along x (the factor 1/(2i) is left to
 // the caller).  Q = 1: qubit b (the paper's qubit 2) moves; Q = 0: qubit a (qubit 1).
 template <typename T, int Q>
-__device__ __forceinline__ void iprime4_lanes(cx<T> (&a)[5], cx<T> (&b)[5]) {
-  collide2(a, b);
+__device__ __forceinline__ void iprime_r_lanes(cx<T> (&a)[5], cx<T> (&b)[5]) {
+  collide_r(a, b);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {   // S^T: q(x) <- q(x + 1)
     if (Q) b[m] = from_next_lane(b[m]);
     else   a[m] = from_next_lane(a[m]);
   }
-  collide2(a, b);
+  collide_r(a, b);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {   // S: q(x) <- q(x - 1)
     if (Q) b[m] = from_prev_lane(b[m]);
@@ -75,18 +75,33 @@ __device__ __forceinline__ void iprime4_lanes(cx<T> (&a)[5], cx<T> (&b)[5]) {
   }
 }
 
+// What an interleaved substep U I' leaves the state multiplied by, in modulus: 2 from the I'
+// (collide_r) times UScale from U.
+template <typename T>
+constexpr int kSubstepScale = 2 * UScale<T>::value;
+
 // Angles of interleaved substep j = 0..3 of a four-I' sequence, on a state that
-// carries the factor 4^j of the j I' before it: the n terms' angles and F's scale
-// times 16^-j (exact).  Formed from the unscaled angles in registers, so that a
-// run-time j reads no kernel argument inside the row loop.
+// carries the factor kSubstepScale^j (and i^j) of the j substeps before it: the n terms'
+// angles and F's scale times kSubstepScale^-2j (exact).  Formed from the unscaled angles in
+// registers, so that a run-time j reads no kernel argument inside the row loop.
 template <typename T>
 __device__ __forceinline__ Angles<T> substep_angles(const Angles<T>& base, int j) {
-  const T f = ldexp(T(1), -4 * j);
+  const T f = ldexp(T(1), (kSubstepScale<T> == 4 ? -4 : -2) * j);
   Angles<T> a = base;
   a.tg0 *= f;
   a.tg25 *= f;
   a.fs = f;
   return a;
+}
+
+// The factor that brings the state back to its true value after kSubsteps (2 or 4) I', with a
+// U before each of them or, in the plain split, with one U before the first (plain_u) or none.
+template <typename T, int kSubsteps>
+__device__ __forceinline__ T substep_unscale(bool plain, bool plain_u) {
+  constexpr T i = kSubsteps == 4 ? T(1) / 16 : T(-1) / 4;   // (2i)^-kSubsteps
+  constexpr T u = T(1) / UScale<T>::value;
+  constexpr T un = kSubsteps == 4 ? u * u * u * u : u * u;
+  return plain ? (plain_u ? i * u : i) : i * un;
 }
 
 __device__ __forceinline__ int64_t wrap64(int64_t x, int64_t n) {
@@ -200,10 +215,11 @@ __global__ __launch_bounds__(256) void k_step1d(StepArgs<T> A) {
   if constexpr (kExt) ext = ext_angle(A, d, xw);
   const bool plain = A.plain != 0;
   cx<T> pold[5];
+  const T unscale = substep_unscale<T, 4>(plain, true);
   // one step: [U] I'_{x,b} [U] I'_{x,b} [U] I'_{x,a} [U] I'_{x,a}; the moving qubit is
-  // a compile-time parameter of each inner loop.  The four I' factors 1/4 are
-  // applied together at the end of the step (exact); U in between sees the state
-  // scaled by 4^j and compensates through its angles.
+  // a compile-time parameter of each inner loop.  The scales of the four substeps are
+  // divided out together at the end of the step (exact); U in between compensates through
+  // its angles.
 #pragma unroll 1
   for (int st = 0; st < A.steps; ++st) {
     if (A.overlap && st == A.steps - 1) {
@@ -213,14 +229,14 @@ __global__ __launch_bounds__(256) void k_step1d(StepArgs<T> A) {
 #pragma unroll 1
     for (int j = 0; j < 2; ++j) {
       if (!plain || j == 0) potential<T, kExt>(a, b, plain ? A.ang_full : substep_angles(A.ang, j), ext);
-      iprime4_lanes<T, 1>(a, b);
+      iprime_r_lanes<T, 1>(a, b);
     }
 #pragma unroll 1
     for (int j = 2; j < 4; ++j) {
       if (!plain) potential<T, kExt>(a, b, substep_angles(A.ang, j), ext);
-      iprime4_lanes<T, 0>(a, b);
+      iprime_r_lanes<T, 0>(a, b);
     }
-    scale_by(a, b, T(1.0 / 256.0));
+    scale_by(a, b, unscale);
   }
   const bool valid = lane >= H && lane < kLanes - H && x < L;
   if (valid) {
@@ -265,16 +281,12 @@ __global__ __launch_bounds__(256) void k_step1d(StepArgs<T> A) {
 // and the coefficients of W share one exchange, and the second collide takes
 // the other.  In exact arithmetic the result is the step of k_step1d.
 //
-// own' of the unnormalised collide, on either wave: with s = own + other and
-// e = own - other, own' = (s_re + e_im, s_im - e_re).  For own = a this is 2a',
-// for own = b (e = -(a - b) exactly) it is 2b'.
+// own' of the collide times (1 + i) (collide_r), on either wave: own' = own + i other.
 template <typename T>
 __device__ __forceinline__ void collide_own(cx<T> (&x)[5], const cx<T> (&y)[5]) {
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    const T sr = x[m].re + y[m].re, si = x[m].im + y[m].im;
-    const T er = x[m].re - y[m].re, ei = x[m].im - y[m].im;
-    x[m] = cx<T>{sr + ei, si - er};
+    x[m] = cx<T>{x[m].re - y[m].im, x[m].im + y[m].re};
   }
 }
 
@@ -354,6 +366,7 @@ __global__ __launch_bounds__(kLanes * kPairWaves) void k_step1d_pair(StepArgs<T>
   T ext = T(0);
   if constexpr (kExt) ext = ext_angle(A, d, xw);
   const bool plain = A.plain != 0;
+  const T unscale = substep_unscale<T, 4>(plain, true);
   cx<T> pold[5];
 #pragma unroll 1
   for (int st = 0; st < A.steps; ++st) {
@@ -369,7 +382,7 @@ __global__ __launch_bounds__(kLanes * kPairWaves) void k_step1d_pair(StepArgs<T>
 #pragma unroll 1
     for (int j = 2; j < 4; ++j) pair_substep<T, 0, kExt>(x, X, !plain, substep_angles(A.ang, j), ext);
 #pragma unroll
-    for (int m = 0; m < 5; ++m) x[m] = T(1.0 / 256.0) * x[m];
+    for (int m = 0; m < 5; ++m) x[m] = unscale * x[m];
   }
   const bool valid = real && lane >= H && lane < kLanes - H && x0 < L;
   if (valid) {
@@ -484,6 +497,7 @@ __global__ __launch_bounds__(256) void k_step1d_lanes(StepArgs<T> A) {
   T ext = T(0);
   if constexpr (kExt) ext = ext_angle(A, d, xw);
   const bool plain = A.plain != 0;
+  const T unscale = substep_unscale<T, 4>(plain, true);
   cx<T> pold[5];
 #pragma unroll 1
   for (int st = 0; st < A.steps; ++st) {
@@ -500,7 +514,7 @@ __global__ __launch_bounds__(256) void k_step1d_lanes(StepArgs<T> A) {
       lanes_substep<T, kExt, false>(x, even, !plain, substep_angles(A.ang, 2 * h + 1), ext);
     }
 #pragma unroll
-    for (int m = 0; m < 5; ++m) x[m] = T(1.0 / 256.0) * x[m];
+    for (int m = 0; m < 5; ++m) x[m] = unscale * x[m];
   }
   const bool valid = i >= H && i < kLaneTile - H && x0 < L;
   if (valid) {
@@ -540,14 +554,14 @@ __global__ __launch_bounds__(256) void k_step1d_lanes(StepArgs<T> A) {
 //   mq: the moving qubit after the second collide at row r - 2.
 template <typename T, int Q>
 __device__ __forceinline__ void y_stage_core(cx<T> (&a)[5], cx<T> (&b)[5], cx<T> (&cn)[5], cx<T> (&mq)[5]) {
-  collide2(a, b);                     // c(r)
+  collide_r(a, b);                    // c(r)
   cx<T> ta[5], tb[5];
 #pragma unroll
   for (int m = 0; m < 5; ++m) {       // t(r-1) = (c(r-1).nonq, c(r).q)   [S^T: q(y) <- q(y+1)]
     if (Q) { ta[m] = cn[m]; tb[m] = b[m]; cn[m] = a[m]; }
     else   { ta[m] = a[m]; tb[m] = cn[m]; cn[m] = b[m]; }
   }
-  collide2(ta, tb);                   // m(r-1), times 4
+  collide_r(ta, tb);                  // m(r-1), times 2i
 #pragma unroll
   for (int m = 0; m < 5; ++m) {       // out(r-1) = (m(r-1).nonq, m(r-2).q)  [S: q(y) <- q(y-1)]
     if (Q) { a[m] = ta[m]; b[m] = mq[m]; mq[m] = tb[m]; }
@@ -623,6 +637,8 @@ void k_step2d(StepArgs<T> A) {
   const bool xvalid = lane >= halo && lane < kLanes - halo && x < nx;
   const bool plain = A.plain != 0;
   const bool plain_u = A.plain_u != 0;
+  const T unscale_y = substep_unscale<T, kStages>(plain, plain_u && kPart != kYSecond);
+  const T unscale_x = substep_unscale<T, 4>(plain, false);
   // byte offsets of this lane's site in a row: the load's (periodic column) and the
   // store's (beyond any record count for a halo lane or a column past the lattice)
   const uint32_t row_bytes = (uint32_t)nx * (uint32_t)sizeof(cx<T>);
@@ -695,10 +711,10 @@ void k_step2d(StepArgs<T> A) {
     }
     // y half: stages (y,b), (y,b), (y,a), (y,a), each [U] I'_y, all four or two of them in
     // this launch; slot i of this lane's LDS holds stage i's pending rows.  The plain split
-    // applies its single U at the step's first stage.  Stage i leaves its output times 4
-    // (the factor 1/4 of its I' is deferred): all rows pass the same stages, so pending and
-    // streaming rows carry the same scale, and the U of stage i takes angles for a state
-    // times 4^i; one exact multiplication ends each half.
+    // applies its single U at the step's first stage.  Stage i leaves its output times the
+    // deferred factor of its substep (kSubstepScale): all rows pass the same stages, so pending
+    // and streaming rows carry the same scale, and the U of stage i takes angles for it; one
+    // exact multiplication ends each half.
     if constexpr (kPart != kYSecond) {
 #pragma unroll 1
       for (int i = 0; i < 2; ++i) {
@@ -721,19 +737,19 @@ void k_step2d(StepArgs<T> A) {
     const int yo = y0 - kLag + r;
     const bool done = r >= kLag;
     if (done) {
-      scale_by(a, b, T(kStages == 4 ? 1.0 / 256.0 : 1.0 / 16.0));
+      scale_by(a, b, unscale_y);
       if (kPart != kYFirst && !zp) {     // x half (not after the b stages, not in a z pass)
 #pragma unroll 1
         for (int j = 0; j < 2; ++j) {
           if (!plain) potential<T, kExt>(a, b, substep_angles(A.ang, j), er[kStages]);
-          iprime4_lanes<T, 1>(a, b);
+          iprime_r_lanes<T, 1>(a, b);
         }
 #pragma unroll 1
         for (int j = 2; j < 4; ++j) {
           if (!plain) potential<T, kExt>(a, b, substep_angles(A.ang, j), er[kStages]);
-          iprime4_lanes<T, 0>(a, b);
+          iprime_r_lanes<T, 0>(a, b);
         }
-        scale_by(a, b, T(1.0 / 256.0));
+        scale_by(a, b, unscale_x);
         if (A.overlap && yo < nrow) {
           // the state before the step at this site; in a step of several launches it is the
           // location this lane writes below (and no other lane reads or writes it), so it is

@@ -190,21 +190,21 @@ struct Angles {
 };
 
 // ---------------------------------------------------------------------------
-// Collide (sqrt SWAP on each (a_m, b_m) pair), without its factor 1/2:
-//   2 a' = (a + b) - i (a - b),   2 b' = (a + b) + i (a - b).
-// Two collides and one exact multiplication by 1/4 give C C exactly as the
-// scaled form would (scaling by powers of two commutes with rounding); the
-// fused step kernels collect the four factors 1/4 of a step's I' into one
-// multiplication by 1/256 (scale_by) and evaluate U in between with Angles::fs.
+// Collide (sqrt SWAP on each (a_m, b_m) pair), times (1 + i):
+//   (1 + i) a' = a + i b,   (1 + i) b' = b + i a,
+// since a' = ((1 - i) a + (1 + i) b) / 2 and b' likewise: two additions per amplitude, one
+// rounding, no multiplication.  An I' (two collides) then leaves the state times 2i, which
+// the fused step kernels carry from substep to substep: U commutes with a phase and sees
+// the modulus through its angles (Angles, substep_angles), and the four I' of a half-step
+// make (2i)^4 = 16, the two of half of it (2i)^2 = -4: exact real factors, divided out once.
 // ---------------------------------------------------------------------------
 template <typename T>
-QLG_HD void collide2(cx<T> (&a)[5], cx<T> (&b)[5]) {
+QLG_HD void collide_r(cx<T> (&a)[5], cx<T> (&b)[5]) {
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    const T sr = a[m].re + b[m].re, si = a[m].im + b[m].im;
-    const T dr = a[m].re - b[m].re, di = a[m].im - b[m].im;
-    a[m] = cx<T>{sr + di, si - dr};
-    b[m] = cx<T>{sr - di, si + dr};
+    const cx<T> x = a[m], y = b[m];
+    a[m] = cx<T>{x.re - y.im, x.im + y.re};
+    b[m] = cx<T>{y.re - x.im, y.im + x.re};
   }
 }
 
@@ -217,9 +217,14 @@ QLG_HD void scale_by(cx<T> (&a)[5], cx<T> (&b)[5], T f) {
   }
 }
 
+// x <- -i f x: with f = 1/2 the exact inverse of the factor 2i that collide_r leaves per I'.
 template <typename T>
-QLG_HD void scale_quarter(cx<T> (&a)[5], cx<T> (&b)[5]) {
-  scale_by(a, b, T(0.25));
+QLG_HD void unphase_by(cx<T> (&a)[5], cx<T> (&b)[5], T f) {
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    a[m] = cx<T>{f * a[m].im, -f * a[m].re};
+    b[m] = cx<T>{f * b[m].im, -f * b[m].re};
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -242,223 +247,308 @@ struct Consts {
   static constexpr double r38 = 0.6123724356957945245493210;  // sqrt(3/8)
 };
 
-// Coefficients of W for one site, computed once and applied to a and to b.
-//
-// The real spin-2 rotation d(beta) satisfies d_{-m',-m} = (-1)^{m'-m} d_{m'm}, so it
-// commutes with the flip (J x)_m = (-1)^m x_{-m} and splits into blocks on the
-// combinations x_m +- x_{-m}: applied through them it takes 21 multiply-adds per
-// complex 5-vector instead of 25.  In terms of c = cos beta, s = sin beta the block
-// entries are
-//   A = (d22 + d2-2)/2 = 1/2 - s^2/4,  B = (d22 - d2-2)/2 = (d11 + d1-1)/2 = c/2,
-//   C = (d21 + d2-1)/2 = -s/2,         E = (d21 - d2-1)/2 = -s c/2,
-//   G = (d11 - d1-1)/2 = c^2 - 1/2,
-// with d20 = sqrt(3/8) s^2, d10 = -sqrt(3/2) s c, d00 = (3 c^2 - 1)/2.
+// What the state carries after one application of `potential`: the rotation leaves it in the
+// sums and differences of the m, -m pairs, and in FP64 the factor 1/2 of the way back is left
+// to the deferred scale of the step (exact).  FP32 adds its correction to x once instead (see
+// w_apply) and keeps the scale.
 template <typename T>
-struct DBlocks {
-  T dA, dB, dC, dE, dG, d20, d10, d00;
+struct UScale {
+  static constexpr int value = sizeof(T) == 8 ? 2 : 1;
+};
+
+QLG_HD float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
+QLG_HD double fma_t(double a, double b, double c) { return fma(a, b, c); }
+
+// (cos x - 1) / x^2 and sin(x) / x as polynomials in y = x^2, for |x| <= 1/8: the first omitted
+// terms are x^10/12! and x^10/11! in FP64 (2e-18 and 2e-17 at x = 1/8) and x^6/8! and x^6/7! in
+// FP32 (1e-10 and 8e-10).
+QLG_HD void phase_series(float y, float* c, float* s) {
+  *c = fma_t(y, fma_t(y, -1.0f / 720, 1.0f / 24), -0.5f);
+  *s = fma_t(y, fma_t(y, 1.0f / 120, -1.0f / 6), 1.0f);
+}
+QLG_HD void phase_series(double y, double* c, double* s) {
+  double pc = -1.0 / 3628800.0, ps = 1.0 / 362880.0;   // -1/10!, 1/9!
+  pc = fma(y, pc, 1.0 / 40320.0);
+  ps = fma(y, ps, -1.0 / 5040.0);
+  pc = fma(y, pc, -1.0 / 720.0);
+  ps = fma(y, ps, 1.0 / 120.0);
+  pc = fma(y, pc, 1.0 / 24.0);
+  ps = fma(y, ps, -1.0 / 6.0);
+  *c = fma(y, pc, -0.5);
+  *s = fma(y, ps, 1.0);
+}
+// cos h and sin(h) / h as polynomials in y = h^2, for |h| <= 1/16 (first omitted terms
+// h^10/10! = 3e-19 and h^10/11! in FP64, h^6/6! = 8e-11 and h^6/7! in FP32).
+QLG_HD void half_angle_series(float y, float* c, float* s) {
+  *c = fma_t(y, fma_t(y, 1.0f / 24, -0.5f), 1.0f);
+  *s = fma_t(y, fma_t(y, 1.0f / 120, -1.0f / 6), 1.0f);
+}
+QLG_HD void half_angle_series(double y, double* c, double* s) {
+  double pc = 1.0 / 40320.0, ps = 1.0 / 362880.0;
+  pc = fma(y, pc, -1.0 / 720.0);
+  ps = fma(y, ps, -1.0 / 5040.0);
+  pc = fma(y, pc, 1.0 / 24.0);
+  ps = fma(y, ps, 1.0 / 120.0);
+  pc = fma(y, pc, -0.5);
+  ps = fma(y, ps, -1.0 / 6.0);
+  *c = fma(y, pc, 1.0);
+  *s = fma(y, ps, 1.0);
+}
+
+// R - I of the spin rotation R = exp(-i phi n.f), as the real 5 x 5 matrix that it is on
+//   (s2, i t2, i s1, t1, x0),   s_m = x_m + x_-m,  t_m = x_m - x_-m
+// (integer spin is a real representation, R_{-m',-m} = (-1)^{m'-m} conj R_{m'm}).  Rows 2 and 1
+// give twice the correction of the m = +-2 and +-1 pairs' sums and differences; row 0 carries
+// the factor UScale.  Names: row, then column; a trailing i marks an entry that multiplies
+// i times its column.
+//   S2 = ss22 s2 + i st22i t2 + i ss21i s1 + st21 t1 + s20 x0
+//   T2 = tt22 t2 + i ts22i s2 + i tt21i t1 + ts21 s1 + i t20i x0   and so on.
+//
+// From the Cayley-Klein parameters A = c - i Z, B = -(Y + i X) of the rotation, with
+// c = cos(phi/2) and (X, Y, Z) = sin(phi/2) n:
+//   R22 = A^4, R21 = 2 A^3 B, R20 = sqrt6 A^2 B^2, R2-1 = 2 A B^3, R2-2 = B^4,
+//   R12 = -2 A^3 B*, R11 = A^2 (1 - 4 s), R10 = sqrt6 A B (1 - 2 s), R1-1 = B^2 (3 - 4 s),
+//   R1-2 = 2 A* B^3, R02 = sqrt6 A^2 B*^2, R01 = -sqrt6 A B* (1 - 2 s), R00 = 1 - 6 s + 6 s^2,
+// s = |B|^2 = X^2 + Y^2.  A^2 = 1 - e - 2 i c Z with e = s + 2 Z^2, so that every entry of
+// R - I is formed from small quantities (relative accuracy, no cancellation against 1), the
+// direction of F is never divided out, and B = 0 (F along z) leaves every entry that couples
+// |m| to another |m'| exactly zero.
+//
+// The self-interaction is what bounds the step kernels (vector instructions).  Building this
+// matrix once per site takes about as many as the frame of F (Euler angles, d(beta), the phases
+// of each m) that stood here before; applying it takes 50 multiply-adds and 8 to 18 additions
+// per 5-vector, where the frame took 138 instructions.  With collide_r (40 additions per I'
+// instead of 80) 20 steps of 2048^2 in complex128 went from 19.7 to 15.9 ms, in complex64 with
+// every component populated from 14.2 to 10.5 ms, 50 steps of 256 uneven 1D runs from 8.1 to
+// 6.4 ms.
+template <typename T>
+struct Rot2 {
+  T ss22, st22i, ss21i, st21, s20;
+  T tt22, ts22i, tt21i, ts21, t20i;
+  T ss11, st11i, ss12i, st12, s10i;
+  T tt11, ts11i, tt12i, ts12, t10;
+  T x0s2, x0t2i, x0s1i, x0t1, x00;
 };
 
 template <typename T>
-QLG_HD DBlocks<T> d_blocks(T cb, T sb) {
-  const T r32 = T(Consts::r32), r38 = T(Consts::r38);
-  const T sb2 = sb * sb, cb2 = cb * cb, sbcb = sb * cb;
-  DBlocks<T> D;
-  D.dA = T(0.5) - T(0.25) * sb2;
-  D.dB = T(0.5) * cb;
-  D.dC = T(-0.5) * sb;
-  D.dE = T(-0.5) * sbcb;
-  D.dG = cb2 - T(0.5);
-  D.d20 = r38 * sb2;
-  D.d10 = -r32 * sbcb;
-  D.d00 = T(1.5) * cb2 - T(0.5);
-  return D;
+QLG_HD void rot2(T c, T X, T Y, T Z, Rot2<T>& M) {
+  constexpr T r6 = T(Consts::r6), r = T(UScale<T>::value);
+  const T XX = X * X;
+  const T s = fma_t(Y, Y, XX), B = fma_t(Y, Y, -XX), C = (X + X) * Y;   // B^2 = B + i C
+  const T Z2 = Z + Z;
+  const T e = fma_t(Z2, Z, s), be = -(Z2 * c), al = T(1) - e;           // A^2 = al + i be
+  // m = +-2 block: R22 - 1 = p + i q, R2-2 = u + i v
+  {
+    const T p = fma_t(e, e - T(2), -(be * be)), q = (al + al) * be;
+    const T u = fma_t(B, B, -(C * C)), v = (B + B) * C;
+    M.ss22 = p + u;
+    M.tt22 = p - u;
+    M.st22i = q - v;
+    M.ts22i = q + v;
+  }
+  // m = +-1 block: R11 - 1 = p + i q, R1-1 = u + i v
+  {
+    const T s4 = T(4) * s;
+    const T p = -fma_t(s4, al, e), q = fma_t(-s4, be, be), k = T(3) - s4;
+    const T u = k * B, v = k * C;
+    M.ss11 = p + u;
+    M.tt11 = p - u;
+    M.st11i = q - v;
+    M.ts11i = q + v;
+  }
+  // -2 A B = a1 + i a2, -2 A B* = a3 - i a4
+  const T ZX = Z * X, ZY = Z * Y;
+  const T ab1 = fma_t(c, Y, ZX), ab2 = fma_t(c, X, -ZY), ab3 = fma_t(c, Y, -ZX), ab4 = fma_t(c, X, ZY);
+  const T a1 = ab1 + ab1, a2 = ab2 + ab2, a3 = ab3 + ab3, a4 = ab4 + ab4;
+  {
+    const T aB = al + B, aD = al - B, bB = be + C, bD = be - C;
+    M.st21 = fma_t(a2, bD, -(a1 * aD));
+    M.ts21 = fma_t(a2, bB, -(a1 * aB));
+    M.ss21i = -fma_t(a1, bB, a2 * aB);
+    M.tt21i = -fma_t(a1, bD, a2 * aD);
+    M.st12 = fma_t(a4, bD, a3 * aB);
+    M.ts12 = fma_t(a4, bB, a3 * aD);
+    M.ss12i = fma_t(a3, bD, -(a4 * aB));
+    M.tt12i = fma_t(a3, bB, -(a4 * aD));
+  }
+  {
+    const T h1 = T(0.5) * r6 * a1, h2 = T(0.5) * r6 * a2;
+    M.s20 = fma_t(h1, a1, -(h2 * a2));
+    M.t20i = (h1 + h1) * a2;
+    const T h3 = T(0.25) * r * r6 * a3, h4 = T(0.25) * r * r6 * a4;
+    M.x0s2 = fma_t(h3, a3, -(h4 * a4));
+    M.x0t2i = -((h3 + h3) * a4);
+    const T k = fma_t(T(-2) * r6, s, r6);
+    M.t10 = -(k * a1);
+    M.s10i = -(k * a2);
+    const T kr = T(0.5) * r * k;
+    M.x0t1 = kr * a3;
+    M.x0s1i = -(kr * a4);
+    const T s6 = T(6) * r * s;
+    M.x00 = fma_t(s6, s, -s6);
+  }
 }
 
+// Coefficients of W for one site, computed once and applied to a and to b.
 template <typename T>
 struct WCoef {
-  cx<T> p[5];                                  // psi = a + b
-  cx<T> cs;                                    // (exp(-i th g2 n/5) - 1) / n (0/0 -> -i th g2/5)
-  cx<T> dl[5];                                 // exp(-i (th g0 n + k phi)) - 1, k = 2..-2
-  cx<T> u, u2;                                 // e^{i alpha}, e^{2 i alpha}
-  DBlocks<T> d;                                // d^2(beta) in the blocks above
+  cx<T> p[5];   // psi = a + b
+  cx<T> mu0;    // exp(-i (th g0 n + ext)) - 1
+  cx<T> cs;     // exp(-i (th g0 n + ext)) (exp(-i th g2 n/5) - 1) / n  (0/0 -> its limit)
+  Rot2<T> R;    // the spin rotation, less the identity
 };
-
-// y = d(beta)^T x and y = d(beta) x for a complex 5-vector (m = 2..-2) through the
-// blocks of WCoef: with s0 = x_2 + x_-2, t0 = x_2 - x_-2, s1 = x_1 + x_-1, t1 = x_1 - x_-1,
-//   (d^T x)_{2,-2} = (A s0 - E t1 + d20 x0) +- (B t0 - C s1),
-//   (d^T x)_{1,-1} = (C t0 + B s1) +- (E s0 + G t1 - d10 x0),
-//   (d^T x)_0      = d20 s0 + d10 t1 + d00 x0,
-//   (d x)_{2,-2}   = (A s0 + E t1 + d20 x0) +- (B t0 + C s1),
-//   (d x)_{1,-1}   = (B s1 - C t0) +- (G t1 - E s0 + d10 x0),
-//   (d x)_0        = d20 s0 - d10 t1 + d00 x0.
-template <typename T, bool kTranspose>
-QLG_HD void d_apply(const DBlocks<T>& W, const cx<T> (&x)[5], cx<T> (&y)[5]) {
-  const cx<T> s0 = x[0] + x[4], t0 = x[0] - x[4], s1 = x[1] + x[3], t1 = x[1] - x[3];
-  const T sgn = kTranspose ? T(-1) : T(1);
-  const cx<T> P = rfma(W.d20, x[2], rfma(sgn * W.dE, t1, W.dA * s0));
-  const cx<T> Q = rfma(sgn * W.dC, s1, W.dB * t0);
-  const cx<T> R = rfma(-sgn * W.dC, t0, W.dB * s1);
-  const cx<T> S = rfma(sgn * W.d10, x[2], rfma(W.dG, t1, (-sgn) * W.dE * s0));
-  y[0] = P + Q;
-  y[4] = P - Q;
-  y[1] = R + S;
-  y[3] = R - S;
-  y[2] = rfma(W.d00, x[2], rfma(-sgn * W.d10, t1, W.d20 * s0));
-}
 
 // kExt: the equation of motion carries the psi-independent term (V(x) + mu) psi_m
 // (Sec. II, "Additional terms"); ext = theta (V(x) + mu) joins the density phase.
 template <typename T, bool kExt = false>
 QLG_HD void w_coefficients(const cx<T> (&a)[5], const cx<T> (&b)[5], const Angles<T> ang, WCoef<T>& W,
                            T ext = T(0)) {
-  const T r6 = T(Consts::r6);
-  T q[5];
 #pragma unroll
-  for (int m = 0; m < 5; ++m) {
-    W.p[m] = a[m] + b[m];
-    q[m] = W.p[m].re * W.p[m].re + W.p[m].im * W.p[m].im;
-  }
-  const T n = q[0] + q[1] + q[2] + q[3] + q[4];
-  const T Fz = ang.fs * (T(2) * (q[0] - q[4]) + (q[1] - q[3]));
-  // F_x + i F_y = psi^H f_+ psi = 2 p2* p1 + sqrt6 p1* p0 + sqrt6 p0* p-1 + 2 p-1* p-2
-  const cx<T> f1 = cmulc(W.p[0], W.p[1]) + cmulc(W.p[3], W.p[4]);
-  const cx<T> f2 = cmulc(W.p[1], W.p[2]) + cmulc(W.p[2], W.p[3]);
-  const T Fx = ang.fs * (T(2) * f1.re + r6 * f2.re);
-  const T Fy = ang.fs * (T(2) * f1.im + r6 * f2.im);
-  const T Fp2 = Fx * Fx + Fy * Fy;
-  const T Fn2 = Fp2 + Fz * Fz;
-  // |F|, F_perp and their reciprocals; below `tiny` the direction is immaterial
-  // (phi ~ 0) and F is taken along z
-  const T tiny2 = sizeof(T) == 4 ? T(1e-36) : T(1e-300);   // normal in both formats
-  const bool has_F = Fn2 > tiny2, has_perp = Fp2 > tiny2;
-  // (selects around unconditional evaluations: no divergent branch)
-  const T rF = rsqrt_t(has_F ? Fn2 : T(1)), rp = rsqrt_t(has_perp ? Fp2 : T(1));
-  const T iF = has_F ? rF : T(0);
-  const T ip = has_perp ? rp : T(0);
-  const T Fn = Fn2 * iF;
-  const T Fperp = Fp2 * ip;
+  for (int m = 0; m < 5; ++m) W.p[m] = a[m] + b[m];
+  const cx<T>* p = W.p;
+  auto sq = [](cx<T> z) { return fma_t(z.re, z.re, z.im * z.im); };
+  const T q0 = sq(p[0]), q1 = sq(p[1]), q3 = sq(p[3]), q4 = sq(p[4]);
+  const T n = fma_t(p[2].re, p[2].re, fma_t(p[2].im, p[2].im, (q0 + q4) + (q1 + q3)));
+  const T Fz = fma_t(T(2), q0 - q4, q1 - q3);
+  // F_x + i F_y = psi^H f_+ psi = 2 (p2* p1 + p-1* p-2) + sqrt6 (p1* p0 + p0* p-1)
+  auto cjmac = [](cx<T> x, cx<T> y, cx<T> acc) {   // acc + conj(x) y
+    return cx<T>{fma_t(x.re, y.re, fma_t(x.im, y.im, acc.re)), fma_t(x.re, y.im, fma_t(-x.im, y.re, acc.im))};
+  };
+  auto cjmul = [](cx<T> x, cx<T> y) {              // conj(x) y
+    return cx<T>{fma_t(x.re, y.re, x.im * y.im), fma_t(x.re, y.im, -(x.im * y.re))};
+  };
+  const cx<T> f1 = cjmac(p[0], p[1], cjmul(p[3], p[4]));
+  const cx<T> f2 = cjmac(p[1], p[2], cjmul(p[2], p[3]));
+  // (th g1 / 2) F: half the rotation vector
+  const T k1 = T(0.5) * ang.tg1 * ang.fs, k2 = k1 + k1, k6 = T(Consts::r6) * k1;
+  const T Hx = fma_t(k2, f1.re, k6 * f2.re), Hy = fma_t(k2, f1.im, k6 * f2.im), Hz = k1 * Fz;
+  const T hh = fma_t(Hx, Hx, fma_t(Hy, Hy, Hz * Hz));
+  const T x0 = kExt ? fma_t(ang.tg0, n, ext) : ang.tg0 * n;   // density phase
+  const T x2 = ang.tg25 * n;                                  // singlet phase
 
-  // half-angle phases: mu = exp(-i x) - 1 = -2 sin(x/2) (sin(x/2) + i cos(x/2)).  When all
-  // three half angles of every lane are at most 1/16 (the usual case) they take the short
-  // series without a branch per lane, the singlet's sin(h)/h included.
-  T s0, c0, s1, c1, s2, c2, sinc;
-  const T h2 = T(0.5) * ang.tg25 * n;
-  const T h0 = kExt ? T(0.5) * (ang.tg0 * n + ext) : T(0.5) * ang.tg0 * n;
-  const T h1 = T(0.5) * ang.tg1 * Fn;
-  if (all_lanes(fmax(fmax(fabs(h0), fabs(h1)), fabs(h2)) <= T(0.0625))) {
-    T x0, x1;
-    sincos_short(h0, &s0, &c0, &x0);
-    sincos_short(h1, &s1, &c1, &x1);
-    sincos_short(h2, &s2, &c2, &sinc);
+  // exp(-i x) - 1 = x (x c - i s) with c = (cos x - 1)/x^2, s = sin(x)/x.  When every angle of
+  // every lane is small (the usual case) all take short series without a branch per lane.
+  T c0, s0, c2, s2, ch, sh;
+  if (all_lanes(fmax(fabs(x0), fabs(x2)) <= T(0.125) && hh <= T(1.0 / 256.0))) {
+    phase_series(x0 * x0, &c0, &s0);
+    phase_series(x2 * x2, &c2, &s2);
+    half_angle_series(hh, &ch, &sh);
   } else {
-    sincos_t(h0, &s0, &c0);
-    sincos_t(h1, &s1, &c1);
-    sincos_t(h2, &s2, &c2);
-    sinc = fabs(h2) < T(1e-4) ? T(1) - h2 * h2 * T(1.0 / 6.0) : s2 * rcp_t(h2);
+    auto general = [](T x, T* c, T* s) {   // half angles: cos x - 1 = -2 sin^2(x/2) without cancellation
+      const T h = T(0.5) * x;
+      if (fabs(h) < T(1e-4)) {
+        phase_series(x * x, c, s);
+        return;
+      }
+      T sn, cn;
+      sincos_t(h, &sn, &cn);
+      const T ih = rcp_t(h), sc = sn * ih;
+      *c = T(-0.5) * sc * sc;
+      *s = sc * cn;
+    };
+    general(x0, &c0, &s0);
+    general(x2, &c2, &s2);
+    const T h = sqrt_t(hh);
+    T sn;
+    sincos_t(h, &sn, &ch);
+    sh = h < T(1e-4) ? fma_t(hh, T(-1.0 / 6.0), T(1)) : sn * rcp_t(h);
   }
-  const cx<T> mu0{T(-2) * s0 * s0, T(-2) * s0 * c0};
-  const cx<T> mu1{T(-2) * s1 * s1, T(-2) * s1 * c1};
-  // nu_k = exp(-i k phi) - 1 for k = 2, 1, -1, -2
-  const cx<T> nu2 = T(2) * mu1 + mu1 * mu1;
-  const cx<T> mu1c = conj(mu1), nu2c = conj(nu2);
-  // E_k - 1 = exp(-i (phi0 + k phi)) - 1 = mu0 + nu_k + mu0 nu_k
-  W.dl[0] = mu0 + nu2 + mu0 * nu2;
-  W.dl[1] = mu0 + mu1 + mu0 * mu1;
-  W.dl[2] = mu0;
-  W.dl[3] = mu0 + mu1c + mu0 * mu1c;
-  W.dl[4] = mu0 + nu2c + mu0 * nu2c;
-
-  // singlet coefficient (exp(-i th g2 n/5) - 1) / n = th g2/5 * sinc(h) * (-sin h - i cos h),
-  // h = th g2 n / 10: no division by n, so empty or denormal sites stay finite
-  W.cs = cx<T>{-ang.tg25 * sinc * s2, -ang.tg25 * sinc * c2};
-
-  // frame of F: u = e^{i alpha}, cos beta, sin beta.  With F_perp = 0, beta is 0 or pi
-  // exactly, and d(beta) is taken exactly diagonal or anti-diagonal, so that components that
-  // are zero and have no source stay exactly zero.
-  const cx<T> u{has_perp ? Fx * ip : T(1), has_perp ? Fy * ip : T(0)};
-  const T cz = Fz >= T(0) ? T(1) : T(-1), cp = Fz * iF;
-  const T cf = has_perp ? cp : cz;
-  const T cb = has_F ? cf : T(1);
-  const T sb = Fperp * iF;   // 0 without F
-  W.u = u;
-  W.u2 = u * u;
-  // spin-2 Wigner small-d matrix d(beta) in the blocks of d_apply
-  W.d = d_blocks(cb, sb);
+  W.mu0 = cx<T>{x0 * x0 * c0, -(x0 * s0)};
+  // singlet coefficient (exp(-i x2) - 1) / n = th g2/5 (x2 c - i s): no division by n, so empty or
+  // denormal sites stay finite; times exp(-i x0) = 1 + mu0
+  const cx<T> cs{ang.tg25 * x2 * c2, -(ang.tg25 * s2)};
+  W.cs = cx<T>{fma_t(W.mu0.re, cs.re, fma_t(-W.mu0.im, cs.im, cs.re)),
+               fma_t(W.mu0.re, cs.im, fma_t(W.mu0.im, cs.re, cs.im))};
+  rot2(ch, sh * Hx, sh * Hy, sh * Hz, W.R);
 }
 
-// x <- exp(-i th g0 n) R P x for one 5-vector x (a or b).
+// x <- UScale exp(-i th g0 n) R P x for one 5-vector x (a or b).
 //
-// Both factors only add small corrections to x: the singlet part sv = cs (v^H x) v
-// and the rotation part Phi t.  In FP32 they are summed first and added to x once, so
-// the full-magnitude value is rounded a single time per application; rounding it
-// after each factor made the FP32 qubit norm drift systematically (6e-5 over
-// 20000 steps of the 1D two-soliton run, against 9e-7 with one rounding).  In FP64
-// that drift is some 1e9 times smaller, and y = x + sv is formed once, by five complex
-// multiply-adds, as the rotation's input and the base its correction is added to:
-// 20 instructions per vector fewer than forming sv, adding it to x, and adding it again.
+// With E = exp(-i th g0 n), R commutes with it and E P x = x + mu0 x + cs (v^H x) v (cs holds
+// E): y = E P x is formed in one pass, then R y = y + (R - I) y through the pairs' sums and
+// differences.  In FP32 the corrections mu0 x, the singlet's and the rotation's are summed
+// first and added to x once, so the full-magnitude value is rounded a single time per
+// application; rounding it after each factor made the FP32 qubit norm drift systematically
+// (6e-5 over 20000 steps of the 1D two-soliton run, against 9e-7 with one rounding).  In FP64
+// that drift is some 1e9 times smaller: the sums and differences start from y's, and the pairs
+// come back as S + T and S - T, twice their value (UScale).
 template <typename T>
 QLG_HD void w_apply(cx<T> (&x)[5], const WCoef<T>& W) {
-  const cx<T> uc = conj(W.u), u2c = conj(W.u2);
-  // singlet correction sv = cs (v^H x) v, conj(v_m) = (-1)^m psi_{-m}, v_m = (-1)^m conj(psi_{-m})
-  cx<T> s = W.p[4] * x[0];
-  s = cfma(T(-1) * W.p[3], x[1], s);
-  s = cfma(W.p[2], x[2], s);
-  s = cfma(T(-1) * W.p[1], x[3], s);
-  s = cfma(W.p[0], x[4], s);
-  const cx<T> tt = W.cs * s;
-  if constexpr (sizeof(T) == 8) {
-    cx<T> y[5];   // x + sv
-    y[0] = cfma(tt, conj(W.p[4]), x[0]);
-    y[1] = cfma(tt, T(-1) * conj(W.p[3]), x[1]);
-    y[2] = cfma(tt, conj(W.p[2]), x[2]);
-    y[3] = cfma(tt, T(-1) * conj(W.p[1]), x[3]);
-    y[4] = cfma(tt, conj(W.p[0]), x[4]);
-    // w = Phi^* y; z = (Lambda' - I) d^T w; t = d z; x = y + Phi t
-    cx<T> w[5];
-    w[0] = y[0] * W.u2;
-    w[1] = y[1] * W.u;
-    w[2] = y[2];
-    w[3] = y[3] * uc;
-    w[4] = y[4] * u2c;
-    cx<T> z[5];
-    d_apply<T, true>(W.d, w, z);
+  const cx<T>* p = W.p;
+  const Rot2<T>& M = W.R;
+  // s = v^H x, conj(v_m) = (-1)^m psi_{-m}
+  auto mac = [](cx<T> u, cx<T> w, cx<T> acc) {     // acc + u w
+    return cx<T>{fma_t(u.re, w.re, fma_t(-u.im, w.im, acc.re)), fma_t(u.re, w.im, fma_t(u.im, w.re, acc.im))};
+  };
+  auto msub = [](cx<T> u, cx<T> w, cx<T> acc) {    // acc - u w
+    return cx<T>{fma_t(-u.re, w.re, fma_t(u.im, w.im, acc.re)), fma_t(-u.re, w.im, fma_t(-u.im, w.re, acc.im))};
+  };
+  auto mul = [](cx<T> u, cx<T> w) { return cx<T>{fma_t(u.re, w.re, -(u.im * w.im)), fma_t(u.re, w.im, u.im * w.re)}; };
+  // acc + c z and acc + i c z, c real
+  auto rmac = [](T c, cx<T> z, cx<T> acc) { return cx<T>{fma_t(c, z.re, acc.re), fma_t(c, z.im, acc.im)}; };
+  auto imac = [](T c, cx<T> z, cx<T> acc) { return cx<T>{fma_t(-c, z.im, acc.re), fma_t(c, z.re, acc.im)}; };
+  cx<T> s = mul(p[4], x[0]);
+  s = msub(p[3], x[1], s);
+  s = mac(p[2], x[2], s);
+  s = msub(p[1], x[3], s);
+  s = mac(p[0], x[4], s);
+  const cx<T> tt = mul(W.cs, s);
+  // e = mu0 x + tt v, v_m = (-1)^m conj(psi_{-m}); in FP64 y = x + e
+  constexpr bool kOnce = sizeof(T) == 4;
+  auto corr = [&](cx<T> xm, cx<T> vm, bool neg) {
+    const cx<T> v = neg ? cx<T>{-vm.re, vm.im} : cx<T>{vm.re, -vm.im};
+    if constexpr (kOnce) return mac(tt, v, mul(W.mu0, xm));
+    else return mac(tt, v, mac(W.mu0, xm, xm));
+  };
+  cx<T> e[5], y[5];
+  e[0] = corr(x[0], p[4], false);
+  e[1] = corr(x[1], p[3], true);
+  e[2] = corr(x[2], p[2], false);
+  e[3] = corr(x[3], p[1], true);
+  e[4] = corr(x[4], p[0], false);
 #pragma unroll
-    for (int k = 0; k < 5; ++k) z[k] = W.dl[k] * z[k];
-    cx<T> t5[5];
-    d_apply<T, false>(W.d, z, t5);
-    x[0] = cfma(t5[0], u2c, y[0]);
-    x[1] = cfma(t5[1], uc, y[1]);
-    x[2] = y[2] + t5[2];
-    x[3] = cfma(t5[3], W.u, y[3]);
-    x[4] = cfma(t5[4], W.u2, y[4]);
-    return;
+  for (int m = 0; m < 5; ++m) y[m] = kOnce ? x[m] + e[m] : e[m];
+  const cx<T> s2 = y[0] + y[4], t2 = y[0] - y[4], s1 = y[1] + y[3], t1 = y[1] - y[3], x0 = y[2];
+  const cx<T> z{T(0), T(0)};
+  // the rows of a pair take their terms in the same order, so that s == +-t stays so exactly
+  // (a component that is zero and has no source stays zero)
+  cx<T> S2 = imac(M.st22i, t2, kOnce ? z : s2), T2 = imac(M.ts22i, s2, kOnce ? z : t2);
+  S2 = rmac(M.ss22, s2, S2);
+  T2 = rmac(M.tt22, t2, T2);
+  S2 = imac(M.ss21i, s1, S2);
+  T2 = imac(M.tt21i, t1, T2);
+  S2 = rmac(M.st21, t1, S2);
+  T2 = rmac(M.ts21, s1, T2);
+  S2 = rmac(M.s20, x0, S2);
+  T2 = imac(M.t20i, x0, T2);
+  cx<T> S1 = imac(M.st11i, t1, kOnce ? z : s1), T1 = imac(M.ts11i, s1, kOnce ? z : t1);
+  S1 = rmac(M.ss11, s1, S1);
+  T1 = rmac(M.tt11, t1, T1);
+  S1 = imac(M.ss12i, s2, S1);
+  T1 = imac(M.tt12i, t2, T1);
+  S1 = rmac(M.st12, t2, S1);
+  T1 = rmac(M.ts12, s2, T1);
+  S1 = imac(M.s10i, x0, S1);
+  T1 = rmac(M.t10, x0, T1);
+  cx<T> X0 = rmac(M.x00, x0, kOnce ? e[2] : x0 + x0);
+  X0 = rmac(M.x0s2, s2, X0);
+  X0 = imac(M.x0t2i, t2, X0);
+  X0 = imac(M.x0s1i, s1, X0);
+  X0 = rmac(M.x0t1, t1, X0);
+  if constexpr (kOnce) {
+    const T h = T(0.5);
+    x[0] = x[0] + rmac(h, S2 + T2, e[0]);
+    x[4] = x[4] + rmac(h, S2 - T2, e[4]);
+    x[1] = x[1] + rmac(h, S1 + T1, e[1]);
+    x[3] = x[3] + rmac(h, S1 - T1, e[3]);
+    x[2] = x[2] + X0;
+  } else {
+    x[0] = S2 + T2;
+    x[4] = S2 - T2;
+    x[1] = S1 + T1;
+    x[3] = S1 - T1;
+    x[2] = X0;
   }
-  cx<T> sv[5];
-  sv[0] = tt * conj(W.p[4]);
-  sv[1] = tt * (T(-1) * conj(W.p[3]));
-  sv[2] = tt * conj(W.p[2]);
-  sv[3] = tt * (T(-1) * conj(W.p[1]));
-  sv[4] = tt * conj(W.p[0]);
-  // w = Phi^* (x + sv): input of the rotation's (small) correction
-  cx<T> w[5];
-  w[0] = (x[0] + sv[0]) * W.u2;
-  w[1] = (x[1] + sv[1]) * W.u;
-  w[2] = x[2] + sv[2];
-  w[3] = (x[3] + sv[3]) * uc;
-  w[4] = (x[4] + sv[4]) * u2c;
-  // z = (Lambda' - I) d^T w
-  cx<T> z[5];
-  d_apply<T, true>(W.d, w, z);
-#pragma unroll
-  for (int k = 0; k < 5; ++k) z[k] = W.dl[k] * z[k];
-  // t = d z; x += sv + Phi t
-  cx<T> t5[5];
-  d_apply<T, false>(W.d, z, t5);
-  x[0] = x[0] + cfma(t5[0], u2c, sv[0]);
-  x[1] = x[1] + cfma(t5[1], uc, sv[1]);
-  x[2] = x[2] + (t5[2] + sv[2]);
-  x[3] = x[3] + cfma(t5[3], W.u, sv[3]);
-  x[4] = x[4] + cfma(t5[4], W.u2, sv[4]);
 }
 
 template <typename T, bool kExt = false>
