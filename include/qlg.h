@@ -97,7 +97,14 @@ typedef struct qlg_obs {
   int32_t reserved;
 } qlg_obs;
 
-/* Launch plan of the fused step; chosen by qlg_autotune or set by the caller. */
+/* Launch plan of the fused step; chosen by qlg_autotune or set by the caller.  Until then
+ * qlg_get_tuning reports the defaults (1 step per pass, 32 rows, no graph, split 0) and the
+ * library takes steps_per_pass and qubit_split (1D) or the band height (2D and 3D) from the
+ * lattice's size; small 2D and 3D lattices then run one launch per axis ("line passes": z, y, x,
+ * four substeps each, the axis along the lanes) instead of bands.  qlg_autotune times that form
+ * too; a plan it keeps in that form reports tile_rows 8.  qlg_set_tuning with another
+ * steps_per_pass, tile_rows or qubit_split than reported gives the plan as described here; one
+ * that changes use_graph alone keeps the form.  All forms compute the same step. */
 typedef struct qlg_tuning {
   int32_t steps_per_pass; /* 1D: steps fused per HBM pass, 4 S halo sites per side of each
                              tile (1..7 with 64-site tiles, 1..3 with the 32-site tiles of
@@ -268,8 +275,9 @@ qlg_status qlg_decode_records(qlg_ctx* ctx, const double* rec_host, int64_t nrec
  * split, batched or not and the total site count rounded up to a power of two; a new
  * context with the same key starts from that plan.  When the environment variable
  * QLG_TUNE_CACHE names a file, qlg_autotune also appends the plan to it as a text line
- * "key steps_per_pass tile_rows use_graph qubit_split", and qlg_init takes the last
- * in-range line with its key from the file before the process's own record. */
+ * "key steps_per_pass tile_rows use_graph qubit_split" (key ending in "|lines" for a plan of
+ * line passes), and qlg_init takes the last in-range line with its key from the file before
+ * the process's own record. */
 qlg_status qlg_set_tuning(qlg_ctx* ctx, const qlg_tuning* tuning);
 qlg_status qlg_get_tuning(const qlg_ctx* ctx, qlg_tuning* tuning);
 qlg_status qlg_autotune(qlg_ctx* ctx);

@@ -118,9 +118,17 @@ ScratchLayout scratch_layout(const Layout& L, int nbatch) {
   return s;
 }
 
+// Who chose the launch form of a context: the library's own rule (kAuto, until qlg_autotune or
+// qlg_set_tuning), or a plan of bands / of line passes (2D and 3D; 1D: kBands).
+enum class Form { kAuto, kBands, kLines };
+struct Plan {
+  qlg_tuning t;
+  Form form;
+};
+
 // Process-wide autotune cache keyed by (arch, dtype, ndim, split, size class).
 std::mutex g_tune_mu;
-std::map<std::string, qlg_tuning> g_tune_cache;
+std::map<std::string, Plan> g_tune_cache;
 
 }  // namespace
 
@@ -160,8 +168,11 @@ struct qlg_ctx {
   int32_t* d_tile2inst = nullptr;
   int32_t* d_chunk2inst = nullptr;
   int32_t* d_tile2inst_z = nullptr;   // 3D z pass
-  int32_t ntiles = 0, ntiles_z = 0;
-  qlg_tuning tuning{1, 32, 0, 0};
+  int32_t ntiles = 0, ntiles_z = 0, nline_y = 0, nline_z = 0;
+  qlg_tuning tuning{1, 32, 0, 0};  // as set, tuned or the default; qlg_get_tuning's answer
+  Form form = Form::kAuto;
+  qlg_tuning eff{1, 32, 0, 0};     // what the launches use (build_tiles)
+  bool lines = false;              // 2D and 3D: steps run as line passes
   qlg::ExtPot ext;               // external potential (caller's device array) and mu
   bool tuned = false;
   int static_dev = -1;            // device whose static scratch this context uses, or -1
@@ -191,6 +202,8 @@ struct qlg_ctx {
     g.tile2inst_z = d_tile2inst_z;
     g.ntiles = ntiles;
     g.ntiles_z = ntiles_z;
+    g.nline_y = nline_y;
+    g.nline_z = nline_z;
     g.nchunks = L.nchunks;
     g.nbatch = p.nbatch;
     return g;
@@ -219,22 +232,101 @@ void drop_graphs(qlg_ctx* c) {
   c->graphs.clear();
 }
 
+int64_t simd_count() {
+  int dev = 0, cus = 0;
+  (void)hipGetDevice(&dev);
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
+  return 4 * (int64_t)cus;
+}
+
+int64_t band_tiles(const qlg_ctx* c, int rows) {
+  int64_t t = 0;
+  for (const auto& d : c->L.inst) { int a, b; tiles_2d(d.nx, d.ny, rows, &a, &b); t += (int64_t)a * b * d.nz; }
+  return t;
+}
+
+// The launch form, band height, 1D steps per pass and qubit split of a context for which neither
+// qlg_autotune nor qlg_set_tuning has chosen.  The lines are where the measured times per step
+// cross on MI355X (1024 SIMDs; us, complex128 / complex64):
+//   1D: a lattice that leaves SIMDs idle buys time with redundant work, as many steps per pass and
+//     lanes per site as keep one wavefront per SIMD (1024 sites: 4.5 / 4.1 with the two-lane kernel
+//     at 3 steps per pass against 7.4 / 7.1 at one step; 16384: 5.1 / 4.6 at 2); with two
+//     wavefronts per SIMD 4 steps of the one-lane kernel (65536: 9.1 / 7.0 against 12.1 / 9.5),
+//     beyond that 2 (524288: 48.7 / 30.0; 1: 50.2 / 31.0, 3: 54.3 / 34.0).
+//   2D and 3D: line passes finish a launch in four substeps, a band only after its rows, but read
+//     and write the state once per axis.  Interleaved, lines against the best bands: 64^2 17 / 18
+//     against 103 / 96; 1024^2 225 / 133 against 269 / 175; 1448^2 427 / 262 against 431 / 298;
+//     2048^2 857 / 522 against 807 / 477; 3D, where bands take two passes too, 64^3 130 / 93
+//     against 189 / 175, 256^3 5360 / 2990 against 5850 / 3250.  Plain split (a seventh of the
+//     arithmetic): 512^2 43 / 26 against 57 / 45; 1024^2 170 / 69 against 117 / 76; 64^3 67 / 41
+//     against 93 / 71; 110^3 329 / 121 against 267 / 118.
+// Larger lattices run bands, of the height whose tiles cost least in rounds of one tile per SIMD
+// (a band of r rows takes r + 8 through the y half and r through the x half).
+void auto_plan(qlg_ctx* c) {
+  c->eff = c->tuning;
+  c->lines = false;
+  const int64_t nsimd = std::max<int64_t>(simd_count(), 1);
+  if (c->p.ndim == 1) {
+    auto waves = [&](int steps, int split) {
+      int64_t t = 0;
+      for (const auto& d : c->L.inst) t += tiles_1d(d.nx, steps, split);
+      return t;
+    };
+    int steps = 2, split = 0;
+    if (waves(3, 2) <= nsimd) steps = 3, split = 2;
+    else if (waves(2, 2) <= nsimd) steps = 2, split = 2;
+    else if (waves(4, 0) <= 2 * nsimd) steps = 4;
+    c->eff.steps_per_pass = steps;
+    c->eff.qubit_split = split;
+    return;
+  }
+  const int64_t sites = c->L.psi_elems / 5;
+  const bool c64 = c->p.dtype == QLG_C64, plain = c->p.split == QLG_SPLIT_PLAIN;
+  const int64_t most = plain ? (c->p.ndim == 2 ? (c64 ? 1100000 : 700000) : (c64 ? 1000000 : 500000))
+                             : (c->p.ndim == 2 ? (c64 ? 2500000 : 2000000) : int64_t(1) << 25);
+  if (sites <= most) {
+    c->lines = true;
+    c->eff.tile_rows = qlg::kLineTileRows;
+    return;
+  }
+  int64_t best = 0;
+  for (int r = kMaxTileRows; r >= kMinTileRows; --r) {
+    const int64_t cost = (band_tiles(c, r) + nsimd - 1) / nsimd * (2 * r + 8);
+    if (!best || cost < best) { best = cost; c->eff.tile_rows = r; }
+  }
+}
+
 // Rebuild the wave-tile tables for the current plan.
 qlg_status build_tiles(qlg_ctx* c) {
   std::vector<int32_t> t2i, t2i_z;
+  if (c->form == Form::kAuto) {
+    auto_plan(c);
+  } else {
+    c->eff = c->tuning;
+    c->lines = c->form == Form::kLines;
+    if (c->lines) c->eff.tile_rows = qlg::kLineTileRows;
+  }
+  const int W = qlg::line_cols(c->p.dtype);
+  c->nline_y = c->nline_z = 0;
   for (int i = 0; i < c->p.nbatch; ++i) {
     InstDesc& d = c->L.inst[i];
     d.tile_begin = (int32_t)t2i.size();
     if (c->p.ndim == 1) {
-      d.ntx = tiles_1d(d.nx, c->tuning.steps_per_pass, c->tuning.qubit_split);
+      d.ntx = tiles_1d(d.nx, c->eff.steps_per_pass, c->eff.qubit_split);
       d.nty = 1;
     } else {
-      tiles_2d(d.nx, d.ny, c->tuning.tile_rows, &d.ntx, &d.nty);
+      tiles_2d(d.nx, d.ny, c->eff.tile_rows, &d.ntx, &d.nty);
     }
     for (int64_t k = 0; k < (int64_t)d.ntx * d.nty * d.nz; ++k) t2i.push_back(i);
-    if (c->p.ndim == 3) {
+    if (c->lines) {
+      const int32_t ncol = (d.nx + W - 1) / W;
+      d.line_y = c->nline_y;
+      d.line_z = c->nline_z;
+      c->nline_y += ncol * ((d.ny + qlg::kValid2D - 1) / qlg::kValid2D) * d.nz;
+      if (c->p.ndim == 3) c->nline_z += ncol * ((d.nz + qlg::kValid2D - 1) / qlg::kValid2D) * d.ny;
+    } else if (c->p.ndim == 3) {
       d.tile_begin_z = (int32_t)t2i_z.size();
-      tiles_z(d.nx, d.nz, c->tuning.tile_rows, &d.ntx_z, &d.ntz);
+      tiles_z(d.nx, d.nz, c->eff.tile_rows, &d.ntx_z, &d.ntz);
       for (int64_t k = 0; k < (int64_t)d.ntx_z * d.ntz * d.ny; ++k) t2i_z.push_back(i);
     }
   }
@@ -270,11 +362,13 @@ double angle_scale(const qlg_ctx* c) {   // interleaved theta = eps^2 / (4 d)
   return c->p.eps * c->p.eps / (4.0 * c->p.ndim);
 }
 
-// Whether one step leaves the state in the copy it started from: a 3D step (its z pass
+// Whether one pass leaves the state in the copy it started from: a 3D step (its z pass
 // from `in` to `out`, its y-x pass back), and a 2D step whose y half is split over two
-// launches (the same way).  Otherwise a pass writes the other copy.
-bool step_returns(const qlg_ctx* c) {
-  return c->p.ndim == 3 || (c->p.ndim == 2 && c->tuning.qubit_split == 1);
+// launches or that runs as two line passes (the same way).  Otherwise a pass writes the
+// other copy, as does a 3D step of three line passes (one that records the overlap has two).
+bool pass_returns(const qlg_ctx* c, bool overlap) {
+  if (c->p.ndim == 3) return !c->lines || overlap;
+  return c->p.ndim == 2 && (c->lines || c->eff.qubit_split == 1);
 }
 
 // One pass of the fused step from `in` to `out` (1D: `steps` steps; 2D: one step).
@@ -282,7 +376,9 @@ bool step_returns(const qlg_ctx* c) {
 // alternate between `in` and `out`, ending in `in`: 3D the z pass (one launch, or two with
 // the split) and the y-x pass (one or two), 2D the two halves of the y half, the second
 // with the x half; with keep_state (timing runs) every launch reads `in` and writes `out`,
-// leaving `in` unchanged.  ev0 / ev1 are stamped at the start of the first and the end of
+// leaving `in` unchanged.  A plan of line passes runs one launch per axis (z, y, x); in 3D the
+// third would overwrite nothing it needs but the second the state before the step, so the step
+// that records the overlap runs its y and x axes as one band launch.  ev0 / ev1 are stamped at the start of the first and the end of
 // the last kernel.
 hipError_t launch_pass(qlg_ctx* c, int steps, bool overlap, void* in, void* out, hipEvent_t ev0 = nullptr,
                        hipEvent_t ev1 = nullptr, bool keep_state = false) {
@@ -293,25 +389,34 @@ hipError_t launch_pass(qlg_ctx* c, int steps, bool overlap, void* in, void* out,
   const double tg0 = th * c->p.g0, tg1 = th * c->p.g1, tg25 = th * c->p.g2 / 5.0;
   qlg::ExtPot ext = c->ext;
   ext.theta = th;
-  const int rows = c->tuning.tile_rows;
+  const int rows = c->eff.tile_rows;
   const int dt = c->p.dtype;
   if (c->p.ndim == 1)
-    return qlg::launch_step1d(dt, steps, c->tuning.qubit_split, plain, overlap, in, out, g, tg0, tg1, tg25, ext,
+    return qlg::launch_step1d(dt, steps, c->eff.qubit_split, plain, overlap, in, out, g, tg0, tg1, tg25, ext,
                               ov, c->stream, ev0, ev1);
   const double ff = c->p.ndim == 2 ? 8.0 : 12.0;
   // A 3D step over four launches overwrites `in` (the state before the step) with its second
   // launch, so a step that records the overlap with that state runs as two launches.  Both
   // forms compute the same numbers: the split stores the state between its launches at its
   // true scale, an exact power-of-two rescaling of the one-launch form's intermediate.
-  const bool ysplit = c->tuning.qubit_split == 1 && !(c->p.ndim == 3 && overlap);
-  if (c->p.ndim == 2 && !ysplit)
+  const bool ysplit = !c->lines && c->eff.qubit_split == 1 && !(c->p.ndim == 3 && overlap);
+  if (c->p.ndim == 2 && !ysplit && !c->lines)
     return qlg::launch_step2d(dt, plain, overlap, rows, false, true, qlg::kWhole, ff, in, out, in, g, tg0, tg1,
                               tg25, ext, ov, c->stream, ev0, ev1);
   // the launches of one step: (z pass, part, applies the plain U, records the overlap)
-  struct L { bool zpass; int part; bool plain_u; bool last; };
+  // axis: of a line pass, or -1 for a band launch
+  struct L { bool zpass; int part; bool plain_u; bool last; int axis = -1; };
   L seq[4];
   int n = 0;
-  if (c->p.ndim == 3) {
+  if (c->lines) {
+    if (c->p.ndim == 3) seq[n++] = {false, qlg::kWhole, true, false, 2};
+    if (c->p.ndim == 3 && overlap) {
+      seq[n++] = {false, qlg::kWhole, false, true};
+    } else {
+      seq[n++] = {false, qlg::kWhole, c->p.ndim == 2, false, 1};
+      seq[n++] = {false, qlg::kWhole, false, true, 0};
+    }
+  } else if (c->p.ndim == 3) {
     if (ysplit) {
       seq[n++] = {true, qlg::kYFirst, true, false};
       seq[n++] = {true, qlg::kYSecond, false, false};
@@ -322,16 +427,19 @@ hipError_t launch_pass(qlg_ctx* c, int steps, bool overlap, void* in, void* out,
   if (ysplit) {
     seq[n++] = {false, qlg::kYFirst, c->p.ndim == 2, false};
     seq[n++] = {false, qlg::kYSecond, false, true};
-  } else {
+  } else if (!c->lines) {
     seq[n++] = {false, qlg::kWhole, false, true};
   }
   void* src = in;
   void* dst = out;
   for (int k = 0; k < n; ++k) {
     const L& l = seq[k];
-    hipError_t e = qlg::launch_step2d(dt, plain, l.last && overlap, rows, l.zpass, l.plain_u, l.part, ff, src,
-                                      dst, in, g, tg0, tg1, tg25, ext, ov, c->stream, k == 0 ? ev0 : nullptr,
-                                      k == n - 1 ? ev1 : nullptr);
+    const hipEvent_t f0 = k == 0 ? ev0 : nullptr, f1 = k == n - 1 ? ev1 : nullptr;
+    hipError_t e = l.axis >= 0
+                       ? qlg::launch_line(dt, l.axis, plain, l.last && overlap, l.plain_u, ff, src, dst, in, g, tg0,
+                                          tg1, tg25, ext, ov, c->stream, f0, f1)
+                       : qlg::launch_step2d(dt, plain, l.last && overlap, rows, l.zpass, l.plain_u, l.part, ff, src,
+                                            dst, in, g, tg0, tg1, tg25, ext, ov, c->stream, f0, f1);
     if (e != hipSuccess) return e;
     if (!keep_state) std::swap(src, dst);
   }
@@ -341,7 +449,7 @@ hipError_t launch_pass(qlg_ctx* c, int steps, bool overlap, void* in, void* out,
 // Enqueue nsteps as passes of steps_per_pass (1D) or single steps (2D), ping-ponging
 // between the two copies.  The last pass records the overlap partials.
 qlg_status enqueue_steps(qlg_ctx* c, int64_t nsteps, int* cur, bool timed) {
-  const int S = c->p.ndim == 1 ? c->tuning.steps_per_pass : 1;
+  const int S = c->p.ndim == 1 ? c->eff.steps_per_pass : 1;
   int64_t left = nsteps;
   int64_t launch = 0;
   while (left > 0) {
@@ -354,7 +462,7 @@ qlg_status enqueue_steps(qlg_ctx* c, int64_t nsteps, int* cur, bool timed) {
     }
     hipError_t e = launch_pass(c, s, last, c->copy(*cur), c->copy(1 - *cur), e0, e1);
     if (e != hipSuccess) return hip_check(c, e, "step kernel launch");
-    if (!step_returns(c)) *cur = 1 - *cur;
+    if (!pass_returns(c, last)) *cur = 1 - *cur;
     left -= s;
     ++launch;
   }
@@ -394,7 +502,8 @@ const char* tuning_error(const qlg_ctx* c, const qlg_tuning& n) {
 // names a file, qlg_autotune appends "key steps_per_pass tile_rows use_graph qubit_split" to
 // it, and a new context takes the plan of the last line with its key (a line with a plan
 // that is out of range for the context is ignored).  Read before the process-wide cache.
-bool tune_file_lookup(const qlg_ctx* c, const std::string& key, qlg_tuning* out) {
+// A plan of line passes is stored under its key with "|lines" after it.
+bool tune_file_lookup(const qlg_ctx* c, const std::string& key, Plan* out) {
   const char* path = std::getenv("QLG_TUNE_CACHE");
   if (!path || !*path) return false;
   FILE* f = std::fopen(path, "r");
@@ -403,20 +512,23 @@ bool tune_file_lookup(const qlg_ctx* c, const std::string& key, qlg_tuning* out)
   char k[200];
   qlg_tuning t{};
   while (std::fscanf(f, "%199s %d %d %d %d", k, &t.steps_per_pass, &t.tile_rows, &t.use_graph,
-                     &t.qubit_split) == 5)
-    if (key == k && !tuning_error(c, t)) { *out = t; found = true; }
+                     &t.qubit_split) == 5) {
+    const bool lines = c->p.ndim >= 2 && key + "|lines" == k;
+    if ((lines || key == k) && !tuning_error(c, t)) { *out = Plan{t, lines ? Form::kLines : Form::kBands}; found = true; }
+  }
   std::fclose(f);
-  if (found && c->p.ndim == 1) out->tile_rows = 0;
-  if (found) out->use_graph = out->use_graph ? 1 : 0;
+  if (found && c->p.ndim == 1) out->t.tile_rows = 0;
+  if (found) out->t.use_graph = out->t.use_graph ? 1 : 0;
   return found;
 }
 
-void tune_file_store(const std::string& key, const qlg_tuning& t) {
+void tune_file_store(const std::string& key, const Plan& p) {
+  const qlg_tuning& t = p.t;
   const char* path = std::getenv("QLG_TUNE_CACHE");
   if (!path || !*path) return;
   FILE* f = std::fopen(path, "a");
   if (!f) return;
-  std::fprintf(f, "%s %d %d %d %d\n", key.c_str(), t.steps_per_pass, t.tile_rows, t.use_graph, t.qubit_split);
+  std::fprintf(f, "%s%s %d %d %d %d\n", key.c_str(), p.form == Form::kLines ? "|lines" : "", t.steps_per_pass, t.tile_rows, t.use_graph, t.qubit_split);
   std::fclose(f);
 }
 
@@ -515,13 +627,17 @@ static qlg_status init_ctx(const qlg_params* p, void* state_dev, size_t state_by
   {
     const std::string key = tune_key(c);
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    qlg_tuning t{};
-    if (tune_file_lookup(c, key, &t)) {
-      c->tuning = t;
-      c->tuned = true;
-    } else {
+    Plan t{};
+    bool found = tune_file_lookup(c, key, &t);
+    if (!found) {
       auto it = g_tune_cache.find(key);
-      if (it != g_tune_cache.end()) { c->tuning = it->second; c->tuned = true; }
+      found = it != g_tune_cache.end();
+      if (found) t = it->second;
+    }
+    if (found) {
+      c->tuning = t.t;
+      c->form = t.form;
+      c->tuned = true;
     }
   }
   s = build_tiles(c);
@@ -707,7 +823,7 @@ qlg_status qlg_step(qlg_ctx* c, int64_t nsteps) {
   if (s) return s;
   if (nsteps < 0) return fail(c, QLG_ERR_ARG, "nsteps must be >= 0");
   if (nsteps == 0) return QLG_OK;
-  const int S = c->p.ndim == 1 ? c->tuning.steps_per_pass : 1;
+  const int S = c->p.ndim == 1 ? c->eff.steps_per_pass : 1;
   const int64_t launches = (nsteps + S - 1) / S;
   if (c->timing) {
     const size_t need = 2 * (size_t)std::min<int64_t>(launches, 4096);
@@ -756,7 +872,7 @@ qlg_status qlg_step(qlg_ctx* c, int64_t nsteps) {
     }
     s = hip_check(c, hipGraphLaunch(it->second, c->stream), "graph launch");
     if (s) return s;
-    if (launches % 2 && !step_returns(c)) c->cur = 1 - c->cur;
+    if (((launches - 1) % 2 && !pass_returns(c, false)) != !pass_returns(c, true)) c->cur = 1 - c->cur;
   } else {
     int cur = c->cur;
     s = enqueue_steps(c, nsteps, &cur, false);
@@ -814,6 +930,10 @@ qlg_status qlg_set_tuning(qlg_ctx* c, const qlg_tuning* t) {
   if (const char* why = tuning_error(c, n)) return fail(c, QLG_ERR_ARG, why);
   if (c->p.ndim == 1) n.tile_rows = 0;
   n.use_graph = n.use_graph ? 1 : 0;
+  // a call that changes nothing but use_graph keeps the launch form
+  if (n.steps_per_pass != c->tuning.steps_per_pass || n.tile_rows != c->tuning.tile_rows ||
+      n.qubit_split != c->tuning.qubit_split)
+    c->form = Form::kBands;
   c->tuning = n;
   return build_tiles(c);
 }
@@ -832,25 +952,18 @@ qlg_status qlg_autotune(qlg_ctx* c) {
   // wins, so that timing noise does not flip the plan (fewer launches first, then the
   // one-lane-per-site kernel before the split ones; 2D and 3D: the whole y half in one
   // launch before the split one, taller bands first).
-  std::vector<qlg_tuning> cand;
+  std::vector<Plan> cand;
   if (c->p.ndim == 1) {
     for (int S = kMaxSteps1D; S >= 1; --S)
       for (int split = 0; split <= 2; ++split)
         if (S <= (split == 0 ? kMaxSteps1D : split == 1 ? kTunePairSteps : kMaxStepsLanes))
-          cand.push_back(qlg_tuning{S, 0, c->tuning.use_graph, split});
+          cand.push_back(Plan{qlg_tuning{S, 0, c->tuning.use_graph, split}, Form::kBands});
   } else {
     // powers of two, plus the smallest band heights whose tile count fits k waves per SIMD
     // (k = 1..4): fewer halo rows without a tail of SIMDs that hold one wave more
     std::vector<int> rows = {16, 32, 64, 128};
-    int dev = 0, cus = 0;
-    (void)hipGetDevice(&dev);
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
-    const int64_t nsimd = 4 * (int64_t)cus;
-    auto ntiles = [&](int r) {
-      int64_t t = 0;
-      for (const auto& d : c->L.inst) { int a, b; tiles_2d(d.nx, d.ny, r, &a, &b); t += (int64_t)a * b * d.nz; }
-      return t;
-    };
+    const int64_t nsimd = simd_count();
+    auto ntiles = [&](int r) { return band_tiles(c, r); };
     for (int k = 1; k <= 4 && nsimd > 0; ++k) {
       int r = kMinTileRows;
       while (r < kMaxTileRows && ntiles(r) > k * nsimd) ++r;
@@ -858,14 +971,17 @@ qlg_status qlg_autotune(qlg_ctx* c) {
     }
     std::sort(rows.begin(), rows.end(), [](int x, int y) { return x > y; });
     for (int split = 0; split <= 1; ++split)
-      for (int r : rows) cand.push_back(qlg_tuning{1, r, c->tuning.use_graph, split});
+      for (int r : rows) cand.push_back(Plan{qlg_tuning{1, r, c->tuning.use_graph, split}, Form::kBands});
+    cand.push_back(Plan{qlg_tuning{1, qlg::kLineTileRows, c->tuning.use_graph, 0}, Form::kLines});
   }
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess) return fail(c, QLG_ERR_DEVICE, "event create");
   if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return fail(c, QLG_ERR_DEVICE, "event create"); }
   std::vector<double> per_step_ms;
-  for (const auto& t : cand) {
+  for (const auto& pl : cand) {
+    const qlg_tuning& t = pl.t;
     c->tuning = t;
+    c->form = pl.form;
     if ((s = build_tiles(c))) break;
     const int S = c->p.ndim == 1 ? t.steps_per_pass : 1;
     // passes read the current copy and write the other one without swapping: the state is
@@ -913,10 +1029,11 @@ qlg_status qlg_autotune(qlg_ctx* c) {
   if (s) return s;
   if (per_step_ms.empty()) return fail(c, QLG_ERR_STATE, "autotune: no candidate plan");
   const double best = *std::min_element(per_step_ms.begin(), per_step_ms.end());
-  qlg_tuning best_t = cand[0];
+  Plan best_t = cand[0];
   for (size_t k = 0; k < cand.size(); ++k)
     if (per_step_ms[k] <= 1.02 * best) { best_t = cand[k]; break; }
-  c->tuning = best_t;
+  c->tuning = best_t.t;
+  c->form = best_t.form;
   c->tuned = true;
   {
     const std::string key = tune_key(c);

@@ -781,6 +781,171 @@ void k_step2d(StepArgs<T> A) {
 }
 
 // ---------------------------------------------------------------------------
+// 2D and 3D step as line passes: the four substeps of one axis per launch, that axis along the lanes
+// ---------------------------------------------------------------------------
+// A wavefront takes 64 consecutive sites of a line along the axis, 56 interior and 4 halo on each
+// side (four I' of radius one), and runs the axis' four substeps in registers with lane moves: no
+// row pipeline, so a launch lasts four substeps where a band of R rows lasts R + 8 of them.  A step
+// is one launch per axis (z, y, x), the state read and written once per launch: twice (three
+// times) the HBM traffic of a band launch, for 64/56 of the arithmetic instead of
+// 64/56 (R + 8)/R in the row pipeline.  For lattices that cannot give every SIMD a tall band, and
+// where the extra traffic stays in the caches (qlg_api.cpp chooses).
+
+// Four substeps [U] I' with the axis along the lanes (plain split: U before the first one, in the
+// launch that applies the step's single U).
+template <typename T, bool kExt>
+__device__ __forceinline__ void line_substeps(const StepArgs<T>& A, cx<T> (&a)[5], cx<T> (&b)[5], T ext) {
+  const bool plain = A.plain != 0, plain_u = A.plain_u != 0;
+#pragma unroll 1
+  for (int j = 0; j < 2; ++j) {
+    if (!plain || (j == 0 && plain_u))
+      potential<T, kExt>(a, b, plain ? A.ang_full : substep_angles(A.ang, j), ext);
+    iprime_r_lanes<T, 1>(a, b);
+  }
+#pragma unroll 1
+  for (int j = 2; j < 4; ++j) {
+    if (!plain) potential<T, kExt>(a, b, substep_angles(A.ang, j), ext);
+    iprime_r_lanes<T, 0>(a, b);
+  }
+  scale_by(a, b, substep_unscale<T, 4>(plain, plain_u));
+}
+
+// Lines along x: a workgroup takes kLineRows (or half of them, to fill the chip with smaller
+// workgroups) rows of one 56-column tile, one row per wavefront.  The tiles are those of the
+// 8-row band table, one overlap partial each; a launch that records the overlap runs the
+// whole tile in one workgroup and sums its wavefronts in LDS.
+constexpr int kLineRows = 8;
+template <typename T, bool kExt>
+__global__ __launch_bounds__(kLanes * kLineRows) void k_line_x(StepArgs<T> A) {
+  __shared__ double red[2][kLineRows];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & (kLanes - 1);
+  const int nw = blockDim.x / kLanes, parts = kLineRows / nw;   // workgroups per tile
+  const int blk = xcd_contiguous_block(blockIdx.x, gridDim.x);
+  const int w = blk / parts;
+  const InstDesc d = A.inst[A.tile2inst[w]];
+  const int t = w - d.tile_begin;
+  const int tx = t % d.ntx, tb = t / d.ntx;
+  const int y = (tb % d.nty) * kLineRows + (blk % parts) * nw + wv, plane = tb / d.nty;
+  double ore = 0.0, oim = 0.0;
+  if (y < d.ny) {   // wavefront-uniform
+    const int x = tx * kValid2D - kHalo2D + lane;
+    const int xw = (int)wrap64(x, d.nx);
+    const bool own = lane >= kHalo2D && lane < kLanes - kHalo2D && x < d.nx;
+    const int64_t row = ((int64_t)plane * d.ny + y) * d.nx;
+    const cx<T>* src = A.in + d.off + row + xw;
+    cx<T> a[5], b[5];
+#pragma unroll
+    for (int m = 0; m < 5; ++m) {
+      a[m] = src[m * d.stride];
+      b[m] = src[(5 + m) * d.stride];
+    }
+    T ext = T(0);
+    if constexpr (kExt) ext = ext_angle(A, d, row + xw);
+    line_substeps<T, kExt>(A, a, b, ext);
+    if (own) {
+      const int64_t s = d.off + row + x;
+      if (A.overlap) {
+        // the state before the step: the location this lane writes below, and no other lane reads
+#pragma unroll
+        for (int m = 0; m < 5; ++m) {
+          const cx<T> c = cmulc(a[m] + b[m], A.prev[s + m * d.stride] + A.prev[s + (5 + m) * d.stride]);
+          ore += (double)c.re;
+          oim += (double)c.im;
+        }
+        asm volatile("" ::: "memory");   // prev may be out: its loads stay before the stores
+      }
+#pragma unroll
+      for (int m = 0; m < 5; ++m) {
+        A.out[s + m * d.stride] = a[m];
+        A.out[s + (5 + m) * d.stride] = b[m];
+      }
+    }
+  }
+  if (!A.overlap) return;
+  ore = wave_sum(ore);
+  oim = wave_sum(oim);
+  if (lane == 0) {
+    red[0][wv] = ore;
+    red[1][wv] = oim;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    double s = 0.0;
+    for (int j = 0; j < kLineRows; ++j) s += red[threadIdx.x][j];
+    A.ovpart[2 * w + threadIdx.x] = s;
+  }
+}
+
+// Lines along y or z: a workgroup takes kLineCols neighbouring columns (64 bytes of a row) of one
+// 56-row tile, one column per wavefront.  The tile, 64 rows with halo x kLineCols columns x 10
+// planes, is read and written along x and turned in LDS; rows are padded by one element, so that
+// neither side has bank conflicts.
+template <typename T>
+constexpr int kLineCols = 64 / (int)sizeof(cx<T>);
+template <typename T, bool kExt>
+__global__ __launch_bounds__(kLanes * kLineCols<T>) void k_line_yz(StepArgs<T> A, int nbatch) {
+  constexpr int W = kLineCols<T>;
+  __shared__ cx<T> buf[10][kLanes][W + 1];
+  const bool zp = A.zpass != 0;
+  // the instance is the last one whose first group is not beyond this one
+  const int grp = xcd_contiguous_block(blockIdx.x, gridDim.x);
+  int lo = 0, hi = nbatch;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if ((zp ? A.inst[mid].line_z : A.inst[mid].line_y) <= grp) lo = mid;
+    else hi = mid;
+  }
+  const InstDesc d = A.inst[lo];
+  const int n = zp ? d.nz : d.ny;   // extent along the lines
+  const int64_t rstride = zp ? (int64_t)d.nx * d.ny : (int64_t)d.nx;
+  const int64_t pstride = zp ? (int64_t)d.nx : (int64_t)d.nx * d.ny;
+  const int t = grp - (zp ? d.line_z : d.line_y);
+  const int ncol = (d.nx + W - 1) / W, ntile = (n + kValid2D - 1) / kValid2D;
+  const int gx = t % ncol, tr = t / ncol;
+  const int r0 = (tr % ntile) * kValid2D - kHalo2D, plane = tr / ntile;
+  const int64_t base = d.off + plane * pstride;
+  // loads and stores: this thread's element of the tile
+  const int er = threadIdx.x / W, ec = threadIdx.x % W;
+  const int ex = gx * W + ec, ey = r0 + er;
+  const bool ex_ok = ex < d.nx;
+  {
+    const cx<T>* src = A.in + base + wrap64(ey, n) * rstride + (ex_ok ? ex : d.nx - 1);
+    cx<T> v[10];
+#pragma unroll
+    for (int p = 0; p < 10; ++p) v[p] = src[p * d.stride];
+#pragma unroll
+    for (int p = 0; p < 10; ++p) buf[p][er][ec] = v[p];
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & (kLanes - 1), wv = threadIdx.x >> 6;
+  cx<T> a[5], b[5];
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    a[m] = buf[m][lane][wv];
+    b[m] = buf[5 + m][lane][wv];
+  }
+  T ext = T(0);
+  if constexpr (kExt) {
+    const int cxw = gx * W + wv < d.nx ? gx * W + wv : d.nx - 1;
+    ext = ext_angle(A, d, plane * pstride + wrap64(r0 + lane, n) * rstride + cxw);
+  }
+  line_substeps<T, kExt>(A, a, b, ext);
+  // each wavefront writes back the column it read
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    buf[m][lane][wv] = a[m];
+    buf[5 + m][lane][wv] = b[m];
+  }
+  __syncthreads();
+  if (er >= kHalo2D && er < kLanes - kHalo2D && ey < n && ex_ok) {
+    cx<T>* dst = A.out + base + ey * rstride + ex;
+#pragma unroll
+    for (int p = 0; p < 10; ++p) dst[p * d.stride] = buf[p][er][ec];
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Elementwise layout kernels (one thread per site, 256-site chunks per instance)
 // ---------------------------------------------------------------------------
 struct SiteRef {
@@ -1013,13 +1178,13 @@ static StepArgs<T> step_args(const void* in, void* out, const LaunchGeom& g, dou
 }
 
 // Launch `kernel`; with events, the dispatch packet stamps them at kernel start and end.
-template <typename K, typename A>
+template <typename K, typename... A>
 static void launch_timed(K kernel, dim3 grid, dim3 block, size_t lds, hipStream_t st, hipEvent_t ev0,
-                         hipEvent_t ev1, A args) {
+                         hipEvent_t ev1, A... args) {
   if (ev0 || ev1)
-    hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, st, ev0, ev1, 0u, args);
+    hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, st, ev0, ev1, 0u, args...);
   else
-    hipLaunchKernelGGL(kernel, grid, block, lds, st, args);
+    hipLaunchKernelGGL(kernel, grid, block, lds, st, args...);
 }
 
 hipError_t launch_step1d(int dtype, int steps, int split, bool plain, bool overlap, const void* in, void* out,
@@ -1115,6 +1280,40 @@ hipError_t launch_step2d(int dtype, bool plain, bool overlap, int tile_rows, boo
                                   tg0, tg1, tg25, ext, ovpart, st, ev0, ev1);
   return launch_step2d_t<double>(plain, overlap, tile_rows, zpass, plain_u, part, full_factor, in, out, prev, g,
                                  tg0, tg1, tg25, ext, ovpart, st, ev0, ev1);
+}
+
+template <typename T>
+static hipError_t launch_line_t(int axis, bool plain, bool overlap, bool plain_u, double full_factor, const void* in,
+                                void* out, const void* prev, const LaunchGeom& g, double tg0, double tg1, double tg25,
+                                const ExtPot& ext, double* ovpart, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  auto args = step_args<T>(in, out, g, tg0, tg1, tg25, full_factor, ext, ovpart, 1, kLineRows, plain, overlap);
+  args.prev = (const cx<T>*)prev;
+  args.plain_u = plain_u ? 1 : 0;
+  args.zpass = axis == 2 ? 1 : 0;
+  if (axis == 0) {
+    const int nw = overlap ? kLineRows : kLineRows / 2;
+    const dim3 grid(g.ntiles * (kLineRows / nw)), block(kLanes * nw);
+    if (ext.on()) launch_timed(k_line_x<T, true>, grid, block, 0, st, ev0, ev1, args);
+    else launch_timed(k_line_x<T, false>, grid, block, 0, st, ev0, ev1, args);
+    return hipGetLastError();
+  }
+  const dim3 grid(axis == 2 ? g.nline_z : g.nline_y), block(kLanes * kLineCols<T>);
+  if (ext.on()) launch_timed(k_line_yz<T, true>, grid, block, 0, st, ev0, ev1, args, g.nbatch);
+  else launch_timed(k_line_yz<T, false>, grid, block, 0, st, ev0, ev1, args, g.nbatch);
+  return hipGetLastError();
+}
+
+hipError_t launch_line(int dtype, int axis, bool plain, bool overlap, bool plain_u, double full_factor, const void* in,
+                       void* out, const void* prev, const LaunchGeom& g, double tg0, double tg1, double tg25,
+                       const ExtPot& ext, double* ovpart, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  static_assert(kLineCols<float> == line_cols(0) && kLineCols<double> == line_cols(1), "columns per line group");
+  static_assert(kLineRows == kLineTileRows, "rows of an x tile");
+  if (axis < 0 || axis > 2 || (axis == 2 && g.nline_z == 0) || (axis == 1 && g.nline_y == 0)) return hipErrorInvalidValue;
+  if (dtype == 0)
+    return launch_line_t<float>(axis, plain, overlap, plain_u, full_factor, in, out, prev, g, tg0, tg1, tg25, ext,
+                                ovpart, st, ev0, ev1);
+  return launch_line_t<double>(axis, plain, overlap, plain_u, full_factor, in, out, prev, g, tg0, tg1, tg25, ext,
+                               ovpart, st, ev0, ev1);
 }
 
 #define QLG_ELEMWISE(NAME, KERNEL, SRC_T, DST_T)                                                    \
