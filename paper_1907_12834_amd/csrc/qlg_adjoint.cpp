@@ -4,7 +4,7 @@
 // Reverse sweep over a recorded run of nsteps with a checkpoint every K steps:
 //   for each segment, last to first:
 //     recompute, from the segment's checkpoint, the input of every self-interaction substep of
-//     its steps (a chain of per-substep kernels, the four x substeps of a step in one);
+//     its steps (one launch per axis and step);
 //     for each step of the segment, last to first, and each substep k, last to first:
 //       lambda <- I'_k^H lambda          (exact inverse of the unitary kinetic factor)
 //       lambda <- (dU/dz)^H lambda       (FP64 Jacobian at the recomputed substep input)
@@ -30,7 +30,7 @@ struct Sizes {
   int nsub = 4;        // substeps per step
   int nrec = 4;        // recorded self-interaction inputs per step (nsub, or 1 for the plain split)
   int64_t nchunks = 0; // 256-site chunks of the per-site kernels
-  int64_t nx4 = 0;     // wavefronts of the fused x substeps (56 columns of one row each)
+  int64_t nx = 0, nrecg[2] = {0, 0}, nadjg[2] = {0, 0};   // x tiles, y and z groups of the line passes
   int64_t nparts = 0;  // dg partials (3 doubles each) of one step's reverse sweep
   int64_t part_steps = 1;  // steps whose dg partials are kept before they are summed
   size_t off_zrec = 0, off_y = 0, off_lam = 0, off_part = 0, off_xpre = 0, off_acc = 0, off_red = 0;
@@ -40,17 +40,17 @@ struct Sizes {
 
 size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
-// dg partials per chunk of the fused per-site substep kernel (one per wavefront)
-constexpr int64_t kSubAdjParts = qlg::kChunk / qlg::kLanes;
-
-// wavefronts of k_adj_x4: ceil(nx / 56) per row of each instance
-int64_t adjoint_x4_waves(const qlg_params* p) {
-  int64_t n = 0;
+// x tiles, and y and z groups of `cols` columns, of the line passes
+void adjoint_lines(const qlg_params* p, int cols, int64_t* x, int64_t (&yz)[2]) {
+  *x = yz[0] = yz[1] = 0;
+  constexpr int V = qlg::kValid2D;
   for (int i = 0; i < p->nbatch; ++i) {
-    const int64_t ny = p->ndim >= 2 ? p->ny[i] : 1, nz = p->ndim == 3 ? p->nz[i] : 1;
-    n += (p->nx[i] + qlg::kValid2D - 1) / qlg::kValid2D * ny * nz;
+    const int64_t nx = p->nx[i], ny = p->ndim >= 2 ? p->ny[i] : 1, nz = p->ndim == 3 ? p->nz[i] : 1;
+    const int64_t c = (nx + cols - 1) / cols;
+    *x += (nx + V - 1) / V * ny * nz;
+    if (p->ndim >= 2) yz[0] += c * ((ny + V - 1) / V) * nz;
+    if (p->ndim == 3) yz[1] += c * ((nz + V - 1) / V) * ny;
   }
-  return n;
 }
 
 int64_t adjoint_chunks(const qlg_params* p) {
@@ -77,12 +77,12 @@ qlg_status sizes_for(const qlg_params* p, int64_t nsteps, int32_t K, Sizes* s) {
   // counts them (every extent of the instance, 1D to 3D)
   const int64_t nchunks = adjoint_chunks(p);
   s->nchunks = nchunks;
-  s->nx4 = adjoint_x4_waves(p);
-  // a step's dg partials: per chunk for the substeps of the plain split, per wavefront (four per
-  // chunk) for the z and y substeps of the interleaved split, then per wavefront for its four
-  // fused x substeps
+  adjoint_lines(p, qlg::line_cols(p->dtype), &s->nx, s->nrecg);
+  adjoint_lines(p, qlg::kAdjCols, &s->nx, s->nadjg);
+  // a step's dg partials: per chunk for the substeps of the plain split, per wavefront of the line
+  // passes (x, then y, then z) for the interleaved split
   s->nparts = p->split == QLG_SPLIT_PLAIN ? s->nsub * nchunks
-                                         : (s->nsub - 4) * kSubAdjParts * nchunks + s->nx4;
+                                         : s->nx + qlg::kAdjCols * (s->nadjg[0] + s->nadjg[1]);
   size_t o = 0;
   // inputs of every self-interaction of one checkpoint segment: [K][nrec] state copies
   s->off_zrec = o;  o += up256((size_t)K * (size_t)s->nrec * s->copy);
@@ -92,8 +92,10 @@ qlg_status sizes_for(const qlg_params* p, int64_t nsteps, int32_t K, Sizes* s) {
   // per segment), one step for the plain split (summed per step)
   s->part_steps = p->split == QLG_SPLIT_PLAIN ? 1 : K;
   s->off_part = o;
-  o += up256(sizeof(double) * 3 * (size_t)s->part_steps * (size_t)std::max<int64_t>(s->nparts, 1));
-  s->off_xpre = o;  o += up256(sizeof(int) * ((size_t)p->nbatch + 1));   // k_adj_x4's instance prefix
+  // (at least what a partial per 64-site wavefront of every y and z substep would take)
+  const int64_t room = std::max<int64_t>(s->nparts, 4 * (s->nsub - 4) * nchunks + s->nx);
+  o += up256(sizeof(double) * 3 * (size_t)s->part_steps * (size_t)std::max<int64_t>(room, 1));
+  s->off_xpre = o;  o += up256(sizeof(int) * qlg::kLinePrefixes * ((size_t)p->nbatch + 1));   // the line passes' instance tables
   s->off_acc = o;   o += up256(sizeof(double) * 4);
   s->off_red = o;   o += up256(sizeof(double) * 3 * (size_t)qlg::kDgBlocks);   // the segment sum's blocks
   // a second [K][nrec] record buffer, last, so that the next segment's inputs can be recomputed
@@ -198,11 +200,10 @@ qlg_status qlg_adjoint_step(qlg_ctx* ctx, int64_t nsteps, int32_t K, const void*
   // with the second record buffer, the recompute of segment i - 1 runs on the context's second
   // stream while the reverse sweep of segment i runs on its stream
   const bool overlap = work_bytes >= s.work && s.nck > 1;
-  // every per-chunk substep kernel writes 3 partials per chunk of the context's layout, the fused x
-  // kernel 3 per wavefront; the workspace region between off_part and off_xpre must hold a step's
+  // the plain split's kernels write 3 partials per chunk of the context's layout, the line passes 3 per
+  // wavefront; the workspace region between off_part and off_xpre must hold a step's (a segment's)
   const bool plain = p.split == QLG_SPLIT_PLAIN;
-  const int64_t nparts_ctx = plain ? (int64_t)s.nsub * v.geom.nchunks
-                                   : (int64_t)(s.nsub - 4) * kSubAdjParts * v.geom.nchunks + s.nx4;
+  const int64_t nparts_ctx = plain ? (int64_t)s.nsub * v.geom.nchunks : s.nparts;
   if (v.geom.nchunks != s.nchunks ||
       (size_t)3 * (size_t)s.part_steps * std::max<int64_t>(nparts_ctx, 1) * sizeof(double) > s.off_xpre - s.off_part)
     return qlg::ctx_fail(ctx, QLG_ERR_ARG, "adjoint partials exceed their workspace region");
@@ -220,8 +221,11 @@ qlg_status qlg_adjoint_step(qlg_ctx* ctx, int64_t nsteps, int32_t K, const void*
   const qlg::LaunchGeom& g = v.geom;
   const hipStream_t str = v.stream;
   const int nd = p.ndim, dt = p.dtype, nsub = s.nsub, nrec = s.nrec;
-  const int nchunks = g.nchunks;
   int* xpre = (int*)(W + s.off_xpre);
+  const int64_t lim = INT32_MAX;
+  if (!plain && std::max({s.nx, s.nrecg[0], s.nrecg[1], qlg::kAdjCols * s.nadjg[0], qlg::kAdjCols * s.nadjg[1]}) > lim)
+    return qlg::ctx_fail(ctx, QLG_ERR_ARG, "lattice too large for the adjoint's tile tables");
+  const qlg::LineCounts lines{(int)s.nx, {(int)s.nrecg[0], (int)s.nrecg[1]}, {(int)s.nadjg[0], (int)s.nadjg[1]}};
   const double theta = p.eps * p.eps / (4.0 * nd);
   const double theta_u = plain ? p.eps * p.eps : theta;
   // substep k of a step acts along z, y, x in that order (the last axis of each dimension first)
@@ -230,10 +234,11 @@ qlg_status qlg_adjoint_step(qlg_ctx* ctx, int64_t nsteps, int32_t K, const void*
   auto zbuf = [&](int b, int64_t j, int r) { return zrec[b] + ((size_t)j * nrec + r) * s.copy; };
   auto seg_steps = [&](int64_t seg) { return (int)std::min<int64_t>(K, nsteps - seg * K); };
 
-  // Forward chain of segment seg from its checkpoint into record buffer b: substep k of step j
-  // is "I'_{k-1} then U_k" (the I' of the previous substep, none for the first one), recording
-  // every U input.  A chain is issued in ranges of steps, in order: chain_to(c, j1, q) issues
-  // steps c.j .. j1 - 1 on stream q; src and yb carry the state between the calls.
+  // Forward chain of segment seg from its checkpoint into record buffer b, recording every U input:
+  // one launch per axis (z, y, x) of each step for the interleaved split; for the plain split one per
+  // substep, "I'_{k-1} then U_k" (the I' of the previous substep, none for the first one).  A chain is
+  // issued in ranges of steps, in order: chain_to(c, j1, q) issues steps c.j .. j1 - 1 on stream q;
+  // src and yb carry the state between the calls.
   struct Chain {
     int64_t seg;
     int b;
@@ -247,30 +252,17 @@ qlg_status qlg_adjoint_step(qlg_ctx* ctx, int64_t nsteps, int32_t K, const void*
     const int b = c.b;
     hipError_t e = hipSuccess;
     if (!plain) {
-      // interleaved split: link (0, 0) alone, then per step the links (j, 1 .. nsub - 4) one
-      // launch each and the four links that apply x factors, (j, nsub - 3 .. nsub - 1) and
-      // (j + 1, 0), in one launch (three in the segment's last step)
       const double tg0 = theta_u * p.g0, tg1 = theta_u * p.g1, tg25 = theta_u * p.g2 / 5.0;
-      if (c.j == 0 && j1 > 0) {
-        e = qlg::launch_chain(dt, c.src, ybuf[c.yb], zbuf(b, 0, 0), g, -1, 0, true, tg0, tg1, tg25, v.ext, theta_u,
-                              q);
-        c.src = ybuf[c.yb];
-        c.yb ^= 1;
-      }
       for (; c.j < j1 && e == hipSuccess; ++c.j) {
-        const int j = c.j;
-        for (int k = 1; k <= nsub - 4 && e == hipSuccess; ++k) {
-          e = qlg::launch_chain(dt, c.src, ybuf[c.yb], zbuf(b, j, k), g, axis_of(k - 1), qb_of(k - 1), true, tg0,
-                                tg1, tg25, v.ext, theta_u, q);
-          c.src = ybuf[c.yb];
-          c.yb ^= 1;
+        for (int axis = nd - 1; axis >= 0 && e == hipSuccess; --axis) {
+          const int k0 = 4 * (nd - 1 - axis);   // the axis' first substep
+          // the pass before an x pass writes the x pass' first record, its input, in place
+          void* dst = axis == 1 ? (void*)zbuf(b, c.j, k0 + 4) : (void*)ybuf[c.yb];
+          e = qlg::launch_recompute(dt, axis, c.src, dst, zbuf(b, c.j, k0), s.copy, axis == 0 && nd > 1 ? 1 : 0, g, lines,
+                                    xpre, tg0, tg1, tg25, v.ext, theta_u, q);
+          if (axis != 1) c.yb ^= 1;
+          c.src = dst;
         }
-        if (e != hipSuccess) break;
-        void* const r[4] = {zbuf(b, j, nsub - 3), zbuf(b, j, nsub - 2), zbuf(b, j, nsub - 1),
-                            j + 1 < n_in ? zbuf(b, j + 1, 0) : nullptr};
-        e = qlg::launch_chain_x4(dt, c.src, ybuf[c.yb], r, g, xpre, (int)s.nx4, tg0, tg1, tg25, v.ext, theta_u, q);
-        c.src = ybuf[c.yb];
-        c.yb ^= 1;
       }
       return e;
     }
@@ -298,7 +290,7 @@ qlg_status qlg_adjoint_step(qlg_ctx* ctx, int64_t nsteps, int32_t K, const void*
 
   hipError_t e = qlg::launch_zero(acc, 4, str);
   if (e == hipSuccess) e = qlg::launch_lam_layout(true, lambda_dev, lam[0], g, str);
-  if (e == hipSuccess && !plain) e = qlg::launch_x4_prefix(g, xpre, str);
+  if (e == hipSuccess && !plain) e = qlg::launch_line_prefix(dt, g, xpre, str);
   if (e != hipSuccess) return qlg::ctx_hip(ctx, e, "adjoint setup");
   hipStream_t aux = nullptr;
   hipEvent_t* ev = nullptr;   // [0], [1]: records of buffer 0, 1 ready; [2]: a sweep done; [3]: setup done
@@ -340,24 +332,18 @@ qlg_status qlg_adjoint_step(qlg_ctx* ctx, int64_t nsteps, int32_t K, const void*
     for (int j = n_in - 1; j >= 0; --j) {
       double* pj = part + (size_t)3 * (plain ? 0 : (size_t)j * s.nparts);   // this step's partials
       if (!plain) {
-        // the step's last four substeps (along x) in one kernel, their dg partials after those
-        // of the nsub - 4 per-chunk substeps
-        const void* zx[4] = {zbuf(b, j, nsub - 1), zbuf(b, j, nsub - 2), zbuf(b, j, nsub - 3), zbuf(b, j, nsub - 4)};
-        e = qlg::launch_adj_x4(dt, zx, lam[lc], lam[1 - lc], g, xpre, (int)s.nx4, theta_u, p.g0, p.g1, p.g2,
-                               v.ext, pj + (size_t)3 * (nsub - 4) * kSubAdjParts * nchunks, str);
-        if (e != hipSuccess) return qlg::ctx_hip(ctx, e, "adjoint x substeps kernel");
-        lc = 1 - lc;
-      }
-      for (int k = plain ? nsub - 1 : nsub - 5; k >= 0; --k) {
-        if (plain) {
-          e = qlg::launch_sub_iprime_adj(lam[lc], lam[1 - lc], g, axis_of(k), qb_of(k), str);
-          if (e != hipSuccess) return qlg::ctx_hip(ctx, e, "adjoint kinetic kernel");
-        } else {
-          // kinetic pull-back and self-interaction VJP of substep k in one kernel
-          e = qlg::launch_sub_adj(dt, zbuf(b, j, k), lam[lc], lam[1 - lc], g, axis_of(k), qb_of(k), theta_u, p.g0,
-                                  p.g1, p.g2, v.ext, pj + (size_t)3 * k * kSubAdjParts * nchunks, str);
-          if (e != hipSuccess) return qlg::ctx_hip(ctx, e, "adjoint substep kernel");
+        // the step's axes, x first, each its four substeps in one launch
+        for (int axis = 0; axis < nd; ++axis) {
+          e = qlg::launch_adjoint(dt, axis, zbuf(b, j, 4 * (nd - 1 - axis)), s.copy, lam[lc], lam[1 - lc], g, lines, xpre,
+                                  theta_u, p.g0, p.g1, p.g2, v.ext, pj, str);
+          if (e != hipSuccess) return qlg::ctx_hip(ctx, e, "adjoint line pass");
+          lc = 1 - lc;
+          pj += 3 * (axis == 0 ? s.nx : qlg::kAdjCols * s.nadjg[axis - 1]);
         }
+      }
+      for (int k = plain ? nsub - 1 : -1; k >= 0; --k) {
+        e = qlg::launch_sub_iprime_adj(lam[lc], lam[1 - lc], g, axis_of(k), qb_of(k), str);
+        if (e != hipSuccess) return qlg::ctx_hip(ctx, e, "adjoint kinetic kernel");
         lc = 1 - lc;
       }
       if (plain) {

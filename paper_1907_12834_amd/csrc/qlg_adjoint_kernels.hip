@@ -4,16 +4,18 @@
 // linear and unitary, so their pull-back is the exact inverse I'^H = C^H S C^H S^T
 // applied to the cotangent (no stored state).  The self-interaction is
 // nonlinear: its pull-back (qlg_vjp.hpp, FP64) needs the substep's input
-// state, which a chain of per-substep kernels regenerates from the segment's
-// checkpoint (the per-site formulas of the fused forward kernels; the compiler
-// may contract them into FMAs differently, so the regenerated FP32 states can
-// differ from the forward's in the last bit).
+// state, which the recompute regenerates from the segment's checkpoint.
 //
-// All kernels are one thread per site over 256-site chunks of each instance.
+// Interleaved split: line passes, as the forward's (qlg_kernels.hip): the four
+// substeps of one axis per launch, the axis along the lanes, 56 owned sites and
+// 4 halo sites on each side per wavefront.  Plain split and objectives: one
+// thread per site over 256-site chunks of each instance.
 
 #include <algorithm>
+#include <type_traits>
 
 #include "qlg_adjoint_kernels.hpp"
+#include "qlg_lanes.hpp"
 #include "qlg_math.hpp"
 #include "qlg_vjp.hpp"
 
@@ -27,17 +29,6 @@ struct Site {
   int s, x, y, z;
   bool ok;
 };
-
-// Workgroups are dispatched round-robin over the 8 XCDs of the chip, each with its own L2.
-// Consecutive chunks (a row and the rows next to it, whose cotangents and states the kinetic
-// pull-back and the chain's I' read again) are given to one XCD, so that those re-reads hit
-// its L2.
-constexpr int kXcds = 8;
-__device__ __forceinline__ int chunk_of_block(int b, int nblocks) {
-  const int x = b % kXcds, l = b / kXcds;
-  const int per = nblocks / kXcds, extra = nblocks % kXcds;
-  return x * per + (x < extra ? x : extra) + l;
-}
 
 // This thread's site in chunk c (thread t of the workgroup takes site t of the chunk).
 __device__ __forceinline__ Site site_of_chunk(const LaunchGeom& g, int c) {
@@ -53,7 +44,7 @@ __device__ __forceinline__ Site site_of_chunk(const LaunchGeom& g, int c) {
 }
 
 __device__ __forceinline__ Site site_here(const LaunchGeom& g) {
-  return site_of_chunk(g, chunk_of_block(blockIdx.x, gridDim.x));
+  return site_of_chunk(g, xcd_contiguous_block(blockIdx.x, gridDim.x));
 }
 
 // site index of the neighbour at offset dir (+1 / -1) along axis (0 = x, 1 = y, 2 = z), periodic
@@ -134,60 +125,21 @@ __device__ __forceinline__ void collide_r_adj(cx<double> (&a)[5], cx<double> (&b
   }
 }
 
-// Moves of a double by one lane across the whole wavefront (DPP wave_shl:1 / wave_shr:1);
-// the end lane, a halo lane here, reads 0.
-template <int Ctrl>
-__device__ __forceinline__ double lane_move(double v) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, Ctrl, 0xF, 0xF, true);
-  const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), Ctrl, 0xF, 0xF, true);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-constexpr int kFromNextLane = 0x130;   // lane i reads lane i + 1
-constexpr int kFromPrevLane = 0x138;   // lane i reads lane i - 1
-template <int Ctrl>
-__device__ __forceinline__ float lane_move(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), Ctrl, 0xF, 0xF, true));
-}
-template <int Ctrl, typename T>
-__device__ __forceinline__ cx<T> lane_move(cx<T> v) {
-  return cx<T>{lane_move<Ctrl>(v.re), lane_move<Ctrl>(v.im)};
-}
-
-// 2 f I'_{x,q}, with x along the lanes, in the operation order of
-// iprime_site: C, q from x + 1, C, q from x - 1, and the collides' factor 2i
-// divided out (f = 1/2, or less where the state carries a factor of its own).  Q = 1: qubit b moves; Q = 0: qubit a.
-template <int Q, typename T>
-__device__ __forceinline__ void iprime_lanes(cx<T> (&a)[5], cx<T> (&b)[5], T f) {
-  collide_r(a, b);
-#pragma unroll
-  for (int m = 0; m < 5; ++m) {
-    if (Q) b[m] = lane_move<kFromNextLane>(b[m]);
-    else   a[m] = lane_move<kFromNextLane>(a[m]);
-  }
-  collide_r(a, b);
-  unphase_by(a, b, f);
-#pragma unroll
-  for (int m = 0; m < 5; ++m) {
-    if (Q) b[m] = lane_move<kFromPrevLane>(b[m]);
-    else   a[m] = lane_move<kFromPrevLane>(a[m]);
-  }
-}
-
-// lambda <- I'^H_{x,q} lambda with x along the lanes: q from x + 1, C^H, q from x - 1, C^H
-// (the order of iprime_adj_site), the factors of the two C^H divided out.  Q = 1: qubit b moves; Q = 0: qubit a.
+// lambda <- I'^H_{x,q} lambda with the axis along the lanes: q from the next lane, C^H, q from the
+// one before, C^H (the order of iprime_adj_site), the factors of the two C^H divided out.
+// Q = 1: qubit b moves; Q = 0: qubit a.
 template <int Q>
 __device__ __forceinline__ void iprime_adj_lanes(cx<double> (&a)[5], cx<double> (&b)[5]) {
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    if (Q) b[m] = lane_move<kFromNextLane>(b[m]);
-    else   a[m] = lane_move<kFromNextLane>(a[m]);
+    if (Q) b[m] = from_next_lane(b[m]);
+    else   a[m] = from_next_lane(a[m]);
   }
   collide_r_adj(a, b);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    if (Q) b[m] = lane_move<kFromPrevLane>(b[m]);
-    else   a[m] = lane_move<kFromPrevLane>(a[m]);
+    if (Q) b[m] = from_prev_lane(b[m]);
+    else   a[m] = from_prev_lane(a[m]);
   }
   collide_r_adj(a, b);
   unphase_by(a, b, -0.5);
@@ -337,79 +289,32 @@ __global__ __launch_bounds__(kChunk) void k_sub_vjp(const cx<T>* __restrict__ z,
   block_sum3(dg[0], dg[1], dg[2], part + 3 * (int64_t)r.c);
 }
 
-// One adjoint substep of the interleaved split, fused: lambda_out = (dU)^H I'^H lambda_in,
-// the kinetic pull-back recomputed per site from lambda_in at x-1, x, x+1 along `axis`,
-// then the FP64 self-interaction VJP at the substep input z; dg partials per wavefront.
-// Workgroups of one wavefront (a quarter of a chunk): a wavefront that finishes frees its
-// SIMD slot for the next at once, so the two wavefronts of a SIMD drift apart and one loads
-// while the other computes.  (Workgroups of a whole chunk, summed in LDS behind a barrier,
-// started and ended four wavefronts together, which kept the loads and the arithmetic of a
-// SIMD's wavefronts in step.)
-template <typename T>
-__global__ __launch_bounds__(kLanes) void k_sub_adj(const cx<T>* __restrict__ z,
-                                                   const cx<double>* __restrict__ lin,
-                                                   cx<double>* __restrict__ lout, LaunchGeom g, int axis, int qb,
-                                                   double theta, double g0, double g1, double g2,
-                                                   const double* __restrict__ pot, double mu,
-                                                   double* __restrict__ part) {
-  constexpr int kWaves = kChunk / kLanes;
-  // wavefront unit u: quarter u % 4 of chunk u / 4, units of one XCD consecutive
-  const int u = chunk_of_block(blockIdx.x, gridDim.x);
-  Site r = site_of_chunk(g, u / kWaves);
-  r.s += (u % kWaves) * kLanes;   // site_of_chunk counts threadIdx.x from the chunk's start
-  r.ok = r.s < r.d.sites;
-  r.x = r.ok ? r.s % r.d.nx : 0;
-  r.y = r.ok ? (r.s / r.d.nx) % r.d.ny : 0;
-  r.z = r.ok ? r.s / (r.d.nx * r.d.ny) : 0;
-  double dg[3] = {0.0, 0.0, 0.0};
-  if (r.ok) {
-    cx<double> la[5], lb[5];
-    iprime_adj_site(lin, r, axis, qb, la, lb);
-    cx<double> a[5], b[5];
-    load_site_nt(z, r.d, r.s, a, b);
-    potential_vjp(a, b, la, lb, theta, g0, g1, g2, dg, ext_here(r, pot, mu, theta));
-    store_site(lout, r.d, r.s, la, lb);
-  }
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) dg[k] += __shfl_xor(dg[k], o, kLanes);
-  }
-  if (threadIdx.x == 0) {
-    part[3 * (int64_t)u] = dg[0];
-    part[3 * (int64_t)u + 1] = dg[1];
-    part[3 * (int64_t)u + 2] = dg[2];
-  }
-}
-
-// Buffer-resource stores (a lane whose offset lies beyond the record count stores nothing), so
-// that every path through a loop issues the same memory instructions and the compiler's waits
-// for loads issued ahead stay exact.
-constexpr int kBufWord3 = 0x00020000;   // resource word 3 on gfx9: 32-bit data format, no swizzle
-constexpr uint32_t kOffNone = 0x80000000u;
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, kBufWord3);
-}
-
-// A wavefront tile of the fused x kernels: 56 columns of one row of one instance plus 4 halo
-// columns on each side.  The instance is the last i with xpre[i] <= w; the tables are read
-// through the constant address space (scalar loads, not ordered behind vector memory).
-struct X4Tile {
+// ---------------------------------------------------------------------------
+// Interleaved split: recompute and pull-back as line passes
+// ---------------------------------------------------------------------------
+// A tile of a line pass: 64 sites of one line along the axis (56 owned, 4 halo on each side) per
+// wavefront.  Along x a wavefront takes one row's tile; along y or z a workgroup takes W
+// neighbouring columns of one tile, turned in LDS (as k_line_yz).  pre[i] is the first tile (x) or
+// group (y, z) of instance i, pre[nbatch] their number; both are read through the constant
+// address space (scalar loads).
+struct LineTile {
   InstDesc d;
-  int row;   // row of the instance (y + ny z)
-  int s;     // this lane's site (periodic column)
-  int x;     // this lane's column before the wrap
-  bool own;  // one of the 56 columns this tile writes
+  int64_t row;       // first site of the line's plane (y, z) or of the row (x)
+  int64_t rstride;   // sites between neighbours along the line
+  int n;             // extent along the line
+  int r;             // this lane's position along the line before the wrap
+  int rw;            // and after it
+  int gx;            // first column of the group (y, z)
+  int64_t line;      // planes * nx before this group's plane: records' line = line + column
+  bool own;
 };
-__device__ __forceinline__ X4Tile x4_tile(const LaunchGeom& g, const int* xpre_g, int w, int lane) {
+__device__ __forceinline__ int line_instance(const LaunchGeom& g, const int* pre_g, int w, InstDesc* d, int* t) {
   typedef const __attribute__((address_space(4))) int32_t* CInt;
-  const CInt xpre = (CInt)xpre_g;
+  const CInt pre = (CInt)pre_g;
   int lo = 0, hi = g.nbatch;
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
-    if (xpre[mid] <= w) lo = mid;
+    if (pre[mid] <= w) lo = mid;
     else hi = mid;
   }
   static_assert(sizeof(InstDesc) % 4 == 0, "InstDesc is read as 32-bit words");
@@ -418,213 +323,266 @@ __device__ __forceinline__ X4Tile x4_tile(const LaunchGeom& g, const int* xpre_g
   int32_t buf[kWords];
 #pragma unroll
   for (int i = 0; i < kWords; ++i) buf[i] = words[i];
-  X4Tile r;
-  __builtin_memcpy(&r.d, buf, sizeof(InstDesc));
-  const int t = w - xpre[lo];
+  __builtin_memcpy(d, buf, sizeof(InstDesc));
+  *t = w - pre[lo];
+  return lo;
+}
+__device__ __forceinline__ LineTile line_tile_x(const LaunchGeom& g, const int* pre, int w, int lane) {
+  LineTile r;
+  int t;
+  line_instance(g, pre, w, &r.d, &t);
   const int ntx = (r.d.nx + kValid2D - 1) / kValid2D;
-  const int tx = t % ntx;
-  r.row = t / ntx;
-  r.x = tx * kValid2D - kHalo2D + lane;
-  const int xw = r.x < 0 ? r.x + r.d.nx * ((-r.x + r.d.nx - 1) / r.d.nx) : r.x % r.d.nx;
-  r.own = lane >= kHalo2D && lane < kLanes - kHalo2D && r.x < r.d.nx;
-  r.s = r.row * r.d.nx + xw;
+  r.n = r.d.nx;
+  r.row = (int64_t)(t / ntx) * r.d.nx;
+  r.rstride = 1;
+  r.r = t % ntx * kValid2D - kHalo2D + lane;
+  r.rw = (int)wrap64(r.r, r.n);
+  r.own = lane >= kHalo2D && lane < kLanes - kHalo2D && r.r < r.n;
+  r.gx = 0;
+  r.line = 0;
   return r;
 }
-
-// The four adjoint substeps along x of a step, fused: for k = k0 + 3, ..., k0 (qubits a, a, b, b),
-//   lambda <- (dU_k)^H I'^H_{x,q_k} lambda  at the recorded inputs z_k.
-// A tile is 56 columns of one row (x tiles of each row, rows of each instance in order,
-// instances by the prefix table xpre) plus 4 halo columns on each side: each I'^H reaches one
-// site, so after the four substeps the middle 56 lanes hold the cotangent of their sites, read
-// and written once instead of once per substep.  The x shifts are lane moves.  Only the 56 owned
-// lanes add to the dg partial of the tile (part[3 w + 0..2]).
-// One wavefront per SIMD (its registers, 256 + about 130 accumulation registers, do not fit the
-// 256 of two waves without spilling to scratch, which measured 1.5x slower), persistent: a
-// wavefront walks tiles of its XCD's contiguous range, and during a tile's last substep it loads
-// the next tile's cotangent, potential and first record, whose latency a wavefront alone on its
-// SIMD would otherwise wait out at the start of every tile.
-template <typename T>
-__global__ __launch_bounds__(kChunk) void k_adj_x4(const cx<T>* __restrict__ z3, const cx<T>* __restrict__ z2,
-                                                  const cx<T>* __restrict__ z1, const cx<T>* __restrict__ z0,
-                                                  const cx<double>* __restrict__ lin, cx<double>* __restrict__ lout,
-                                                  LaunchGeom g, const int* __restrict__ xpre, int nwaves,
-                                                  double theta, double g0, double g1, double g2,
-                                                  const double* __restrict__ pot, double mu,
-                                                  double* __restrict__ part) {
-  constexpr int kWaves = kChunk / kLanes;
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & (kLanes - 1);
-  // tiles [c0, c1) of this workgroup's XCD, taken with the stride of the XCD's wavefront count
-  // (a grid of fewer than 8 workgroups: each workgroup a group of its own)
-  const int nb = gridDim.x, ng = nb < kXcds ? nb : kXcds;
-  const int xcd = blockIdx.x % ng, lb = blockIdx.x / ng;
-  const int stride = (nb / ng + (xcd < nb % ng ? 1 : 0)) * kWaves;
-  const int per = nwaves / ng, extra = nwaves % ng;
-  const int c0 = xcd * per + (xcd < extra ? xcd : extra);
-  const int c1 = c0 + per + (xcd < extra ? 1 : 0);
-  int w = c0 + lb * kWaves + wv;
-  if (w >= c1) return;   // wavefront-uniform; no workgroup-level synchronisation below
-  // the potential's phase at a site: a resource of size 0 without a potential reads 0
-  auto ext_at = [&](const X4Tile& t) __attribute__((always_inline)) {
-    const __amdgpu_buffer_rsrc_t pr = buf_rsrc(pot ? pot + t.d.psi_off / 5 : nullptr,
-                                               pot ? (uint32_t)t.d.sites * 8u : 0u);
-    const double v = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(pr, t.s * 8, 0, 0));
-    return theta * (v + mu);
-  };
-  // the records of substeps k0 + 2, k0 + 1, k0 as a pointer formed by arithmetic (a select
-  // between three pointers in a loop is otherwise made a table in private memory)
-  auto zrec = [&](int i) __attribute__((always_inline)) {
-    const uintptr_t p = (uintptr_t)z2 * (uintptr_t)(i == 0) + (uintptr_t)z1 * (uintptr_t)(i == 1) +
-                        (uintptr_t)z0 * (uintptr_t)(i == 2);
-    return (const cx<T>*)p;
-  };
-  cx<double> nla[5], nlb[5];
-  cx<T> na[5], nb5[5];
-  double next_ext;
-  {
-    const X4Tile t0 = x4_tile(g, xpre, w, lane);
-    load_site(lin, t0.d, t0.s, nla, nlb);
-    next_ext = ext_at(t0);
-    load_site_nt(z3, t0.d, t0.s, na, nb5);
+template <int W>
+__device__ __forceinline__ LineTile line_tile_yz(const LaunchGeom& g, const int* pre, int grp, int lane, bool zp) {
+  LineTile r;
+  int t;
+  line_instance(g, pre, grp, &r.d, &t);
+  r.n = zp ? r.d.nz : r.d.ny;
+  r.rstride = zp ? (int64_t)r.d.nx * r.d.ny : (int64_t)r.d.nx;
+  const int ncol = (r.d.nx + W - 1) / W, ntile = (r.n + kValid2D - 1) / kValid2D;
+  const int tr = t / ncol, plane = tr / ntile;
+  r.gx = t % ncol * W;
+  r.row = plane * (zp ? (int64_t)r.d.nx : (int64_t)r.d.nx * r.d.ny);
+  r.line = (int64_t)plane * r.d.nx;
+  r.r = tr % ntile * kValid2D - kHalo2D + lane;
+  r.rw = (int)wrap64(r.r, r.n);
+  r.own = lane >= kHalo2D && lane < kLanes - kHalo2D && r.r < r.n;
+  return r;
+}
+// This thread's element of a group's tile, 64 positions along the line x W columns, for the loads
+// and stores that run along x.
+template <int W>
+struct TileElem {
+  int er, ec;
+  int64_t src, dst;
+  bool store;
+  __device__ __forceinline__ TileElem(const LineTile& t) {
+    er = threadIdx.x / W;
+    ec = threadIdx.x % W;
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int ey = t.r - lane + er, ex = t.gx + ec;
+    src = t.d.off + t.row + wrap64(ey, t.n) * t.rstride + (ex < t.d.nx ? ex : t.d.nx - 1);
+    dst = t.d.off + t.row + ey * t.rstride + ex;
+    store = er >= kHalo2D && er < kLanes - kHalo2D && ey < t.n && ex < t.d.nx;
   }
-  for (;;) {
-    const X4Tile cur = x4_tile(g, xpre, w, lane);
-    cx<double> la[5], lb5[5];
-#pragma unroll
-    for (int m = 0; m < 5; ++m) {
-      la[m] = nla[m];
-      lb5[m] = nlb[m];
-    }
-    const double ext = next_ext;
-    double dg[3] = {0.0, 0.0, 0.0};
-    // substeps k0 + 3, k0 + 2 (qubit a), k0 + 1 (qubit b), each at the record in na, nb5 and
-    // loading the next one
+};
+
+// The recompute of one axis: z_0 = in, z_{k+1} = I'_k U(z_k) for k = 0..3 (qubits b, b, a, a),
+// out = z_4.  rec + k rstep receives z_k, k >= first (along x a record is a state copy; along y
+// and z it runs along the lines, site r of the line of column x and plane p at (p nx + x) n + r,
+// so that the pull-back's lanes read it without a turn).
+template <typename T, bool kExt, typename Put>
+__device__ __forceinline__ void recompute_substeps(cx<T> (&a)[5], cx<T> (&b)[5], const Angles<T>& ang, T ext, Put put) {
+  constexpr T kUnscale = T(0.5) / UScale<T>::value;   // of U and of the I' after it
 #pragma unroll 1
-    for (int i = 0; i < 3; ++i) {
-      cx<double> a[5], b[5];
-#pragma unroll
-      for (int m = 0; m < 5; ++m) {
-        a[m] = cx<double>{(double)na[m].re, (double)na[m].im};
-        b[m] = cx<double>{(double)nb5[m].re, (double)nb5[m].im};
-      }
-      load_site_nt(zrec(i), cur.d, cur.s, na, nb5);
-      if (i < 2) iprime_adj_lanes<0>(la, lb5);
-      else iprime_adj_lanes<1>(la, lb5);
-      double dgl[3] = {0.0, 0.0, 0.0};
-      potential_vjp<true>(a, b, la, lb5, theta, g0, g1, g2, dgl, ext);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) dg[k] += cur.own ? dgl[k] : 0.0;
-    }
-    // substep k0 (qubit b), with the next tile's cotangent, potential and first record loaded
-    // first (the last tile loads its own again: nothing writes lin, pot or the records)
-    const int wn = w + stride;
-    const bool more = wn < c1;
-    {
-      cx<double> a[5], b[5];
-#pragma unroll
-      for (int m = 0; m < 5; ++m) {
-        a[m] = cx<double>{(double)na[m].re, (double)na[m].im};
-        b[m] = cx<double>{(double)nb5[m].re, (double)nb5[m].im};
-      }
-      const X4Tile nt = x4_tile(g, xpre, more ? wn : w, lane);
-      load_site(lin, nt.d, nt.s, nla, nlb);
-      next_ext = ext_at(nt);
-      load_site_nt(z3, nt.d, nt.s, na, nb5);
-      iprime_adj_lanes<1>(la, lb5);
-      double dgl[3] = {0.0, 0.0, 0.0};
-      potential_vjp<true>(a, b, la, lb5, theta, g0, g1, g2, dgl, ext);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) dg[k] += cur.own ? dgl[k] : 0.0;
-    }
-    // the owned columns' cotangents: one row of each plane, lanes outside it drop their stores
-    const uint32_t off = cur.own ? (uint32_t)cur.x * 16u : kOffNone;
-    const uint32_t rb = (uint32_t)cur.d.nx * 16u;
-#pragma unroll
-    for (int m = 0; m < 5; ++m) {
-      const cx<double>* pa = lout + cur.d.off + m * cur.d.stride + (int64_t)cur.row * cur.d.nx;
-      const cx<double>* pb = lout + cur.d.off + (5 + m) * cur.d.stride + (int64_t)cur.row * cur.d.nx;
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, la[m]), buf_rsrc(pa, rb), (int)off, 0, 0);
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, lb5[m]), buf_rsrc(pb, rb), (int)off, 0, 0);
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) dg[k] += __shfl_xor(dg[k], o, kLanes);
-    }
-    // lanes 0, 1, 2 store dg[0], dg[1], dg[2] of the tile
-    const double mine = lane == 0 ? dg[0] : lane == 1 ? dg[1] : dg[2];
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, mine), buf_rsrc(part + 3 * (int64_t)w, 24u),
-                                          (int)(lane < 3 ? (uint32_t)lane * 8u : kOffNone), 0, 0);
-    if (!more) break;
-    w = wn;
+  for (int k = 0; k < 2; ++k) {
+    put(k);
+    potential<T, kExt>(a, b, ang, ext);
+    iprime_r_lanes<T, 1>(a, b);
+    unphase_by(a, b, kUnscale);
+  }
+#pragma unroll 1
+  for (int k = 2; k < 4; ++k) {
+    put(k);
+    potential<T, kExt>(a, b, ang, ext);
+    iprime_r_lanes<T, 0>(a, b);
+    unphase_by(a, b, kUnscale);
   }
 }
 
-// The links of the recorded forward chain that apply x kinetic factors, fused: for the links
-// (j, nsub - 3), (j, nsub - 2), (j, nsub - 1) and, when r3 is set, (j + 1, 0),
-//   z <- I'_{x,q}(y) (q = b, b, a, a),  r_i <- z,  y <- U(z),
-// on the tiles of k_adj_x4 (56 columns of one row plus 4 halo columns on each side, the x
-// shifts as lane moves): the state is read and written once for the four links.  Only the
-// owned lanes store their records and the output.
-template <typename T>
-__global__ __launch_bounds__(kChunk) void k_chain_x4(const cx<T>* __restrict__ in, cx<T>* __restrict__ out,
-                                                    cx<T>* __restrict__ r0, cx<T>* __restrict__ r1,
-                                                    cx<T>* __restrict__ r2, cx<T>* __restrict__ r3,
-                                                    LaunchGeom g, const int* __restrict__ xpre, int nwaves,
-                                                    Angles<T> ang, const double* __restrict__ pot, double mu,
-                                                    double theta) {
+template <typename T, bool kExt>
+__global__ __launch_bounds__(kChunk) void k_recompute_x(const cx<T>* __restrict__ in, cx<T>* __restrict__ out,
+                                                       cx<T>* __restrict__ rec, int64_t rstep, int first,
+                                                       LaunchGeom g, const int* __restrict__ pre, int nwaves,
+                                                       Angles<T> ang, const double* __restrict__ pot, double mu,
+                                                       double theta) {
   constexpr int kWaves = kChunk / kLanes;
-  const int w = chunk_of_block(blockIdx.x, gridDim.x) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = xcd_contiguous_block(blockIdx.x, gridDim.x) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (w >= nwaves) return;
+  const LineTile t = line_tile_x(g, pre, w, threadIdx.x & (kLanes - 1));
+  const int s = (int)t.row + t.rw;
+  cx<T> a[5], b[5];
+  load_site(in, t.d, s, a, b);
+  T ext = T(0);
+  if constexpr (kExt) ext = T(theta) * T((pot ? pot[t.d.psi_off / 5 + s] : 0.0) + mu);
+  recompute_substeps<T, kExt>(a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
+    if (t.own && k >= first) store_site_nt(rec + k * rstep, t.d, s, a, b);
+  });
+  if (t.own) store_site(out, t.d, s, a, b);
+}
+
+template <typename T, int W, bool kExt>
+__global__ __launch_bounds__(kLanes * W) void k_recompute_yz(const cx<T>* __restrict__ in, cx<T>* __restrict__ out,
+                                                            cx<T>* __restrict__ rec, int64_t rstep, LaunchGeom g,
+                                                            const int* __restrict__ pre, int zp, Angles<T> ang,
+                                                            const double* __restrict__ pot, double mu, double theta) {
+  __shared__ cx<T> buf[10][kLanes][W + 1];
+  const int lane = threadIdx.x & (kLanes - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const LineTile t = line_tile_yz<W>(g, pre, xcd_contiguous_block(blockIdx.x, gridDim.x), lane, zp != 0);
+  const TileElem<W> e(t);
+  {
+    cx<T> v[10];
+#pragma unroll
+    for (int p = 0; p < 10; ++p) v[p] = in[e.src + p * t.d.stride];
+#pragma unroll
+    for (int p = 0; p < 10; ++p) buf[p][e.er][e.ec] = v[p];
+  }
+  __syncthreads();
+  cx<T> a[5], b[5];
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    a[m] = buf[m][lane][wv];
+    b[m] = buf[5 + m][lane][wv];
+  }
+  const int x = t.gx + wv;
+  const bool own = t.own && x < t.d.nx;
+  const int s = (int)((t.line + x) * t.n) + t.r;   // in a record
+  T ext = T(0);
+  if constexpr (kExt) {
+    const int64_t at = t.d.psi_off / 5 + t.row + t.rw * t.rstride + (x < t.d.nx ? x : t.d.nx - 1);
+    ext = T(theta) * T((pot ? pot[at] : 0.0) + mu);
+  }
+  recompute_substeps<T, kExt>(a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
+    if (own) store_site_nt(rec + k * rstep, t.d, s, a, b);
+  });
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    buf[m][lane][wv] = a[m];
+    buf[5 + m][lane][wv] = b[m];
+  }
+  __syncthreads();
+  if (e.store) {
+#pragma unroll
+    for (int p = 0; p < 10; ++p) out[e.dst + p * t.d.stride] = buf[p][e.er][e.ec];
+  }
+}
+
+// The pull-back through one axis: for k = 3, ..., 0 (qubits a, a, b, b),
+//   lambda <- (dU_k)^H I'^H_k lambda  at the recorded inputs z_k = rec + k rstep,
+// site s of the records on this lane.  dg: the sums of this lane's site (owned lanes only).
+template <typename T>
+__device__ __forceinline__ void adjoint_substeps(cx<double> (&la)[5], cx<double> (&lb)[5], const cx<T>* __restrict__ rec,
+                                                int64_t rstep, const InstDesc& d, int s, double theta, double g0,
+                                                double g1, double g2, double ext, double (&dg)[3]) {
+  auto substep = [&](int k, auto q) __attribute__((always_inline)) {
+    cx<double> a[5], b[5];
+    load_site_nt(rec + k * rstep, d, s, a, b);
+    iprime_adj_lanes<decltype(q)::value>(la, lb);
+    potential_vjp(a, b, la, lb, theta, g0, g1, g2, dg, ext);
+  };
+#pragma unroll 1
+  for (int k = 3; k >= 2; --k) substep(k, std::integral_constant<int, 0>{});
+#pragma unroll 1
+  for (int k = 1; k >= 0; --k) substep(k, std::integral_constant<int, 1>{});
+}
+
+// dL/dg of a wavefront's owned lanes into part[0..2].
+__device__ __forceinline__ void store_dg(double (&dg)[3], bool own, int lane, double* __restrict__ part) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    dg[k] = own ? dg[k] : 0.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) dg[k] += __shfl_xor(dg[k], o, kLanes);
+  }
+  if (lane == 0) {
+    part[0] = dg[0];
+    part[1] = dg[1];
+    part[2] = dg[2];
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kChunk) __attribute__((amdgpu_waves_per_eu(2)))
+void k_adjoint_x(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>* __restrict__ lin,
+                 cx<double>* __restrict__ lout, LaunchGeom g, const int* __restrict__ pre, int nwaves, double theta,
+                 double g0, double g1, double g2, const double* __restrict__ pot, double mu,
+                 double* __restrict__ part) {
+  constexpr int kWaves = kChunk / kLanes;
+  const int w = xcd_contiguous_block(blockIdx.x, gridDim.x) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (w >= nwaves) return;
   const int lane = threadIdx.x & (kLanes - 1);
-  int lo = 0, hi = g.nbatch;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (xpre[mid] <= w) lo = mid;
-    else hi = mid;
-  }
-  const InstDesc d = g.inst[lo];
-  const int t = w - xpre[lo];
-  const int ntx = (d.nx + kValid2D - 1) / kValid2D;
-  const int tx = t % ntx, row = t / ntx;
-  const int x = tx * kValid2D - kHalo2D + lane;
-  const int xw = x < 0 ? x + d.nx * ((-x + d.nx - 1) / d.nx) : x % d.nx;
-  const bool own = lane >= kHalo2D && lane < kLanes - kHalo2D && x < d.nx;
-  const int s = row * d.nx + xw;
-  cx<T> a[5], b[5];
-  load_site(in, d, s, a, b);
-  const bool ext = pot || mu != 0.0;
-  const T e = T(theta) * T((pot ? pot[d.psi_off / 5 + s] : 0.0) + mu);
-  auto link = [&](cx<T>* __restrict__ rec) {
-    if (own) store_site_nt(rec, d, s, a, b);
-    if (ext) potential<T, true>(a, b, ang, e);
-    else potential(a, b, ang);
-  };
-  constexpr T kAfterU = T(0.5) / UScale<T>::value;   // U leaves its factor to the I' after it
-  iprime_lanes<1>(a, b, T(0.5));
-  link(r0);
-  iprime_lanes<1>(a, b, kAfterU);
-  link(r1);
-  iprime_lanes<0>(a, b, kAfterU);
-  link(r2);
-  if (r3) {
-    iprime_lanes<0>(a, b, kAfterU);
-    link(r3);
-  }
-  scale_by(a, b, T(1) / UScale<T>::value);
-  if (own) store_site(out, d, s, a, b);
+  const LineTile t = line_tile_x(g, pre, w, lane);
+  const int s = (int)t.row + t.rw;
+  cx<double> la[5], lb[5];
+  load_site(lin, t.d, s, la, lb);
+  const double ext = theta * ((pot ? pot[t.d.psi_off / 5 + s] : 0.0) + mu);
+  double dg[3] = {0.0, 0.0, 0.0};
+  adjoint_substeps(la, lb, rec, rstep, t.d, s, theta, g0, g1, g2, ext, dg);
+  if (t.own) store_site(lout, t.d, s, la, lb);
+  store_dg(dg, t.own, lane, part + 3 * (int64_t)w);
 }
 
-// xpre[i] = wavefronts of k_adj_x4 before instance i (xpre[nbatch] = all of them).
-__global__ void k_x4_prefix(LaunchGeom g, int* __restrict__ xpre) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+template <typename T>
+__global__ __launch_bounds__(kLanes * kAdjCols) __attribute__((amdgpu_waves_per_eu(2)))
+void k_adjoint_yz(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>* __restrict__ lin,
+                  cx<double>* __restrict__ lout, LaunchGeom g, const int* __restrict__ pre, int zp, double theta,
+                  double g0, double g1, double g2, const double* __restrict__ pot, double mu,
+                  double* __restrict__ part) {
+  constexpr int W = kAdjCols;
+  __shared__ cx<double> buf[10][kLanes][W + 1];
+  const int lane = threadIdx.x & (kLanes - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = xcd_contiguous_block(blockIdx.x, gridDim.x);
+  const LineTile t = line_tile_yz<W>(g, pre, grp, lane, zp != 0);
+  const TileElem<W> e(t);
+  {
+    cx<double> v[10];
+#pragma unroll
+    for (int p = 0; p < 10; ++p) v[p] = lin[e.src + p * t.d.stride];
+#pragma unroll
+    for (int p = 0; p < 10; ++p) buf[p][e.er][e.ec] = v[p];
+  }
+  __syncthreads();
+  cx<double> la[5], lb[5];
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    la[m] = buf[m][lane][wv];
+    lb[m] = buf[5 + m][lane][wv];
+  }
+  const int x = t.gx + wv, xc = x < t.d.nx ? x : t.d.nx - 1;
+  const bool own = t.own && x < t.d.nx;
+  const int s = (int)((t.line + xc) * t.n) + t.rw;   // in a record
+  const double ext = theta * ((pot ? pot[t.d.psi_off / 5 + t.row + t.rw * t.rstride + xc] : 0.0) + mu);
+  double dg[3] = {0.0, 0.0, 0.0};
+  adjoint_substeps(la, lb, rec, rstep, t.d, s, theta, g0, g1, g2, ext, dg);
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    buf[m][lane][wv] = la[m];
+    buf[5 + m][lane][wv] = lb[m];
+  }
+  store_dg(dg, own, lane, part + 3 * ((int64_t)grp * W + wv));
+  __syncthreads();
+  if (e.store) {
+#pragma unroll
+    for (int p = 0; p < 10; ++p) lout[e.dst + p * t.d.stride] = buf[p][e.er][e.ec];
+  }
+}
+
+// The instance tables of the line passes, one after the other (nbatch + 1 entries each): x tiles, y
+// and z groups of the recompute (rec_cols columns), y and z groups of the pull-back (kAdjCols).
+__global__ void k_line_prefix(LaunchGeom g, int rec_cols, int* __restrict__ pre) {
+  const int q = threadIdx.x;
+  if (q >= kLinePrefixes) return;
+  int* p = pre + q * (g.nbatch + 1);
+  const int cols = q <= 2 ? rec_cols : kAdjCols;
   int acc = 0;
   for (int i = 0; i < g.nbatch; ++i) {
-    xpre[i] = acc;
+    p[i] = acc;
     const InstDesc d = g.inst[i];
-    acc += (d.nx + kValid2D - 1) / kValid2D * d.ny * d.nz;
+    if (q == 0) acc += (d.nx + kValid2D - 1) / kValid2D * d.ny * d.nz;
+    else if (q & 1) acc += (d.nx + cols - 1) / cols * ((d.ny + kValid2D - 1) / kValid2D) * d.nz;
+    else acc += (d.nx + cols - 1) / cols * ((d.nz + kValid2D - 1) / kValid2D) * d.ny;
   }
-  xpre[g.nbatch] = acc;
+  p[g.nbatch] = acc;
 }
 
 // acc[0..2] += sum over chunks of part (single block, fixed order).  Unrolling
@@ -851,59 +809,63 @@ hipError_t launch_sub_vjp(int dtype, const void* z, void* lam, const LaunchGeom&
   return hipGetLastError();
 }
 
-hipError_t launch_sub_adj(int dtype, const void* z, const void* lam_in, void* lam_out, const LaunchGeom& g, int axis,
-                          int qb, double theta, double g0, double g1, double g2, const ExtPot& ext, double* part,
-                          hipStream_t st) {
-  if (g.nchunks == 0) return hipSuccess;
-  const dim3 grid(g.nchunks * (kChunk / kLanes)), block(kLanes);
-  if (dtype == 0)
-    hipLaunchKernelGGL(k_sub_adj<float>, grid, block, 0, st, (const cx<float>*)z, (const cx<double>*)lam_in,
-                       (cx<double>*)lam_out, g, axis, qb, theta, g0, g1, g2, ext.V, ext.mu, part);
-  else
-    hipLaunchKernelGGL(k_sub_adj<double>, grid, block, 0, st, (const cx<double>*)z, (const cx<double>*)lam_in,
-                       (cx<double>*)lam_out, g, axis, qb, theta, g0, g1, g2, ext.V, ext.mu, part);
-  return hipGetLastError();
-}
-
-hipError_t launch_chain_x4(int dtype, const void* in, void* out, void* const rec[4], const LaunchGeom& g,
-                           const int* xpre, int nwaves, double tg0, double tg1, double tg25, const ExtPot& ext,
-                           double theta, hipStream_t st) {
-  if (nwaves <= 0) return hipSuccess;
+hipError_t launch_recompute(int dtype, int axis, const void* in, void* out, void* rec, size_t rec_bytes, int first,
+                            const LaunchGeom& g, const LineCounts& n, const int* pre, double tg0, double tg1,
+                            double tg25, const ExtPot& ext, double theta, hipStream_t st) {
   constexpr int kWaves = kChunk / kLanes;
-  const dim3 grid((nwaves + kWaves - 1) / kWaves), block(kChunk);
-  if (dtype == 0)
-    hipLaunchKernelGGL(k_chain_x4<float>, grid, block, 0, st, (const cx<float>*)in, (cx<float>*)out,
-                       (cx<float>*)rec[0], (cx<float>*)rec[1], (cx<float>*)rec[2], (cx<float>*)rec[3], g, xpre,
-                       nwaves, Angles<float>{(float)tg0, (float)tg1, (float)tg25}, ext.V, ext.mu, theta);
-  else
-    hipLaunchKernelGGL(k_chain_x4<double>, grid, block, 0, st, (const cx<double>*)in, (cx<double>*)out,
-                       (cx<double>*)rec[0], (cx<double>*)rec[1], (cx<double>*)rec[2], (cx<double>*)rec[3], g,
-                       xpre, nwaves, Angles<double>{tg0, tg1, tg25}, ext.V, ext.mu, theta);
+  const int* p = pre + axis * (g.nbatch + 1);
+  auto go = [&](auto tag, auto cols) {
+    using T = decltype(tag);
+    constexpr int W = decltype(cols)::value;
+    const Angles<T> ang{(T)tg0, (T)tg1, (T)tg25};
+    const int64_t rstep = (int64_t)(rec_bytes / sizeof(cx<T>));
+    if (axis == 0) {
+      const dim3 grid((n.x + kWaves - 1) / kWaves), block(kChunk);
+      if (ext.on())
+        hipLaunchKernelGGL((k_recompute_x<T, true>), grid, block, 0, st, (const cx<T>*)in, (cx<T>*)out, (cx<T>*)rec, rstep,
+                           first, g, p, n.x, ang, ext.V, ext.mu, theta);
+      else
+        hipLaunchKernelGGL((k_recompute_x<T, false>), grid, block, 0, st, (const cx<T>*)in, (cx<T>*)out, (cx<T>*)rec,
+                           rstep, first, g, p, n.x, ang, ext.V, ext.mu, theta);
+      return;
+    }
+    const dim3 grid(n.rec[axis - 1]), block(kLanes * W);
+    if (ext.on())
+      hipLaunchKernelGGL((k_recompute_yz<T, W, true>), grid, block, 0, st, (const cx<T>*)in, (cx<T>*)out, (cx<T>*)rec,
+                         rstep, g, p, axis == 2 ? 1 : 0, ang, ext.V, ext.mu, theta);
+    else
+      hipLaunchKernelGGL((k_recompute_yz<T, W, false>), grid, block, 0, st, (const cx<T>*)in, (cx<T>*)out, (cx<T>*)rec,
+                         rstep, g, p, axis == 2 ? 1 : 0, ang, ext.V, ext.mu, theta);
+  };
+  if (dtype == 0) go(0.0f, std::integral_constant<int, line_cols(0)>{});
+  else go(0.0, std::integral_constant<int, line_cols(1)>{});
   return hipGetLastError();
 }
 
-hipError_t launch_x4_prefix(const LaunchGeom& g, int* xpre, hipStream_t st) {
-  hipLaunchKernelGGL(k_x4_prefix, dim3(1), dim3(64), 0, st, g, xpre);
-  return hipGetLastError();
-}
-
-hipError_t launch_adj_x4(int dtype, const void* const z[4], const void* lam_in, void* lam_out, const LaunchGeom& g,
-                         const int* xpre, int nwaves, double theta, double g0, double g1, double g2,
-                         const ExtPot& ext, double* part, hipStream_t st) {
-  if (nwaves <= 0) return hipSuccess;
+hipError_t launch_adjoint(int dtype, int axis, const void* rec, size_t rec_bytes, const void* lam_in, void* lam_out,
+                          const LaunchGeom& g, const LineCounts& n, const int* pre, double theta, double g0, double g1,
+                          double g2, const ExtPot& ext, double* part, hipStream_t st) {
   constexpr int kWaves = kChunk / kLanes;
-  // one wavefront per SIMD: at most one workgroup of four per CU, each walking several tiles
-  constexpr int kAdjX4Blocks = 256;
-  const dim3 grid(std::min((nwaves + kWaves - 1) / kWaves, kAdjX4Blocks)), block(kChunk);
-  const double* pot = ext.V;
-  if (dtype == 0)
-    hipLaunchKernelGGL(k_adj_x4<float>, grid, block, 0, st, (const cx<float>*)z[0], (const cx<float>*)z[1],
-                       (const cx<float>*)z[2], (const cx<float>*)z[3], (const cx<double>*)lam_in,
-                       (cx<double>*)lam_out, g, xpre, nwaves, theta, g0, g1, g2, pot, ext.mu, part);
-  else
-    hipLaunchKernelGGL(k_adj_x4<double>, grid, block, 0, st, (const cx<double>*)z[0], (const cx<double>*)z[1],
-                       (const cx<double>*)z[2], (const cx<double>*)z[3], (const cx<double>*)lam_in,
-                       (cx<double>*)lam_out, g, xpre, nwaves, theta, g0, g1, g2, pot, ext.mu, part);
+  auto go = [&](auto tag) {
+    using T = decltype(tag);
+    const int64_t rstep = (int64_t)(rec_bytes / sizeof(cx<T>));
+    if (axis == 0) {
+      hipLaunchKernelGGL(k_adjoint_x<T>, dim3((n.x + kWaves - 1) / kWaves), dim3(kChunk), 0, st, (const cx<T>*)rec, rstep,
+                         (const cx<double>*)lam_in, (cx<double>*)lam_out, g, pre, n.x, theta, g0, g1, g2, ext.V, ext.mu,
+                         part);
+      return;
+    }
+    hipLaunchKernelGGL(k_adjoint_yz<T>, dim3(n.adj[axis - 1]), dim3(kLanes * kAdjCols), 0, st, (const cx<T>*)rec, rstep,
+                       (const cx<double>*)lam_in, (cx<double>*)lam_out, g, pre + (2 + axis) * (g.nbatch + 1),
+                       axis == 2 ? 1 : 0, theta, g0, g1, g2, ext.V, ext.mu, part);
+  };
+  if (dtype == 0) go(0.0f);
+  else go(0.0);
+  return hipGetLastError();
+}
+
+hipError_t launch_line_prefix(int dtype, const LaunchGeom& g, int* pre, hipStream_t st) {
+  hipLaunchKernelGGL(k_line_prefix, dim3(1), dim3(64), 0, st, g, line_cols(dtype), pre);
   return hipGetLastError();
 }
 

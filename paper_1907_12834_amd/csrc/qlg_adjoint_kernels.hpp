@@ -15,27 +15,26 @@ hipError_t launch_sub_iprime_adj(const void* in, void* out, const LaunchGeom& g,
 // lam <- (dU)^H lam at z; acc[0..2] += dL/dg (part: nchunks x 3 doubles of scratch)
 hipError_t launch_sub_vjp(int dtype, const void* z, void* lam, const LaunchGeom& g, double theta, double g0,
                           double g1, double g2, const ExtPot& ext, double* part, double* acc, hipStream_t st);
-// Fused adjoint substep of the interleaved split: lam_out = (dU)^H I'_{axis,qb}^H lam_in at the
-// substep input z; dg partials per wavefront (a quarter of a chunk) into part[4 nchunks][3]
-// (no accumulation).
-hipError_t launch_sub_adj(int dtype, const void* z, const void* lam_in, void* lam_out, const LaunchGeom& g, int axis,
-                          int qb, double theta, double g0, double g1, double g2, const ExtPot& ext, double* part,
-                          hipStream_t st);
-// The four adjoint substeps along x of one step in one launch (k_adj_x4): z[0..3] are the
-// recorded inputs of substeps k0 + 3, k0 + 2, k0 + 1, k0 (the order they are undone in);
-// nwaves = xpre[nbatch] wavefronts of 56 columns of one row; one dg partial per wavefront
-// into part[nwaves][3] (no accumulation).
-hipError_t launch_adj_x4(int dtype, const void* const z[4], const void* lam_in, void* lam_out, const LaunchGeom& g,
-                         const int* xpre, int nwaves, double theta, double g0, double g1, double g2,
-                         const ExtPot& ext, double* part, hipStream_t st);
-// The chain links that apply x kinetic factors, fused (k_chain_x4): links (j, nsub - 3 ..
-// nsub - 1) and, when rec[3] is not null, (j + 1, 0); rec[i] receives the input of the
-// link's U, out the state after the last.  Tiles as launch_adj_x4's.
-hipError_t launch_chain_x4(int dtype, const void* in, void* out, void* const rec[4], const LaunchGeom& g,
-                           const int* xpre, int nwaves, double tg0, double tg1, double tg25, const ExtPot& ext,
-                           double theta, hipStream_t st);
-// xpre[0..nbatch]: prefix sums over the instances of ceil(nx / 56) ny nz (device table)
-hipError_t launch_x4_prefix(const LaunchGeom& g, int* xpre, hipStream_t st);
+// Interleaved split: line passes (one axis, 0 = x, 1 = y, 2 = z, of one step per launch).
+constexpr int kAdjCols = 4;        // columns per y or z group of the pull-back (complex128: 64 bytes)
+constexpr int kLinePrefixes = 5;   // instance tables of nbatch + 1 ints each (launch_line_prefix)
+struct LineCounts {
+  int x;         // x tiles (wavefronts), ceil(nx / 56) per row
+  int rec[2];    // y, z groups of the recompute (line_cols(dtype) columns of a 56-site tile)
+  int adj[2];    // y, z groups of the pull-back (kAdjCols columns)
+};
+// The recompute of one axis: z_0 = in, z_{k+1} = I'_k U(z_k), out = z_4; rec + k rec_bytes receives
+// z_k for k >= first (x: as a state copy; y and z: along the lines, first = 0 always).
+hipError_t launch_recompute(int dtype, int axis, const void* in, void* out, void* rec, size_t rec_bytes, int first,
+                            const LaunchGeom& g, const LineCounts& n, const int* pre, double tg0, double tg1,
+                            double tg25, const ExtPot& ext, double theta, hipStream_t st);
+// The pull-back through one axis at the records of the same layout; dg partials per wavefront into
+// part[n.x][3] (x) or part[kAdjCols n.adj[axis - 1]][3] (no accumulation).
+hipError_t launch_adjoint(int dtype, int axis, const void* rec, size_t rec_bytes, const void* lam_in, void* lam_out,
+                          const LaunchGeom& g, const LineCounts& n, const int* pre, double theta, double g0, double g1,
+                          double g2, const ExtPot& ext, double* part, hipStream_t st);
+// pre[kLinePrefixes][nbatch + 1]: the instances' first x tile, y and z group (device table)
+hipError_t launch_line_prefix(int dtype, const LaunchGeom& g, int* pre, hipStream_t st);
 // acc[0..2] += sum of nparts consecutive 3-vectors of part (fixed order)
 hipError_t launch_dg_accumulate(const double* part, int nparts, double* acc, hipStream_t st);
 // The same for many partials: kDgBlocks workgroups sum contiguous ranges of part into

@@ -1,0 +1,102 @@
+// Device helpers that the step kernels and the adjoint kernels share: lane moves, the kinetic
+// operator along the lanes, the angles and scales of a step's substeps, and the order in which
+// workgroups take tiles.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "qlg_math.hpp"
+
+namespace qlg {
+
+// Whole-wavefront moves by one lane through DPP (wave_shl:1, wave_shr:1, both
+// available on CDNA): a VALU operation that the compiler can fold into the
+// arithmetic that consumes it, instead of a round trip through the LDS
+// crossbar.  The end lane, always a halo lane here, reads 0.
+constexpr int kDppWaveShl1 = 0x130;   // lane i reads lane i + 1
+constexpr int kDppWaveShr1 = 0x138;   // lane i reads lane i - 1
+
+template <int Ctrl>
+__device__ __forceinline__ float dpp_move(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), Ctrl, 0xF, 0xF, true));
+}
+template <int Ctrl>
+__device__ __forceinline__ double dpp_move(double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, Ctrl, 0xF, 0xF, true);
+  const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), Ctrl, 0xF, 0xF, true);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+template <typename T>
+__device__ __forceinline__ cx<T> from_next_lane(cx<T> v) {
+  return cx<T>{dpp_move<kDppWaveShl1>(v.re), dpp_move<kDppWaveShl1>(v.im)};
+}
+template <typename T>
+__device__ __forceinline__ cx<T> from_prev_lane(cx<T> v) {
+  return cx<T>{dpp_move<kDppWaveShr1>(v.re), dpp_move<kDppWaveShr1>(v.im)};
+}
+
+// 2i I'_{x,q}: S_q C S_q^T C by collide_r, with lanes along x (the factor 1/(2i) is left to
+// the caller).  Q = 1: qubit b (the paper's qubit 2) moves; Q = 0: qubit a (qubit 1).
+template <typename T, int Q>
+__device__ __forceinline__ void iprime_r_lanes(cx<T> (&a)[5], cx<T> (&b)[5]) {
+  collide_r(a, b);
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {   // S^T: q(x) <- q(x + 1)
+    if (Q) b[m] = from_next_lane(b[m]);
+    else   a[m] = from_next_lane(a[m]);
+  }
+  collide_r(a, b);
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {   // S: q(x) <- q(x - 1)
+    if (Q) b[m] = from_prev_lane(b[m]);
+    else   a[m] = from_prev_lane(a[m]);
+  }
+}
+
+// What an interleaved substep U I' leaves the state multiplied by, in modulus: 2 from the I'
+// (collide_r) times UScale from U.
+template <typename T>
+constexpr int kSubstepScale = 2 * UScale<T>::value;
+
+// Angles of interleaved substep j = 0..3 of a four-I' sequence, on a state that
+// carries the factor kSubstepScale^j (and i^j) of the j substeps before it: the n terms'
+// angles and F's scale times kSubstepScale^-2j (exact).  Formed from the unscaled angles in
+// registers, so that a run-time j reads no kernel argument inside the row loop.
+template <typename T>
+__device__ __forceinline__ Angles<T> substep_angles(const Angles<T>& base, int j) {
+  const T f = ldexp(T(1), (kSubstepScale<T> == 4 ? -4 : -2) * j);
+  Angles<T> a = base;
+  a.tg0 *= f;
+  a.tg25 *= f;
+  a.fs = f;
+  return a;
+}
+
+// The factor that brings the state back to its true value after kSubsteps (2 or 4) I', with a
+// U before each of them or, in the plain split, with one U before the first (plain_u) or none.
+template <typename T, int kSubsteps>
+__device__ __forceinline__ T substep_unscale(bool plain, bool plain_u) {
+  constexpr T i = kSubsteps == 4 ? T(1) / 16 : T(-1) / 4;   // (2i)^-kSubsteps
+  constexpr T u = T(1) / UScale<T>::value;
+  constexpr T un = kSubsteps == 4 ? u * u * u * u : u * u;
+  return plain ? (plain_u ? i * u : i) : i * un;
+}
+
+__device__ __forceinline__ int64_t wrap64(int64_t x, int64_t n) {
+  int64_t r = x % n;
+  return r < 0 ? r + n : r;
+}
+
+// Workgroups are dispatched round-robin over the 8 XCDs of the chip, each with its
+// own L2.  Give each XCD a contiguous range of logical workgroups, so that tiles
+// that share halo rows and columns (consecutive tiles) read them through one L2.
+constexpr int kXcds = 8;
+__device__ __forceinline__ int xcd_contiguous_block(int b, int nblocks) {
+  const int x = b % kXcds, l = b / kXcds;
+  const int per = nblocks / kXcds, extra = nblocks % kXcds;
+  return x * per + (x < extra ? x : extra) + l;
+}
+
+}  // namespace qlg

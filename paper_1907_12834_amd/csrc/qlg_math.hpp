@@ -295,6 +295,38 @@ QLG_HD void half_angle_series(double y, double* c, double* s) {
   *s = fma(y, ps, 1.0);
 }
 
+// The same for any arguments: (c, s) of x0 and x2 through their half angles (cos x - 1 =
+// -2 sin^2(x/2) without cancellation), and (ch, sh) from hh = h^2.  Not inlined: the library
+// routines' constants would otherwise be hoisted out of the substep loops of every kernel,
+// into registers that the usual path needs (the pull-back spilled 40 of them per wavefront).
+template <typename T>
+struct Series {
+  T c0, s0, c2, s2, ch, sh;
+};
+template <typename T>
+__host__ __device__ __attribute__((noinline)) inline Series<T> general_series(T x0, T x2, T hh) {
+  auto phase = [](T x, T* c, T* s) {
+    const T h = T(0.5) * x;
+    if (fabs(h) < T(1e-4)) {
+      phase_series(x * x, c, s);
+      return;
+    }
+    T sn, cn;
+    sincos_t(h, &sn, &cn);
+    const T sc = sn * rcp_t(h);
+    *c = T(-0.5) * sc * sc;
+    *s = sc * cn;
+  };
+  Series<T> r;
+  phase(x0, &r.c0, &r.s0);
+  phase(x2, &r.c2, &r.s2);
+  const T h = sqrt_t(hh);
+  T sn;
+  sincos_t(h, &sn, &r.ch);
+  r.sh = h < T(1e-4) ? fma_t(hh, T(-1.0 / 6.0), T(1)) : sn * rcp_t(h);
+  return r;
+}
+
 // R - I of the spin rotation R = exp(-i phi n.f), as the real 5 x 5 matrix that it is on
 //   (s2, i t2, i s1, t1, x0),   s_m = x_m + x_-m,  t_m = x_m - x_-m
 // (integer spin is a real representation, R_{-m',-m} = (-1)^{m'-m} conj R_{m'm}).  Rows 2 and 1
@@ -428,38 +460,21 @@ QLG_HD void w_coefficients(const cx<T> (&a)[5], const cx<T> (&b)[5], const Angle
 
   // exp(-i x) - 1 = x (x c - i s) with c = (cos x - 1)/x^2, s = sin(x)/x.  When every angle of
   // every lane is small (the usual case) all take short series without a branch per lane.
-  T c0, s0, c2, s2, ch, sh;
-  if (all_lanes(fmax(fabs(x0), fabs(x2)) <= T(0.125) && hh <= T(1.0 / 256.0))) {
-    phase_series(x0 * x0, &c0, &s0);
-    phase_series(x2 * x2, &c2, &s2);
-    half_angle_series(hh, &ch, &sh);
+  Series<T> f;
+  if (__builtin_expect(all_lanes(fmax(fabs(x0), fabs(x2)) <= T(0.125) && hh <= T(1.0 / 256.0)), 1)) {
+    phase_series(x0 * x0, &f.c0, &f.s0);
+    phase_series(x2 * x2, &f.c2, &f.s2);
+    half_angle_series(hh, &f.ch, &f.sh);
   } else {
-    auto general = [](T x, T* c, T* s) {   // half angles: cos x - 1 = -2 sin^2(x/2) without cancellation
-      const T h = T(0.5) * x;
-      if (fabs(h) < T(1e-4)) {
-        phase_series(x * x, c, s);
-        return;
-      }
-      T sn, cn;
-      sincos_t(h, &sn, &cn);
-      const T ih = rcp_t(h), sc = sn * ih;
-      *c = T(-0.5) * sc * sc;
-      *s = sc * cn;
-    };
-    general(x0, &c0, &s0);
-    general(x2, &c2, &s2);
-    const T h = sqrt_t(hh);
-    T sn;
-    sincos_t(h, &sn, &ch);
-    sh = h < T(1e-4) ? fma_t(hh, T(-1.0 / 6.0), T(1)) : sn * rcp_t(h);
+    f = general_series(x0, x2, hh);
   }
-  W.mu0 = cx<T>{x0 * x0 * c0, -(x0 * s0)};
+  W.mu0 = cx<T>{x0 * x0 * f.c0, -(x0 * f.s0)};
   // singlet coefficient (exp(-i x2) - 1) / n = th g2/5 (x2 c - i s): no division by n, so empty or
   // denormal sites stay finite; times exp(-i x0) = 1 + mu0
-  const cx<T> cs{ang.tg25 * x2 * c2, -(ang.tg25 * s2)};
+  const cx<T> cs{ang.tg25 * x2 * f.c2, -(ang.tg25 * f.s2)};
   W.cs = cx<T>{fma_t(W.mu0.re, cs.re, fma_t(-W.mu0.im, cs.im, cs.re)),
                fma_t(W.mu0.re, cs.im, fma_t(W.mu0.im, cs.re, cs.im))};
-  rot2(ch, sh * Hx, sh * Hy, sh * Hz, W.R);
+  rot2(f.ch, f.sh * Hx, f.sh * Hy, f.sh * Hz, W.R);
 }
 
 // x <- UScale exp(-i th g0 n) R P x for one 5-vector x (a or b).
