@@ -30,7 +30,7 @@ struct Sizes {
   int nsub = 4;        // substeps per step
   int nrec = 4;        // recorded self-interaction inputs per step (nsub, or 1 for the plain split)
   int64_t nchunks = 0; // 256-site chunks of the per-site kernels
-  int64_t nx = 0, nrecg[2] = {0, 0}, nadjg[2] = {0, 0};   // x tiles, y and z groups of the line passes
+  int64_t nx = 0, nrecg[2] = {0, 0}, nadjg[2] = {0, 0};   // x windows, y and z groups of the line passes
   int64_t nparts = 0;  // dg partials (3 doubles each) of one step's reverse sweep
   int64_t part_steps = 1;  // steps whose dg partials are kept before they are summed
   size_t off_zrec = 0, off_y = 0, off_lam = 0, off_part = 0, off_xpre = 0, off_acc = 0, off_red = 0;
@@ -40,16 +40,15 @@ struct Sizes {
 
 size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
-// x tiles, and y and z groups of `cols` columns, of the line passes
+// x windows, and y and z groups of `cols` columns, of the line passes
 void adjoint_lines(const qlg_params* p, int cols, int64_t* x, int64_t (&yz)[2]) {
   *x = yz[0] = yz[1] = 0;
-  constexpr int V = qlg::kValid2D;
   for (int i = 0; i < p->nbatch; ++i) {
     const int64_t nx = p->nx[i], ny = p->ndim >= 2 ? p->ny[i] : 1, nz = p->ndim == 3 ? p->nz[i] : 1;
-    const int64_t c = (nx + cols - 1) / cols;
-    *x += (nx + V - 1) / V * ny * nz;
-    if (p->ndim >= 2) yz[0] += c * ((ny + V - 1) / V) * nz;
-    if (p->ndim == 3) yz[1] += c * ((nz + V - 1) / V) * ny;
+    const int64_t ncol = (nx + cols - 1) / cols;
+    *x += qlg::line_windows(nx, ny * nz);
+    if (p->ndim >= 2) yz[0] += ncol * qlg::line_windows(ny, nz);
+    if (p->ndim == 3) yz[1] += ncol * qlg::line_windows(nz, ny);
   }
 }
 
@@ -92,8 +91,12 @@ qlg_status sizes_for(const qlg_params* p, int64_t nsteps, int32_t K, Sizes* s) {
   // per segment), one step for the plain split (summed per step)
   s->part_steps = p->split == QLG_SPLIT_PLAIN ? 1 : K;
   s->off_part = o;
-  // (at least what a partial per 64-site wavefront of every y and z substep would take)
-  const int64_t room = std::max<int64_t>(s->nparts, 4 * (s->nsub - 4) * nchunks + s->nx);
+  // (at least what a partial per 64-site wavefront of every y and z substep and per 56 sites of every
+  // row would take)
+  int64_t rows = 0;
+  for (int i = 0; i < p->nbatch; ++i)
+    rows += (p->nx[i] + qlg::kValid2D - 1) / qlg::kValid2D * (p->ndim >= 2 ? p->ny[i] : 1) * (p->ndim == 3 ? p->nz[i] : 1);
+  const int64_t room = std::max<int64_t>(s->nparts, 4 * (s->nsub - 4) * nchunks + rows);
   o += up256(sizeof(double) * 3 * (size_t)s->part_steps * (size_t)std::max<int64_t>(room, 1));
   s->off_xpre = o;  o += up256(sizeof(int) * qlg::kLinePrefixes * ((size_t)p->nbatch + 1));   // the line passes' instance tables
   s->off_acc = o;   o += up256(sizeof(double) * 4);
@@ -222,8 +225,10 @@ qlg_status qlg_adjoint_step(qlg_ctx* ctx, int64_t nsteps, int32_t K, const void*
   const hipStream_t str = v.stream;
   const int nd = p.ndim, dt = p.dtype, nsub = s.nsub, nrec = s.nrec;
   int* xpre = (int*)(W + s.off_xpre);
+  // 32-bit group numbers, and 32-bit slots (56 per window)
   const int64_t lim = INT32_MAX;
-  if (!plain && std::max({s.nx, s.nrecg[0], s.nrecg[1], qlg::kAdjCols * s.nadjg[0], qlg::kAdjCols * s.nadjg[1]}) > lim)
+  if (!plain && (std::max({s.nrecg[0], s.nrecg[1], qlg::kAdjCols * s.nadjg[0], qlg::kAdjCols * s.nadjg[1]}) > lim ||
+                 s.nx > UINT32_MAX / qlg::kLanes))
     return qlg::ctx_fail(ctx, QLG_ERR_ARG, "lattice too large for the adjoint's tile tables");
   const qlg::LineCounts lines{(int)s.nx, {(int)s.nrecg[0], (int)s.nrecg[1]}, {(int)s.nadjg[0], (int)s.nadjg[1]}};
   const double theta = p.eps * p.eps / (4.0 * nd);

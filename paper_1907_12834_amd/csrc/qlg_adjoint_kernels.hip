@@ -292,21 +292,17 @@ __global__ __launch_bounds__(kChunk) void k_sub_vjp(const cx<T>* __restrict__ z,
 // ---------------------------------------------------------------------------
 // Interleaved split: recompute and pull-back as line passes
 // ---------------------------------------------------------------------------
-// A tile of a line pass: 64 sites of one line along the axis (56 owned, 4 halo on each side) per
-// wavefront.  Along x a wavefront takes one row's tile; along y or z a workgroup takes W
-// neighbouring columns of one tile, turned in LDS (as k_line_yz).  pre[i] is the first tile (x) or
-// group (y, z) of instance i, pre[nbatch] their number; both are read through the constant
-// address space (scalar loads).
+// Along x a wavefront takes one window of the lines laid end to end (line_slot); along y or z a
+// workgroup takes W neighbouring columns of one window, turned in LDS (as k_line_yz).  pre[i] is the
+// first window of instance i, pre[nbatch] their number; both are read through the constant address
+// space (scalar loads).
 struct LineTile {
   InstDesc d;
-  int64_t row;       // first site of the line's plane (y, z) or of the row (x)
-  int64_t rstride;   // sites between neighbours along the line
-  int n;             // extent along the line
-  int r;             // this lane's position along the line before the wrap
-  int rw;            // and after it
-  int gx;            // first column of the group (y, z)
-  int64_t line;      // planes * nx before this group's plane: records' line = line + column
-  bool own;
+  uint32_t window;   // of the instance
+  int n, nlines;     // extent along the lines, number of lines (y, z: of one column)
+  int rstride;       // sites between neighbours along the line
+  int pstride;       // y, z: sites between planes
+  int gx;            // y, z: first column of the group
 };
 __device__ __forceinline__ int line_instance(const LaunchGeom& g, const int* pre_g, int w, InstDesc* d, int* t) {
   typedef const __attribute__((address_space(4))) int32_t* CInt;
@@ -327,53 +323,58 @@ __device__ __forceinline__ int line_instance(const LaunchGeom& g, const int* pre
   *t = w - pre[lo];
   return lo;
 }
-__device__ __forceinline__ LineTile line_tile_x(const LaunchGeom& g, const int* pre, int w, int lane) {
+__device__ __forceinline__ LineTile line_tile_x(const LaunchGeom& g, const int* pre, int w) {
   LineTile r;
   int t;
   line_instance(g, pre, w, &r.d, &t);
-  const int ntx = (r.d.nx + kValid2D - 1) / kValid2D;
+  r.window = t;
   r.n = r.d.nx;
-  r.row = (int64_t)(t / ntx) * r.d.nx;
-  r.rstride = 1;
-  r.r = t % ntx * kValid2D - kHalo2D + lane;
-  r.rw = (int)wrap64(r.r, r.n);
-  r.own = lane >= kHalo2D && lane < kLanes - kHalo2D && r.r < r.n;
-  r.gx = 0;
-  r.line = 0;
+  r.nlines = r.d.ny * r.d.nz;
   return r;
 }
 template <int W>
-__device__ __forceinline__ LineTile line_tile_yz(const LaunchGeom& g, const int* pre, int grp, int lane, bool zp) {
+__device__ __forceinline__ LineTile line_tile_yz(const LaunchGeom& g, const int* pre, int grp, bool zp) {
   LineTile r;
   int t;
   line_instance(g, pre, grp, &r.d, &t);
-  r.n = zp ? r.d.nz : r.d.ny;
-  r.rstride = zp ? (int64_t)r.d.nx * r.d.ny : (int64_t)r.d.nx;
-  const int ncol = (r.d.nx + W - 1) / W, ntile = (r.n + kValid2D - 1) / kValid2D;
-  const int tr = t / ncol, plane = tr / ntile;
+  const int ncol = (r.d.nx + W - 1) / W;
+  r.window = t / ncol;
   r.gx = t % ncol * W;
-  r.row = plane * (zp ? (int64_t)r.d.nx : (int64_t)r.d.nx * r.d.ny);
-  r.line = (int64_t)plane * r.d.nx;
-  r.r = tr % ntile * kValid2D - kHalo2D + lane;
-  r.rw = (int)wrap64(r.r, r.n);
-  r.own = lane >= kHalo2D && lane < kLanes - kHalo2D && r.r < r.n;
+  r.n = zp ? r.d.nz : r.d.ny;
+  r.rstride = zp ? r.d.nx * r.d.ny : r.d.nx;
+  r.pstride = zp ? r.d.nx : r.d.nx * r.d.ny;
+  r.nlines = zp ? r.d.ny : r.d.nz;
   return r;
 }
-// This thread's element of a group's tile, 64 positions along the line x W columns, for the loads
-// and stores that run along x.
+// This thread's element of a group's window, 64 slots x W columns, for the loads and stores that run
+// along x.
 template <int W>
 struct TileElem {
   int er, ec;
-  int64_t src, dst;
+  int64_t at;
   bool store;
   __device__ __forceinline__ TileElem(const LineTile& t) {
     er = threadIdx.x / W;
     ec = threadIdx.x % W;
-    const int lane = threadIdx.x & (kLanes - 1);
-    const int ey = t.r - lane + er, ex = t.gx + ec;
-    src = t.d.off + t.row + wrap64(ey, t.n) * t.rstride + (ex < t.d.nx ? ex : t.d.nx - 1);
-    dst = t.d.off + t.row + ey * t.rstride + ex;
-    store = er >= kHalo2D && er < kLanes - kHalo2D && ey < t.n && ex < t.d.nx;
+    const LineSlot l = line_slot(t.window, er, t.n, t.nlines);
+    const int x = t.gx + ec;
+    at = t.d.off + (l.line * t.pstride + l.at * t.rstride + (x < t.d.nx ? x : t.d.nx - 1));
+    store = l.own && x < t.d.nx;
+  }
+};
+// This lane's place in a record along y or z: site `at` of the line of column x and plane p, at
+// (p nx + x) n + at.
+template <int W>
+struct LaneElem {
+  bool own;
+  int rec;         // place in a record
+  int pot;         // site
+  __device__ __forceinline__ LaneElem(const LineTile& t, int lane, int wv) {
+    const LineSlot l = line_slot(t.window, lane, t.n, t.nlines);
+    const int x = t.gx + wv < t.d.nx ? t.gx + wv : t.d.nx - 1;
+    own = l.own && t.gx + wv < t.d.nx;
+    rec = (l.line * t.d.nx + x) * t.n + l.at;
+    pot = l.line * t.pstride + l.at * t.rstride + x;
   }
 };
 
@@ -409,16 +410,17 @@ __global__ __launch_bounds__(kChunk) void k_recompute_x(const cx<T>* __restrict_
   constexpr int kWaves = kChunk / kLanes;
   const int w = xcd_contiguous_block(blockIdx.x, gridDim.x) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (w >= nwaves) return;
-  const LineTile t = line_tile_x(g, pre, w, threadIdx.x & (kLanes - 1));
-  const int s = (int)t.row + t.rw;
+  const LineTile t = line_tile_x(g, pre, w);
+  const LineSlot l = line_slot(t.window, threadIdx.x & (kLanes - 1), t.n, t.nlines);
+  const int s = l.line * t.n + l.at;
   cx<T> a[5], b[5];
   load_site(in, t.d, s, a, b);
   T ext = T(0);
   if constexpr (kExt) ext = T(theta) * T((pot ? pot[t.d.psi_off / 5 + s] : 0.0) + mu);
   recompute_substeps<T, kExt>(a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
-    if (t.own && k >= first) store_site_nt(rec + k * rstep, t.d, s, a, b);
+    if (l.own && k >= first) store_site_nt(rec + k * rstep, t.d, s, a, b);
   });
-  if (t.own) store_site(out, t.d, s, a, b);
+  if (l.own) store_site(out, t.d, s, a, b);
 }
 
 template <typename T, int W, bool kExt>
@@ -428,12 +430,12 @@ __global__ __launch_bounds__(kLanes * W) void k_recompute_yz(const cx<T>* __rest
                                                             const double* __restrict__ pot, double mu, double theta) {
   __shared__ cx<T> buf[10][kLanes][W + 1];
   const int lane = threadIdx.x & (kLanes - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const LineTile t = line_tile_yz<W>(g, pre, xcd_contiguous_block(blockIdx.x, gridDim.x), lane, zp != 0);
+  const LineTile t = line_tile_yz<W>(g, pre, xcd_contiguous_block(blockIdx.x, gridDim.x), zp != 0);
   const TileElem<W> e(t);
   {
     cx<T> v[10];
 #pragma unroll
-    for (int p = 0; p < 10; ++p) v[p] = in[e.src + p * t.d.stride];
+    for (int p = 0; p < 10; ++p) v[p] = in[e.at + p * t.d.stride];
 #pragma unroll
     for (int p = 0; p < 10; ++p) buf[p][e.er][e.ec] = v[p];
   }
@@ -444,16 +446,11 @@ __global__ __launch_bounds__(kLanes * W) void k_recompute_yz(const cx<T>* __rest
     a[m] = buf[m][lane][wv];
     b[m] = buf[5 + m][lane][wv];
   }
-  const int x = t.gx + wv;
-  const bool own = t.own && x < t.d.nx;
-  const int s = (int)((t.line + x) * t.n) + t.r;   // in a record
+  const LaneElem<W> le(t, lane, wv);
   T ext = T(0);
-  if constexpr (kExt) {
-    const int64_t at = t.d.psi_off / 5 + t.row + t.rw * t.rstride + (x < t.d.nx ? x : t.d.nx - 1);
-    ext = T(theta) * T((pot ? pot[at] : 0.0) + mu);
-  }
+  if constexpr (kExt) ext = T(theta) * T((pot ? pot[t.d.psi_off / 5 + le.pot] : 0.0) + mu);
   recompute_substeps<T, kExt>(a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
-    if (own) store_site_nt(rec + k * rstep, t.d, s, a, b);
+    if (le.own) store_site_nt(rec + k * rstep, t.d, le.rec, a, b);
   });
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
@@ -463,7 +460,7 @@ __global__ __launch_bounds__(kLanes * W) void k_recompute_yz(const cx<T>* __rest
   __syncthreads();
   if (e.store) {
 #pragma unroll
-    for (int p = 0; p < 10; ++p) out[e.dst + p * t.d.stride] = buf[p][e.er][e.ec];
+    for (int p = 0; p < 10; ++p) out[e.at + p * t.d.stride] = buf[p][e.er][e.ec];
   }
 }
 
@@ -511,15 +508,16 @@ void k_adjoint_x(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>*
   const int w = xcd_contiguous_block(blockIdx.x, gridDim.x) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (w >= nwaves) return;
   const int lane = threadIdx.x & (kLanes - 1);
-  const LineTile t = line_tile_x(g, pre, w, lane);
-  const int s = (int)t.row + t.rw;
+  const LineTile t = line_tile_x(g, pre, w);
+  const LineSlot l = line_slot(t.window, lane, t.n, t.nlines);
+  const int s = l.line * t.n + l.at;
   cx<double> la[5], lb[5];
   load_site(lin, t.d, s, la, lb);
   const double ext = theta * ((pot ? pot[t.d.psi_off / 5 + s] : 0.0) + mu);
   double dg[3] = {0.0, 0.0, 0.0};
   adjoint_substeps(la, lb, rec, rstep, t.d, s, theta, g0, g1, g2, ext, dg);
-  if (t.own) store_site(lout, t.d, s, la, lb);
-  store_dg(dg, t.own, lane, part + 3 * (int64_t)w);
+  if (l.own) store_site(lout, t.d, s, la, lb);
+  store_dg(dg, l.own, lane, part + 3 * (int64_t)w);
 }
 
 template <typename T>
@@ -532,12 +530,12 @@ void k_adjoint_yz(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>
   __shared__ cx<double> buf[10][kLanes][W + 1];
   const int lane = threadIdx.x & (kLanes - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = xcd_contiguous_block(blockIdx.x, gridDim.x);
-  const LineTile t = line_tile_yz<W>(g, pre, grp, lane, zp != 0);
+  const LineTile t = line_tile_yz<W>(g, pre, grp, zp != 0);
   const TileElem<W> e(t);
   {
     cx<double> v[10];
 #pragma unroll
-    for (int p = 0; p < 10; ++p) v[p] = lin[e.src + p * t.d.stride];
+    for (int p = 0; p < 10; ++p) v[p] = lin[e.at + p * t.d.stride];
 #pragma unroll
     for (int p = 0; p < 10; ++p) buf[p][e.er][e.ec] = v[p];
   }
@@ -548,26 +546,24 @@ void k_adjoint_yz(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>
     la[m] = buf[m][lane][wv];
     lb[m] = buf[5 + m][lane][wv];
   }
-  const int x = t.gx + wv, xc = x < t.d.nx ? x : t.d.nx - 1;
-  const bool own = t.own && x < t.d.nx;
-  const int s = (int)((t.line + xc) * t.n) + t.rw;   // in a record
-  const double ext = theta * ((pot ? pot[t.d.psi_off / 5 + t.row + t.rw * t.rstride + xc] : 0.0) + mu);
+  const LaneElem<W> le(t, lane, wv);
+  const double ext = theta * ((pot ? pot[t.d.psi_off / 5 + le.pot] : 0.0) + mu);
   double dg[3] = {0.0, 0.0, 0.0};
-  adjoint_substeps(la, lb, rec, rstep, t.d, s, theta, g0, g1, g2, ext, dg);
+  adjoint_substeps(la, lb, rec, rstep, t.d, le.rec, theta, g0, g1, g2, ext, dg);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
     buf[m][lane][wv] = la[m];
     buf[5 + m][lane][wv] = lb[m];
   }
-  store_dg(dg, own, lane, part + 3 * ((int64_t)grp * W + wv));
+  store_dg(dg, le.own, lane, part + 3 * ((int64_t)grp * W + wv));
   __syncthreads();
   if (e.store) {
 #pragma unroll
-    for (int p = 0; p < 10; ++p) lout[e.dst + p * t.d.stride] = buf[p][e.er][e.ec];
+    for (int p = 0; p < 10; ++p) lout[e.at + p * t.d.stride] = buf[p][e.er][e.ec];
   }
 }
 
-// The instance tables of the line passes, one after the other (nbatch + 1 entries each): x tiles, y
+// The instance tables of the line passes, one after the other (nbatch + 1 entries each): x windows, y
 // and z groups of the recompute (rec_cols columns), y and z groups of the pull-back (kAdjCols).
 __global__ void k_line_prefix(LaunchGeom g, int rec_cols, int* __restrict__ pre) {
   const int q = threadIdx.x;
@@ -578,9 +574,8 @@ __global__ void k_line_prefix(LaunchGeom g, int rec_cols, int* __restrict__ pre)
   for (int i = 0; i < g.nbatch; ++i) {
     p[i] = acc;
     const InstDesc d = g.inst[i];
-    if (q == 0) acc += (d.nx + kValid2D - 1) / kValid2D * d.ny * d.nz;
-    else if (q & 1) acc += (d.nx + cols - 1) / cols * ((d.ny + kValid2D - 1) / kValid2D) * d.nz;
-    else acc += (d.nx + cols - 1) / cols * ((d.nz + kValid2D - 1) / kValid2D) * d.ny;
+    const uint32_t nx = d.nx, ny = d.ny, nz = d.nz, ncol = (nx + cols - 1) / cols;
+    acc += q == 0 ? line_windows(nx, ny * nz) : q & 1 ? ncol * line_windows(ny, nz) : ncol * line_windows(nz, ny);
   }
   p[g.nbatch] = acc;
 }

@@ -19,8 +19,8 @@ hipError_t launch_sub_vjp(int dtype, const void* z, void* lam, const LaunchGeom&
 constexpr int kAdjCols = 4;        // columns per y or z group of the pull-back (complex128: 64 bytes)
 constexpr int kLinePrefixes = 5;   // instance tables of nbatch + 1 ints each (launch_line_prefix)
 struct LineCounts {
-  int x;         // x tiles (wavefronts), ceil(nx / 56) per row
-  int rec[2];    // y, z groups of the recompute (line_cols(dtype) columns of a 56-site tile)
+  int x;         // x windows (wavefronts)
+  int rec[2];    // y, z groups of the recompute (line_cols(dtype) columns of a window)
   int adj[2];    // y, z groups of the pull-back (kAdjCols columns)
 };
 // The recompute of one axis: z_0 = in, z_{k+1} = I'_k U(z_k), out = z_4; rec + k rec_bytes receives
@@ -33,7 +33,7 @@ hipError_t launch_recompute(int dtype, int axis, const void* in, void* out, void
 hipError_t launch_adjoint(int dtype, int axis, const void* rec, size_t rec_bytes, const void* lam_in, void* lam_out,
                           const LaunchGeom& g, const LineCounts& n, const int* pre, double theta, double g0, double g1,
                           double g2, const ExtPot& ext, double* part, hipStream_t st);
-// pre[kLinePrefixes][nbatch + 1]: the instances' first x tile, y and z group (device table)
+// pre[kLinePrefixes][nbatch + 1]: the instances' first x window, y and z group (device table)
 hipError_t launch_line_prefix(int dtype, const LaunchGeom& g, int* pre, hipStream_t st);
 // acc[0..2] += sum of nparts consecutive 3-vectors of part (fixed order)
 hipError_t launch_dg_accumulate(const double* part, int nparts, double* acc, hipStream_t st);

@@ -245,6 +245,17 @@ int64_t band_tiles(const qlg_ctx* c, int rows) {
   return t;
 }
 
+// Whether the line passes' 32-bit slot numbers hold every instance's lines.
+bool lines_fit(const qlg_ctx* c) {
+  const int64_t most = int64_t(1) << 31;
+  int64_t slots = 0;
+  for (const auto& d : c->L.inst) {
+    slots += std::max({qlg::line_slots<int64_t>(d.nx) * d.ny * d.nz, qlg::line_slots<int64_t>(d.ny) * d.nx * d.nz,
+                       qlg::line_slots<int64_t>(d.nz) * d.nx * d.ny});
+  }
+  return slots < most;
+}
+
 // The launch form, band height, 1D steps per pass and qubit split of a context for which neither
 // qlg_autotune nor qlg_set_tuning has chosen.  The lines are where the measured times per step
 // cross on MI355X (1024 SIMDs; us, complex128 / complex64):
@@ -254,12 +265,13 @@ int64_t band_tiles(const qlg_ctx* c, int rows) {
 //     wavefronts per SIMD 4 steps of the one-lane kernel (65536: 9.1 / 7.0 against 12.1 / 9.5),
 //     beyond that 2 (524288: 48.7 / 30.0; 1: 50.2 / 31.0, 3: 54.3 / 34.0).
 //   2D and 3D: line passes finish a launch in four substeps, a band only after its rows, but read
-//     and write the state once per axis.  Interleaved, lines against the best bands: 64^2 17 / 18
-//     against 103 / 96; 1024^2 225 / 133 against 269 / 175; 1448^2 427 / 262 against 431 / 298;
-//     2048^2 857 / 522 against 807 / 477; 3D, where bands take two passes too, 64^3 130 / 93
-//     against 189 / 175, 256^3 5360 / 2990 against 5850 / 3250.  Plain split (a seventh of the
-//     arithmetic): 512^2 43 / 26 against 57 / 45; 1024^2 170 / 69 against 117 / 76; 64^3 67 / 41
-//     against 93 / 71; 110^3 329 / 121 against 267 / 118.
+//     and write the state once per axis.  Interleaved, lines against the best bands: 64^2 17 / 17
+//     against 100 / 95; 1024^2 215 / 130 against 267 / 174; 1448^2 420 / 255 against 438 / 292;
+//     1700^2 573 / 374 against 590 / 370; 2048^2 836 / 515 against 800 / 485; 3D, where bands take
+//     two passes too, 64^3 110 / 82 against 182 / 174, 256^3 5200 / 3160 against 5770 / 3240; 360^3
+//     14570 / 9010 against 15230 / 8530.  Plain split (a seventh of the arithmetic): 512^2 40 / 26
+//     against 55 / 44; 1100^2 209 / 79 against 120 / 72; 80^3 102 / 59 against 127 / 80; 110^3
+//     316 / 123 against 228 / 123.
 // Larger lattices run bands, of the height whose tiles cost least in rounds of one tile per SIMD
 // (a band of r rows takes r + 8 through the y half and r through the x half).
 void auto_plan(qlg_ctx* c) {
@@ -282,9 +294,8 @@ void auto_plan(qlg_ctx* c) {
   }
   const int64_t sites = c->L.psi_elems / 5;
   const bool c64 = c->p.dtype == QLG_C64, plain = c->p.split == QLG_SPLIT_PLAIN;
-  const int64_t most = plain ? (c->p.ndim == 2 ? (c64 ? 1100000 : 700000) : (c64 ? 1000000 : 500000))
-                             : (c->p.ndim == 2 ? (c64 ? 2500000 : 2000000) : int64_t(1) << 25);
-  if (sites <= most) {
+  const int64_t most = plain ? (c64 ? 1100000 : 700000) : c->p.ndim == 2 ? 2500000 : int64_t(1) << 25;
+  if (sites <= most && lines_fit(c)) {
     c->lines = true;
     c->eff.tile_rows = qlg::kLineTileRows;
     return;
@@ -303,7 +314,7 @@ qlg_status build_tiles(qlg_ctx* c) {
     auto_plan(c);
   } else {
     c->eff = c->tuning;
-    c->lines = c->form == Form::kLines;
+    c->lines = c->form == Form::kLines && lines_fit(c);
     if (c->lines) c->eff.tile_rows = qlg::kLineTileRows;
   }
   const int W = qlg::line_cols(c->p.dtype);
@@ -319,11 +330,11 @@ qlg_status build_tiles(qlg_ctx* c) {
     }
     for (int64_t k = 0; k < (int64_t)d.ntx * d.nty * d.nz; ++k) t2i.push_back(i);
     if (c->lines) {
-      const int32_t ncol = (d.nx + W - 1) / W;
+      const int64_t ncol = (d.nx + W - 1) / W;
       d.line_y = c->nline_y;
       d.line_z = c->nline_z;
-      c->nline_y += ncol * ((d.ny + qlg::kValid2D - 1) / qlg::kValid2D) * d.nz;
-      if (c->p.ndim == 3) c->nline_z += ncol * ((d.nz + qlg::kValid2D - 1) / qlg::kValid2D) * d.ny;
+      c->nline_y += (int32_t)(ncol * qlg::line_windows<int64_t>(d.ny, d.nz));
+      if (c->p.ndim == 3) c->nline_z += (int32_t)(ncol * qlg::line_windows<int64_t>(d.nz, d.ny));
     } else if (c->p.ndim == 3) {
       d.tile_begin_z = (int32_t)t2i_z.size();
       tiles_z(d.nx, d.nz, c->eff.tile_rows, &d.ntx_z, &d.ntz);
@@ -972,7 +983,7 @@ qlg_status qlg_autotune(qlg_ctx* c) {
     std::sort(rows.begin(), rows.end(), [](int x, int y) { return x > y; });
     for (int split = 0; split <= 1; ++split)
       for (int r : rows) cand.push_back(Plan{qlg_tuning{1, r, c->tuning.use_graph, split}, Form::kBands});
-    cand.push_back(Plan{qlg_tuning{1, qlg::kLineTileRows, c->tuning.use_graph, 0}, Form::kLines});
+    if (lines_fit(c)) cand.push_back(Plan{qlg_tuning{1, qlg::kLineTileRows, c->tuning.use_graph, 0}, Form::kLines});
   }
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess) return fail(c, QLG_ERR_DEVICE, "event create");

@@ -37,6 +37,19 @@ constexpr int kRecord = 16;      // doubles per instance in an observables recor
 constexpr int kLanes = 64;       // wavefront width on gfx950
 constexpr int kHalo2D = 4;       // x halo of the 2D kernel (4 I' per axis per step)
 constexpr int kValid2D = kLanes - 2 * kHalo2D;
+constexpr int kLineHalo = 4;     // halo slots at each end of a line of the line passes
+// The slots a line of n sites takes in a line pass, n + 8 with its halos, or whole 56-site windows
+// where those are fewer (line_slot in qlg_lanes.hpp), and the windows (wavefronts) of nlines lines.
+template <typename I>
+constexpr I line_slots(I n) {
+  const I v = kLanes - 2 * kLineHalo, tiles = (n + v - 1) / v * v;
+  return n + 2 * kLineHalo < tiles ? n + 2 * kLineHalo : tiles;
+}
+template <typename I>
+constexpr I line_windows(I n, I nlines) {
+  const I v = kLanes - 2 * kLineHalo;
+  return (nlines * line_slots(n) - 2 * kLineHalo + v - 1) / v;
+}
 
 struct LaunchGeom {
   const InstDesc* inst;        // device [nbatch]

@@ -695,9 +695,9 @@ void k_step2d(StepArgs<T> A) {
 // ---------------------------------------------------------------------------
 // 2D and 3D step as line passes: the four substeps of one axis per launch, that axis along the lanes
 // ---------------------------------------------------------------------------
-// A wavefront takes 64 consecutive sites of a line along the axis, 56 interior and 4 halo on each
-// side (four I' of radius one), and runs the axis' four substeps in registers with lane moves: no
-// row pipeline, so a launch lasts four substeps where a band of R rows lasts R + 8 of them.  A step
+// A wavefront takes a window of 64 slots of the lines along the axis, 56 of them its own and 4 halo on
+// each side (four I' of radius one; line_slot), and runs the axis' four substeps in registers with
+// lane moves: no row pipeline, so a launch lasts four substeps where a band of R rows lasts R + 8 of them.  A step
 // is one launch per axis (z, y, x), the state read and written once per launch: twice (three
 // times) the HBM traffic of a band launch, for 64/56 of the arithmetic instead of
 // 64/56 (R + 8)/R in the row pipeline.  For lattices that cannot give every SIMD a tall band, and
@@ -722,10 +722,10 @@ __device__ __forceinline__ void line_substeps(const StepArgs<T>& A, cx<T> (&a)[5
   scale_by(a, b, substep_unscale<T, 4>(plain, plain_u));
 }
 
-// Lines along x: a workgroup takes kLineRows (or half of them, to fill the chip with smaller
-// workgroups) rows of one 56-column tile, one row per wavefront.  The tiles are those of the
-// 8-row band table, one overlap partial each; a launch that records the overlap runs the
-// whole tile in one workgroup and sums its wavefronts in LDS.
+// Lines along x, one window per wavefront.  A workgroup takes kLineRows windows, or half of them, of
+// one entry of the 8-row band table (an instance's entries hold at least as many windows as it
+// needs; the others end at once), with one overlap partial per entry: a launch that records the
+// overlap runs the whole entry in one workgroup and sums its wavefronts in LDS.
 constexpr int kLineRows = 8;
 template <typename T, bool kExt>
 __global__ __launch_bounds__(kLanes * kLineRows) void k_line_x(StepArgs<T> A) {
@@ -736,16 +736,12 @@ __global__ __launch_bounds__(kLanes * kLineRows) void k_line_x(StepArgs<T> A) {
   const int blk = xcd_contiguous_block(blockIdx.x, gridDim.x);
   const int w = blk / parts;
   const InstDesc d = A.inst[A.tile2inst[w]];
-  const int t = w - d.tile_begin;
-  const int tx = t % d.ntx, tb = t / d.ntx;
-  const int y = (tb % d.nty) * kLineRows + (blk % parts) * nw + wv, plane = tb / d.nty;
+  const int window = (w - d.tile_begin) * kLineRows + (blk % parts) * nw + wv, nlines = d.ny * d.nz;
   double ore = 0.0, oim = 0.0;
-  if (y < d.ny) {   // wavefront-uniform
-    const int x = tx * kValid2D - kHalo2D + lane;
-    const int xw = (int)wrap64(x, d.nx);
-    const bool own = lane >= kHalo2D && lane < kLanes - kHalo2D && x < d.nx;
-    const int64_t row = ((int64_t)plane * d.ny + y) * d.nx;
-    const cx<T>* src = A.in + d.off + row + xw;
+  if ((uint32_t)window < line_windows((uint32_t)d.nx, (uint32_t)nlines)) {   // wavefront-uniform
+    const LineSlot l = line_slot(window, lane, d.nx, nlines);
+    const int site = l.line * d.nx + l.at;
+    const cx<T>* src = A.in + d.off + site;
     cx<T> a[5], b[5];
 #pragma unroll
     for (int m = 0; m < 5; ++m) {
@@ -753,10 +749,10 @@ __global__ __launch_bounds__(kLanes * kLineRows) void k_line_x(StepArgs<T> A) {
       b[m] = src[(5 + m) * d.stride];
     }
     T ext = T(0);
-    if constexpr (kExt) ext = ext_angle(A, d, row + xw);
+    if constexpr (kExt) ext = ext_angle(A, d, site);
     line_substeps<T, kExt>(A, a, b, ext);
-    if (own) {
-      const int64_t s = d.off + row + x;
+    if (l.own) {
+      const int64_t s = d.off + site;
       if (A.overlap) {
         // the state before the step: the location this lane writes below, and no other lane reads
 #pragma unroll
@@ -790,9 +786,11 @@ __global__ __launch_bounds__(kLanes * kLineRows) void k_line_x(StepArgs<T> A) {
 }
 
 // Lines along y or z: a workgroup takes kLineCols neighbouring columns (64 bytes of a row) of one
-// 56-row tile, one column per wavefront.  The tile, 64 rows with halo x kLineCols columns x 10
-// planes, is read and written along x and turned in LDS; rows are padded by one element, so that
-// neither side has bank conflicts.
+// window, one column per wavefront; a column's lines in all planes are those laid end to end, and
+// neighbouring workgroups take neighbouring columns, so that an XCD keeps to the rows (planes) that it
+// had in the pass along x: with the columns outermost instead, 448^2 complex64 took 40 us a step
+// instead of 34.  The window, 64 slots x kLineCols columns x 10 planes, is read and written along x
+// and turned in LDS; rows are padded by one element, so that neither side has bank conflicts.
 template <typename T>
 constexpr int kLineCols = 64 / (int)sizeof(cx<T>);
 template <typename T, bool kExt>
@@ -810,19 +808,17 @@ __global__ __launch_bounds__(kLanes * kLineCols<T>) void k_line_yz(StepArgs<T> A
   }
   const InstDesc d = A.inst[lo];
   const int n = zp ? d.nz : d.ny;   // extent along the lines
-  const int64_t rstride = zp ? (int64_t)d.nx * d.ny : (int64_t)d.nx;
-  const int64_t pstride = zp ? (int64_t)d.nx : (int64_t)d.nx * d.ny;
+  const int rstride = zp ? d.nx * d.ny : d.nx, pstride = zp ? d.nx : d.nx * d.ny;
   const int t = grp - (zp ? d.line_z : d.line_y);
-  const int ncol = (d.nx + W - 1) / W, ntile = (n + kValid2D - 1) / kValid2D;
-  const int gx = t % ncol, tr = t / ncol;
-  const int r0 = (tr % ntile) * kValid2D - kHalo2D, plane = tr / ntile;
-  const int64_t base = d.off + plane * pstride;
-  // loads and stores: this thread's element of the tile
+  const int ncol = (d.nx + W - 1) / W, nlines = zp ? d.ny : d.nz;
+  const int gx = t % ncol, window = t / ncol;
+  // loads and stores: this thread's element of the window, slot er, column ec
   const int er = threadIdx.x / W, ec = threadIdx.x % W;
-  const int ex = gx * W + ec, ey = r0 + er;
-  const bool ex_ok = ex < d.nx;
+  const int ex = gx * W + ec < d.nx ? gx * W + ec : d.nx - 1;
+  const LineSlot le = line_slot(window, er, n, nlines);
+  const int64_t es = d.off + (le.line * pstride + le.at * rstride + ex);
   {
-    const cx<T>* src = A.in + base + wrap64(ey, n) * rstride + (ex_ok ? ex : d.nx - 1);
+    const cx<T>* src = A.in + es;
     cx<T> v[10];
 #pragma unroll
     for (int p = 0; p < 10; ++p) v[p] = src[p * d.stride];
@@ -839,8 +835,9 @@ __global__ __launch_bounds__(kLanes * kLineCols<T>) void k_line_yz(StepArgs<T> A
   }
   T ext = T(0);
   if constexpr (kExt) {
-    const int cxw = gx * W + wv < d.nx ? gx * W + wv : d.nx - 1;
-    ext = ext_angle(A, d, plane * pstride + wrap64(r0 + lane, n) * rstride + cxw);
+    const LineSlot l = line_slot(window, lane, n, nlines);
+    const int x = gx * W + wv < d.nx ? gx * W + wv : d.nx - 1;
+    ext = ext_angle(A, d, l.line * pstride + l.at * rstride + x);
   }
   line_substeps<T, kExt>(A, a, b, ext);
   // each wavefront writes back the column it read
@@ -850,8 +847,8 @@ __global__ __launch_bounds__(kLanes * kLineCols<T>) void k_line_yz(StepArgs<T> A
     buf[5 + m][lane][wv] = b[m];
   }
   __syncthreads();
-  if (er >= kHalo2D && er < kLanes - kHalo2D && ey < n && ex_ok) {
-    cx<T>* dst = A.out + base + ey * rstride + ex;
+  if (le.own && gx * W + ec < d.nx) {
+    cx<T>* dst = A.out + es;
 #pragma unroll
     for (int p = 0; p < 10; ++p) dst[p * d.stride] = buf[p][er][ec];
   }

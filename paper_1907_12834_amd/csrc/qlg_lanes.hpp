@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "qlg_internal.hpp"
 #include "qlg_math.hpp"
 
 namespace qlg {
@@ -97,6 +98,39 @@ __device__ __forceinline__ int xcd_contiguous_block(int b, int nblocks) {
   const int x = b % kXcds, l = b / kXcds;
   const int per = nblocks / kXcds, extra = nblocks % kXcds;
   return x * per + (x < extra ? x : extra) + l;
+}
+
+// Line passes: the lines along an axis are laid end to end, each with 4 halo slots on both sides
+// (n + 8 slots), and cut into windows of 64 slots that overlap by 8: lane i of window w holds slot
+// 56 w + i, and lanes 4..59 own their sites.  The halo slots between two lines of one window serve as
+// those at its ends do, so a window holds the end of one line and the start of the next: nlines lines
+// take (nlines (n + 8) - 8) / 56 windows, where windows that begin with each line would take
+// nlines ceil(n / 56): 1.4 per line of 70 sites instead of 2, 4.7 of 256 instead of 5.  Where n is at
+// or just below a multiple of 56 the latter are fewer, and the line's slots are that multiple.  Time
+// per step with windows that begin with each line, and with these (us, complex128 / complex64): 64^3
+// 131 / 93, 109 / 82; 50 x 70 x 90 135 / 95, 127 / 90; 128^3 785 / 525, 700 / 435; 256^3 5360 / 3365,
+// 5200 / 3170; 1024^2 215 / 140, 215 / 132; the reverse step of 64^3 368 in complex64, 290.
+constexpr int kLineStride = kLanes - 2 * kLineHalo;
+struct LineSlot {
+  int line;   // its line (past the last one: any)
+  int at;     // its site, periodic
+  bool own;   // a site this lane computes
+};
+__device__ __forceinline__ LineSlot line_slot(uint32_t window, int lane, int n, int nlines) {
+  const uint32_t len = line_slots((uint32_t)n);
+  const uint32_t slot = window * kLineStride, q = slot / len, r = slot - q * len + (uint32_t)lane;
+  LineSlot s;
+  uint32_t d;
+  if (len != (uint32_t)n + 2 * kLineHalo) d = 0;   // whole windows: none crosses lines
+  else if (len >= kLanes) d = r >= len ? 1u : 0u;
+  else d = r / len;
+  const bool in = q + d < (uint32_t)nlines;
+  s.line = (int)(in ? q + d : q);
+  const int pos = (int)(r - d * len) - kLineHalo;
+  if (n < kLineHalo) s.at = (int)((uint32_t)(pos + kLineHalo * n) % (uint32_t)n);
+  else s.at = pos < 0 ? pos + n : pos >= n ? pos - n : pos;   // whole windows: n > 48, pos < n + 12
+  s.own = in && lane >= kLineHalo && lane < kLanes - kLineHalo && s.at == pos;
+  return s;
 }
 
 }  // namespace qlg

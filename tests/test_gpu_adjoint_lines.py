@@ -57,3 +57,11 @@ def test_angles(eps, scale):
     psi[:, :, :20] *= np.linspace(0.01, 1.0, 20)
     psi[1:4, :, 40:50] = 0.0
     _check(psi, eps, 2, 2, "c128")
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("shape", [(9, 48), (7, 49), (40, 5), (20, 7, 49), (7, 49, 5), (100, 3, 6)], ids=str)
+def test_lines_laid_end_to_end(shape, dtype):
+    """Windows that hold the ends of two or more lines along x, y and z."""
+    psi = qi.random_field(shape, seed=63, scale=0.4).astype(np.complex64).astype(np.complex128)
+    _check(psi, 0.3, 3, 2, dtype)

@@ -103,3 +103,21 @@ def test_saved_plan_of_line_passes(tmp_path, monkeypatch):
     assert out[2][0] == {"steps_per_pass": 1, "tile_rows": 24, "use_graph": 0, "qubit_split": 1}
     a, b, c = (x[1].get_qubits()[0].cpu().numpy() for x in out)
     assert np.array_equal(a, b) and rel_l2(c, a) <= 1e-13
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("shapes", [[(11, 47), (9, 48), (10, 49)], [(300, 4)], [(31, 70), (1, 104), (25, 105)],
+                                    [(5, 49, 20), (20, 5, 49)], [(49, 20, 3), (9, 100, 4)], [(100, 7, 9)], [(6, 21, 2)]], ids=str)
+def test_lines_laid_end_to_end(shapes, dtype):
+    """Windows that hold the ends of two lines, of many short ones, or (48, 104 sites: as many slots
+    either way; 49, 105: fewer end to end) begin with each line; and the overlap of the last step."""
+    qs = _qubits(shapes, 101)
+    lat = _lattice(shapes, dtype)
+    lat.set_qubits([torch.from_numpy(q) for q in qs])
+    lat.step(3)
+    tol = 1e-12 if dtype == "c128" else 1e-5
+    for q, got, o in zip(qs, lat.get_qubits(), lat.observables()):
+        ref, prev = _oracle(q, 3, "interleaved"), _oracle(q, 2, "interleaved")
+        assert rel_l2(got.cpu().numpy(), ref) <= tol
+        ov = 0.3 ** (q.ndim - 2) * np.vdot(ref[0] + ref[1], prev[0] + prev[1])
+        assert abs(o["overlap"] - ov) <= tol * abs(ov)
