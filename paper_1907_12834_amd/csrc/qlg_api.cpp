@@ -168,7 +168,7 @@ struct qlg_ctx {
   int32_t* d_tile2inst = nullptr;
   int32_t* d_chunk2inst = nullptr;
   int32_t* d_tile2inst_z = nullptr;   // 3D z pass
-  int32_t ntiles = 0, ntiles_z = 0, nline_y = 0, nline_z = 0;
+  int32_t ntiles = 0, ntiles_z = 0, nline[3] = {0, 0, 0};
   qlg_tuning tuning{1, 32, 0, 0};  // as set, tuned or the default; qlg_get_tuning's answer
   Form form = Form::kAuto;
   qlg_tuning eff{1, 32, 0, 0};     // what the launches use (build_tiles)
@@ -202,8 +202,7 @@ struct qlg_ctx {
     g.tile2inst_z = d_tile2inst_z;
     g.ntiles = ntiles;
     g.ntiles_z = ntiles_z;
-    g.nline_y = nline_y;
-    g.nline_z = nline_z;
+    for (int q = 0; q < 3; ++q) g.nline[q] = nline[q];
     g.nchunks = L.nchunks;
     g.nbatch = p.nbatch;
     return g;
@@ -273,7 +272,11 @@ bool lines_fit(const qlg_ctx* c) {
 //     against 55 / 44; 1100^2 209 / 79 against 120 / 72; 80^3 102 / 59 against 127 / 80; 110^3
 //     316 / 123 against 228 / 123.
 // Larger lattices run bands, of the height whose tiles cost least in rounds of one tile per SIMD
-// (a band of r rows takes r + 8 through the y half and r through the x half).
+// (a band of r rows takes r + 8 through the y half and r through the x half).  In FP64 a round costs
+// the same whether another runs beside it or not.  In FP32 one wavefront leaves a SIMD's issue
+// slots half empty: two take 1.3 times as long as one (2048^2: 4.3 us a row alone, 6.0 in pairs; 9.0,
+// 10.6 and 13.8 for three to five), so a pair of rounds counts 18 and one alone 13 (2048^2: 38 rows in
+// 500 us, where the count of single rounds took 76 rows and 687).
 void auto_plan(qlg_ctx* c) {
   c->eff = c->tuning;
   c->lines = false;
@@ -302,7 +305,8 @@ void auto_plan(qlg_ctx* c) {
   }
   int64_t best = 0;
   for (int r = kMaxTileRows; r >= kMinTileRows; --r) {
-    const int64_t cost = (band_tiles(c, r) + nsimd - 1) / nsimd * (2 * r + 8);
+    const int64_t rounds = (band_tiles(c, r) + nsimd - 1) / nsimd;
+    const int64_t cost = (c64 ? rounds / 2 * 18 + rounds % 2 * 13 : rounds) * (2 * r + 8);
     if (!best || cost < best) { best = cost; c->eff.tile_rows = r; }
   }
 }
@@ -318,7 +322,7 @@ qlg_status build_tiles(qlg_ctx* c) {
     if (c->lines) c->eff.tile_rows = qlg::kLineTileRows;
   }
   const int W = qlg::line_cols(c->p.dtype);
-  c->nline_y = c->nline_z = 0;
+  c->nline[0] = c->nline[1] = c->nline[2] = 0;
   for (int i = 0; i < c->p.nbatch; ++i) {
     InstDesc& d = c->L.inst[i];
     d.tile_begin = (int32_t)t2i.size();
@@ -331,10 +335,10 @@ qlg_status build_tiles(qlg_ctx* c) {
     for (int64_t k = 0; k < (int64_t)d.ntx * d.nty * d.nz; ++k) t2i.push_back(i);
     if (c->lines) {
       const int64_t ncol = (d.nx + W - 1) / W;
-      d.line_y = c->nline_y;
-      d.line_z = c->nline_z;
-      c->nline_y += (int32_t)(ncol * qlg::line_windows<int64_t>(d.ny, d.nz));
-      if (c->p.ndim == 3) c->nline_z += (int32_t)(ncol * qlg::line_windows<int64_t>(d.nz, d.ny));
+      for (int q = 0; q < 3; ++q) d.line[q] = c->nline[q];
+      c->nline[0] += (int32_t)((qlg::line_windows<int64_t>(d.nx, (int64_t)d.ny * d.nz) + qlg::kLineTileRows - 1) / qlg::kLineTileRows);
+      c->nline[1] += (int32_t)(ncol * qlg::line_windows<int64_t>(d.ny, d.nz));
+      if (c->p.ndim == 3) c->nline[2] += (int32_t)(ncol * qlg::line_windows<int64_t>(d.nz, d.ny));
     } else if (c->p.ndim == 3) {
       d.tile_begin_z = (int32_t)t2i_z.size();
       tiles_z(d.nx, d.nz, c->eff.tile_rows, &d.ntx_z, &d.ntz);

@@ -21,12 +21,11 @@ struct InstDesc {
   int32_t ntx, nty;   // tiles along x and bands along y (nty = 1 in 1D); 3D: ntx * nty * nz tiles
   // The band form's 3D z pass: first tile, 64-column tiles along x, bands along z (ntx_z * ntz * ny
   // tiles).  A plan of line passes has no such pass and keeps there the first group of the
-  // instance in its y and z launches.
+  // instance in its x, y and z launches.
   union {
-    struct { int32_t tile_begin_z, ntx_z; };
-    struct { int32_t line_y, line_z; };
+    struct { int32_t tile_begin_z, ntx_z, ntz; };
+    struct { int32_t line[3]; };
   };
-  int32_t ntz;
   int32_t chunk_begin;// first 256-site chunk for elementwise / reduction kernels
   int32_t nchunks;
 };
@@ -57,7 +56,7 @@ struct LaunchGeom {
   const int32_t* chunk2inst;   // device [nchunks]
   const int32_t* tile2inst_z;  // device [ntiles_z], 3D z pass
   int32_t ntiles, nchunks, nbatch, ntiles_z;
-  int32_t nline_y, nline_z;    // workgroups of the y and z line launches (0: not a plan of line passes)
+  int32_t nline[3];            // groups of the x, y and z line launches (0: not a plan of line passes)
 };
 
 // The psi-independent diagonal term (V(x) + mu) psi_m of the equation of motion
@@ -99,7 +98,7 @@ hipError_t launch_step2d(int dtype, bool plain, bool overlap, int tile_rows, boo
 // it, from in to out (not in place).  Needs the 8-row tile table and the groups of the plan of
 // line passes.  plain_u: this pass applies the plain split's U; prev (may equal out): as above, for
 // an x pass that records the overlap.
-constexpr int kLineTileRows = 8;                                             // rows of an x tile
+constexpr int kLineTileRows = 8;                                             // windows of an x group
 constexpr int line_cols(int dtype) { return dtype == 0 ? 8 : 4; }            // columns of a y or z group
 hipError_t launch_line(int dtype, int axis, bool plain, bool overlap, bool plain_u, double full_factor, const void* in,
                        void* out, const void* prev, const LaunchGeom& g, double tg0, double tg1, double tg25,

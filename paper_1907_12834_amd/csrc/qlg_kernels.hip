@@ -722,23 +722,36 @@ __device__ __forceinline__ void line_substeps(const StepArgs<T>& A, cx<T> (&a)[5
   scale_by(a, b, substep_unscale<T, 4>(plain, plain_u));
 }
 
-// Lines along x, one window per wavefront.  A workgroup takes kLineRows windows, or half of them, of
-// one entry of the 8-row band table (an instance's entries hold at least as many windows as it
-// needs; the others end at once), with one overlap partial per entry: a launch that records the
-// overlap runs the whole entry in one workgroup and sums its wavefronts in LDS.
+// The instance of group grp of the line launch along `axis`: the last whose first group is not
+// beyond it.
+__device__ __forceinline__ const InstDesc& line_inst(const InstDesc* inst, int nbatch, int axis, int grp) {
+  int lo = 0, hi = nbatch;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (inst[mid].line[axis] <= grp) lo = mid;
+    else hi = mid;
+  }
+  return inst[lo];
+}
+
+// Lines along x, one window per wavefront and kLineRows windows per group: one workgroup if the
+// launch records the overlap, whose wavefronts are then summed in LDS, or two, to fill the chip with
+// smaller workgroups.  The overlap partials are those of the 8-row band table, at least as many as
+// the groups: a group writes its own and zeros to those that none has.
 constexpr int kLineRows = 8;
 template <typename T, bool kExt>
-__global__ __launch_bounds__(kLanes * kLineRows) void k_line_x(StepArgs<T> A) {
+__global__ __launch_bounds__(kLanes * kLineRows) void k_line_x(StepArgs<T> A, int nbatch) {
   __shared__ double red[2][kLineRows];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & (kLanes - 1);
-  const int nw = blockDim.x / kLanes, parts = kLineRows / nw;   // workgroups per tile
+  const int nw = blockDim.x / kLanes, parts = kLineRows / nw;   // workgroups per group
   const int blk = xcd_contiguous_block(blockIdx.x, gridDim.x);
-  const int w = blk / parts;
-  const InstDesc d = A.inst[A.tile2inst[w]];
-  const int window = (w - d.tile_begin) * kLineRows + (blk % parts) * nw + wv, nlines = d.ny * d.nz;
+  const InstDesc d = line_inst(A.inst, nbatch, 0, blk / parts);
+  const int w = blk / parts - d.line[0], nlines = d.ny * d.nz;   // group of the instance
+  const int window = w * kLineRows + (blk % parts) * nw + wv;
+  const uint32_t nwindows = line_windows((uint32_t)d.nx, (uint32_t)nlines);
   double ore = 0.0, oim = 0.0;
-  if ((uint32_t)window < line_windows((uint32_t)d.nx, (uint32_t)nlines)) {   // wavefront-uniform
+  if ((uint32_t)window < nwindows) {   // wavefront-uniform
     const LineSlot l = line_slot(window, lane, d.nx, nlines);
     const int site = l.line * d.nx + l.at;
     const cx<T>* src = A.in + d.off + site;
@@ -781,7 +794,10 @@ __global__ __launch_bounds__(kLanes * kLineRows) void k_line_x(StepArgs<T> A) {
   if (threadIdx.x < 2) {
     double s = 0.0;
     for (int j = 0; j < kLineRows; ++j) s += red[threadIdx.x][j];
-    A.ovpart[2 * w + threadIdx.x] = s;
+    double* part = A.ovpart + 2 * (int64_t)d.tile_begin + threadIdx.x;
+    part[2 * w] = s;
+    const int ngroups = (int)((nwindows + kLineRows - 1) / kLineRows), nparts = d.ntx * d.nty * d.nz;
+    for (int j = w + ngroups; j < nparts; j += ngroups) part[2 * j] = 0.0;
   }
 }
 
@@ -798,18 +814,11 @@ __global__ __launch_bounds__(kLanes * kLineCols<T>) void k_line_yz(StepArgs<T> A
   constexpr int W = kLineCols<T>;
   __shared__ cx<T> buf[10][kLanes][W + 1];
   const bool zp = A.zpass != 0;
-  // the instance is the last one whose first group is not beyond this one
   const int grp = xcd_contiguous_block(blockIdx.x, gridDim.x);
-  int lo = 0, hi = nbatch;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if ((zp ? A.inst[mid].line_z : A.inst[mid].line_y) <= grp) lo = mid;
-    else hi = mid;
-  }
-  const InstDesc d = A.inst[lo];
+  const InstDesc d = line_inst(A.inst, nbatch, zp ? 2 : 1, grp);
   const int n = zp ? d.nz : d.ny;   // extent along the lines
   const int rstride = zp ? d.nx * d.ny : d.nx, pstride = zp ? d.nx : d.nx * d.ny;
-  const int t = grp - (zp ? d.line_z : d.line_y);
+  const int t = grp - d.line[zp ? 2 : 1];
   const int ncol = (d.nx + W - 1) / W, nlines = zp ? d.ny : d.nz;
   const int gx = t % ncol, window = t / ncol;
   // loads and stores: this thread's element of the window, slot er, column ec
@@ -1201,12 +1210,12 @@ static hipError_t launch_line_t(int axis, bool plain, bool overlap, bool plain_u
   args.zpass = axis == 2 ? 1 : 0;
   if (axis == 0) {
     const int nw = overlap ? kLineRows : kLineRows / 2;
-    const dim3 grid(g.ntiles * (kLineRows / nw)), block(kLanes * nw);
-    if (ext.on()) launch_timed(k_line_x<T, true>, grid, block, 0, st, ev0, ev1, args);
-    else launch_timed(k_line_x<T, false>, grid, block, 0, st, ev0, ev1, args);
+    const dim3 grid(g.nline[0] * (kLineRows / nw)), block(kLanes * nw);
+    if (ext.on()) launch_timed(k_line_x<T, true>, grid, block, 0, st, ev0, ev1, args, g.nbatch);
+    else launch_timed(k_line_x<T, false>, grid, block, 0, st, ev0, ev1, args, g.nbatch);
     return hipGetLastError();
   }
-  const dim3 grid(axis == 2 ? g.nline_z : g.nline_y), block(kLanes * kLineCols<T>);
+  const dim3 grid(g.nline[axis]), block(kLanes * kLineCols<T>);
   if (ext.on()) launch_timed(k_line_yz<T, true>, grid, block, 0, st, ev0, ev1, args, g.nbatch);
   else launch_timed(k_line_yz<T, false>, grid, block, 0, st, ev0, ev1, args, g.nbatch);
   return hipGetLastError();
@@ -1216,8 +1225,8 @@ hipError_t launch_line(int dtype, int axis, bool plain, bool overlap, bool plain
                        void* out, const void* prev, const LaunchGeom& g, double tg0, double tg1, double tg25,
                        const ExtPot& ext, double* ovpart, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   static_assert(kLineCols<float> == line_cols(0) && kLineCols<double> == line_cols(1), "columns per line group");
-  static_assert(kLineRows == kLineTileRows, "rows of an x tile");
-  if (axis < 0 || axis > 2 || (axis == 2 && g.nline_z == 0) || (axis == 1 && g.nline_y == 0)) return hipErrorInvalidValue;
+  static_assert(kLineRows == kLineTileRows, "windows of an x group");
+  if (axis < 0 || axis > 2 || g.nline[axis] == 0) return hipErrorInvalidValue;
   if (dtype == 0)
     return launch_line_t<float>(axis, plain, overlap, plain_u, full_factor, in, out, prev, g, tg0, tg1, tg25, ext,
                                 ovpart, st, ev0, ev1);
