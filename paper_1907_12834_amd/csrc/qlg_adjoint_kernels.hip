@@ -257,9 +257,7 @@ __device__ __forceinline__ void block_sum3(double v0, double v1, double v2, doub
   double v[3] = {v0, v1, v2};
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    double s = v[k];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, kLanes);
+    const double s = wave_sum(v[k]);
     if (lane == 0) red[k][wv] = s;
   }
   __syncthreads();
@@ -487,9 +485,7 @@ __device__ __forceinline__ void adjoint_substeps(cx<double> (&la)[5], cx<double>
 __device__ __forceinline__ void store_dg(double (&dg)[3], bool own, int lane, double* __restrict__ part) {
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    dg[k] = own ? dg[k] : 0.0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) dg[k] += __shfl_xor(dg[k], o, kLanes);
+    dg[k] = wave_sum(own ? dg[k] : 0.0);
   }
   if (lane == 0) {
     part[0] = dg[0];
@@ -600,9 +596,8 @@ __global__ __launch_bounds__(kDgThreads) void k_dg_accumulate(const double* __re
   }
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o, kLanes);
-    if (lane == 0) red[k][wv] = v[k];
+    const double s = wave_sum(v[k]);
+    if (lane == 0) red[k][wv] = s;
   }
   __syncthreads();
   if (threadIdx.x < 3) {

@@ -31,13 +31,6 @@
 
 namespace qlg {
 
-// Sum over the 64 lanes of a wavefront (every lane returns the total).
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kLanes);
-  return v;
-}
-
 // Row access of the 2D kernel through buffer resources.  A resource covers one row of one
 // amplitude plane (base and record count are wavefront-uniform, in scalar registers); a lane
 // passes its byte offset in the row.  The hardware drops a store whose offset is at or beyond
@@ -1024,37 +1017,46 @@ __global__ __launch_bounds__(kChunk) void k_observables(const cx<T>* __restrict_
 //   rec[i][0..9]  observable sums (kNObs), rec[i][10..11] overlap sums,
 //   rec[i][12]    reference qubit-norm sum, rec[i][13] step count,
 //   rec[i][14]    flags (1: overlap valid, 2: reference valid), rec[i][15] = 0.
-__global__ __launch_bounds__(kChunk) void k_reduce_record(LaunchGeom g, const double* __restrict__ part,
-                                                         const double* __restrict__ ovpart,
-                                                         const double* __restrict__ ref,
-                                                         double* __restrict__ rec, double step) {
-  __shared__ double sums[kNObs], ovs[kNObs];
+// The partials are read as they lie, one double per thread, in steps of the block's 960 threads: a
+// multiple of ten, so that a thread stays with one observable.  Then wavefront k adds the threads of
+// observable k (the two overlap sums: wavefronts 10 and 11).  2.6 us on small lattices, where a thread
+// per chunk and twice ten sums over the block took 6.2; 30 us at 16384 chunks (2048^2) instead of 38,
+// bound by what one CU reads of other XCDs' output (44 GB/s; with 32 loads in flight per thread
+// instead of 8 no faster).
+constexpr int kRecordThreads = 960;
+__global__ __launch_bounds__(kRecordThreads) void k_reduce_record(LaunchGeom g, const double* __restrict__ part,
+                                                                 const double* __restrict__ ovpart,
+                                                                 const double* __restrict__ ref,
+                                                                 double* __restrict__ rec, double step) {
+  static_assert(kRecordThreads % kNObs == 0 && kRecordThreads % 2 == 0 && kRecordThreads / kLanes >= kNObs + 2,
+                "threads keep to one observable; a wavefront for each sum");
+  __shared__ double red[2][kRecordThreads], sums[kNObs + 2];
   const InstDesc d = g.inst[blockIdx.x];
-  double v[kNObs];
-#pragma unroll
-  for (int k = 0; k < kNObs; ++k) v[k] = 0.0;
-  for (int c = threadIdx.x; c < d.nchunks; c += kChunk) {
-    const double* p = part + (int64_t)(d.chunk_begin + c) * kNObs;
-#pragma unroll
-    for (int k = 0; k < kNObs; ++k) v[k] += p[k];
-  }
-  block_sum_store(v, sums);
-  __syncthreads();   // block_sum_store's own LDS is reused below
-#pragma unroll
-  for (int k = 0; k < kNObs; ++k) v[k] = 0.0;
+  const int lane = threadIdx.x & (kLanes - 1), wv = threadIdx.x >> 6;
+  double v = 0.0, o = 0.0;
+  const double* p = part + (int64_t)d.chunk_begin * kNObs;
+#pragma unroll 8
+  for (int64_t c = threadIdx.x; c < (int64_t)d.nchunks * kNObs; c += kRecordThreads) v += p[c];
   if (ovpart) {
-    const int nt = d.ntx * d.nty * d.nz;
-    for (int t = threadIdx.x; t < nt; t += kChunk) {
-      v[0] += ovpart[2 * (d.tile_begin + t)];
-      v[1] += ovpart[2 * (d.tile_begin + t) + 1];
-    }
+    const double* q = ovpart + 2 * (int64_t)d.tile_begin;
+#pragma unroll 8
+    for (int64_t t = threadIdx.x; t < 2 * (int64_t)d.ntx * d.nty * d.nz; t += kRecordThreads) o += q[t];
   }
-  block_sum_store(v, ovs);
+  red[0][threadIdx.x] = v;
+  red[1][threadIdx.x] = o;
+  __syncthreads();
+  if (wv < kNObs + 2) {   // wavefront-uniform
+    const bool ov = wv >= kNObs;
+    const int step_k = ov ? 2 : kNObs;
+    double s = 0.0;
+    for (int t = (ov ? wv - kNObs : wv) + step_k * lane; t < kRecordThreads; t += step_k * kLanes) s += red[ov][t];
+    s = wave_sum(s);
+    if (lane == 0) sums[wv] = s;
+  }
   __syncthreads();
   double* r = rec + (int64_t)blockIdx.x * kRecord;
   const int k = threadIdx.x;
-  if (k < kNObs) r[k] = sums[k];
-  else if (k < kNObs + 2) r[k] = ovs[k - kNObs];
+  if (k < kNObs + 2) r[k] = sums[k];
   else if (k == kNObs + 2) r[k] = ref ? ref[(int64_t)blockIdx.x * kRecord] : 0.0;
   else if (k == kNObs + 3) r[k] = step;
   else if (k == kNObs + 4) r[k] = (ovpart ? 1.0 : 0.0) + (ref ? 2.0 : 0.0);
@@ -1264,7 +1266,7 @@ hipError_t launch_observables(int dtype, int ndim, const void* state, const Laun
 
 hipError_t launch_record(const LaunchGeom& g, const double* part, const double* ovpart, const double* ref,
                          double* rec, int64_t step, hipStream_t st) {
-  hipLaunchKernelGGL(k_reduce_record, dim3(g.nbatch), dim3(kChunk), 0, st, g, part, ovpart, ref, rec,
+  hipLaunchKernelGGL(k_reduce_record, dim3(g.nbatch), dim3(kRecordThreads), 0, st, g, part, ovpart, ref, rec,
                      (double)step);
   return hipGetLastError();
 }

@@ -38,6 +38,29 @@ __device__ __forceinline__ cx<T> from_prev_lane(cx<T> v) {
   return cx<T>{dpp_move<kDppWaveShr1>(v.re), dpp_move<kDppWaveShr1>(v.im)};
 }
 
+// Sum over the 64 lanes of a wavefront (every lane returns the total): within the rows of 16 lanes by
+// shifts, then row by row, all through DPP moves.  Six dependent LDS exchanges of 64 bits took about
+// three times as long.
+template <int Ctrl, int RowMask>
+__device__ __forceinline__ double dpp_add(double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, Ctrl, RowMask, 0xF, false);
+  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), Ctrl, RowMask, 0xF, false);
+  return v + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v = dpp_add<0x111, 0xF>(v);   // row_shr:1, 2, 4, 8: lane 15 of each row holds its sum
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  v = dpp_add<0x118, 0xF>(v);
+  v = dpp_add<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+  v = dpp_add<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3: lane 63 holds the total
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, kLanes - 1);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), kLanes - 1);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // 2i I'_{x,q}: S_q C S_q^T C by collide_r, with lanes along x (the factor 1/(2i) is left to
 // the caller).  Q = 1: qubit b (the paper's qubit 2) moves; Q = 0: qubit a (qubit 1).
 template <typename T, int Q>
