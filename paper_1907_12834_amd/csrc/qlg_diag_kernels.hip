@@ -292,85 +292,154 @@ __global__ __launch_bounds__(kV3Threads) void k_vorticity3d(const cx<T>* __restr
 // order on every run: the non-zero count of every 256-site chunk of every plane
 // family (one family in 2D, three in 3D); one workgroup's exclusive scan of the
 // counts (the chunks of an instance are consecutive, then the instances, then
-// the families); then every chunk writes its cores at its offset, ranked inside
-// the chunk by wave ballots.  Workgroup b takes family b / nchunks and chunk
-// b % nchunks; family c's windings sit at c * cstride.
-__global__ __launch_bounds__(kChunk) void k_core_count(const int32_t* __restrict__ wind, LaunchGeom g,
+// the families); then the chunks that hold cores are written at their offsets,
+// ranked inside the chunk by wave ballots.  Chunk number k is chunk k % nchunks of
+// family k / nchunks, whose windings sit at (k / nchunks) * cstride.
+// A wavefront counts four chunks, the loads of all in flight together: a workgroup per chunk cost
+// 12.4 us for the 16384 of 2048^2, by the launch rate of workgroups; now 5.0 us.
+constexpr int kCountChunks = 4;     // chunks per wavefront
+constexpr int kScatterChunks = 8;
+constexpr int kChunkLoads = kChunk / kLanes;
+
+// Chunk number k: its instance, and the sites and windings of this lane, 64 apart.
+struct CoreChunk {
+  InstDesc d;
+  int inst, c, s0;
+  const int32_t* wind;
+  __device__ __forceinline__ CoreChunk(const LaunchGeom& g, const int32_t* w, int64_t cstride, int k, int lane) {
+    c = k / g.nchunks;
+    const int b = k - c * g.nchunks;
+    inst = g.chunk2inst[b];
+    d = g.inst[inst];
+    s0 = (b - d.chunk_begin) * kChunk + lane;
+    wind = w + (c * cstride + d.psi_off / 5);
+  }
+  __device__ __forceinline__ int32_t load(int q) const {
+    const int s = s0 + q * kLanes;
+    const int32_t w = wind[s < d.sites ? s : d.sites - 1];
+    return s < d.sites ? w : 0;
+  }
+};
+
+__global__ __launch_bounds__(kChunk) void k_core_count(const int32_t* __restrict__ wind, LaunchGeom g, int nblocks,
                                                       int64_t cstride, int64_t* __restrict__ counts) {
-  __shared__ int wsum[kChunk / kLanes];
-  const int c = blockIdx.x / g.nchunks, b = blockIdx.x - c * g.nchunks;
-  const InstDesc d = g.inst[g.chunk2inst[b]];
-  const int s = (b - d.chunk_begin) * kChunk + threadIdx.x;
-  const bool core = s < d.sites && wind[c * cstride + d.psi_off / 5 + s] != 0;
-  const int n = __popcll(__ballot(core));
-  if ((threadIdx.x & (kLanes - 1)) == 0) wsum[threadIdx.x / kLanes] = n;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int t = 0;
-    for (int k = 0; k < kChunk / kLanes; ++k) t += wsum[k];
-    counts[blockIdx.x] = t;
+  const int lane = threadIdx.x & (kLanes - 1);
+  const int first = (blockIdx.x * (kChunk / kLanes) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kCountChunks;
+  int32_t w[kCountChunks][kChunkLoads];
+#pragma unroll
+  for (int j = 0; j < kCountChunks; ++j) {
+    const CoreChunk ch(g, wind, cstride, first + j < nblocks ? first + j : nblocks - 1, lane);
+#pragma unroll
+    for (int q = 0; q < kChunkLoads; ++q) w[j][q] = ch.load(q);
+  }
+#pragma unroll
+  for (int j = 0; j < kCountChunks; ++j) {
+    int n = 0;
+#pragma unroll
+    for (int q = 0; q < kChunkLoads; ++q) n += __popcll(__ballot(w[j][q] != 0));
+    if (lane == 0 && first + j < nblocks) counts[first + j] = n;
   }
 }
 
 constexpr int kScanThreads = 1024;
+constexpr int kScanPer = 16;   // counts per thread
 
-// In place: counts[c] <- sum of counts[0..c), and *total <- the sum of all.
+// Inclusive scan over the lanes of a wavefront through DPP: shifts within the rows of 16 lanes, then
+// the last lane of row 0 into row 1, of row 2 into row 3, and of row 1 into rows 2 and 3.
+template <int Ctrl, int RowMask>
+__device__ __forceinline__ int dpp_add(int v) {
+  return v + __builtin_amdgcn_update_dpp(0, v, Ctrl, RowMask, 0xF, false);
+}
+__device__ __forceinline__ int wave_scan(int v) {
+  v = dpp_add<0x111, 0xF>(v);   // row_shr:1, 2, 4, 8
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  v = dpp_add<0x118, 0xF>(v);
+  v = dpp_add<0x142, 0xA>(v);   // row_bcast:15
+  return dpp_add<0x143, 0xC>(v);   // row_bcast:31
+}
+
+// In place: counts[c] <- sum of counts[0..c), and *total <- the sum of all.  A wavefront scans
+// 16 x 64 counts, the 16 wavefronts' sums go through LDS: two barriers per 16384 counts (up to 256
+// each: 32 bits hold their sum), where a scan through LDS of 1024 at a time took 20 barriers for each
+// (31 us for 16384; now 5.8, with the counts read as they lie: sixteen in a row per thread, 18).
 __global__ __launch_bounds__(kScanThreads) void k_core_scan(int64_t* __restrict__ counts, int nchunks,
                                                            int64_t* __restrict__ total) {
-  __shared__ int64_t buf[kScanThreads];
+  constexpr int kW = kScanThreads / kLanes;
+  __shared__ int wsum[kW];
+  const int lane = threadIdx.x & (kLanes - 1), wv = threadIdx.x / kLanes;
   int64_t carry = 0;
-  for (int base = 0; base < nchunks; base += kScanThreads) {
-    const int i = base + threadIdx.x;
-    const int64_t v = i < nchunks ? counts[i] : 0;
-    buf[threadIdx.x] = v;
-    __syncthreads();
-    // Hillis-Steele inclusive scan over the block
-    for (int off = 1; off < kScanThreads; off <<= 1) {
-      const int64_t add = threadIdx.x >= off ? buf[threadIdx.x - off] : 0;
-      __syncthreads();
-      buf[threadIdx.x] += add;
-      __syncthreads();
+  for (int64_t base = 0; base < nchunks; base += kScanThreads * kScanPer) {
+    const int64_t i = base + wv * (kLanes * kScanPer) + lane;
+    int v[kScanPer], run = 0;
+#pragma unroll
+    for (int j = 0; j < kScanPer; ++j) v[j] = i + j * kLanes < nchunks ? (int)counts[i + j * kLanes] : 0;
+#pragma unroll
+    for (int j = 0; j < kScanPer; ++j) {
+      const int inc = wave_scan(v[j]);
+      v[j] = run + inc - v[j];
+      run += __builtin_amdgcn_readlane(inc, kLanes - 1);
     }
-    if (i < nchunks) counts[i] = carry + buf[threadIdx.x] - v;
-    carry += buf[kScanThreads - 1];
-    __syncthreads();   // buf is rewritten by the next block of chunks
+    if (lane == 0) wsum[wv] = run;
+    __syncthreads();
+    int64_t at = carry;
+#pragma unroll
+    for (int j = 0; j < kW; ++j) {
+      at += j < wv ? wsum[j] : 0;
+      carry += wsum[j];
+    }
+#pragma unroll
+    for (int j = 0; j < kScanPer; ++j)
+      if (i + j * kLanes < nchunks) counts[i + j * kLanes] = at + v[j];
+    __syncthreads();   // wsum is rewritten by the next counts
   }
   if (threadIdx.x == 0) *total = carry;
 }
 
-__global__ __launch_bounds__(kChunk) void k_core_scatter(const int32_t* __restrict__ wind, LaunchGeom g,
+// A wavefront looks at eight chunks' offsets and reads the windings of those that hold cores (16384
+// chunks with few cores: 5.8 us; every chunk read by a workgroup of its own, 12.4).
+__global__ __launch_bounds__(kChunk) void k_core_scatter(const int32_t* __restrict__ wind, LaunchGeom g, int nblocks,
                                                         int ndim, int64_t cstride,
                                                         const int64_t* __restrict__ offsets,
+                                                        const int64_t* __restrict__ total,
                                                         int32_t* __restrict__ out, int64_t capacity) {
-  __shared__ int wsum[kChunk / kLanes];
-  const int c = blockIdx.x / g.nchunks, b = blockIdx.x - c * g.nchunks;
-  const int inst = g.chunk2inst[b];
-  const InstDesc d = g.inst[inst];
-  const int s = (b - d.chunk_begin) * kChunk + threadIdx.x;
-  const int32_t w = s < d.sites ? wind[c * cstride + d.psi_off / 5 + s] : 0;
-  const unsigned long long mask = __ballot(w != 0);
-  const int lane = threadIdx.x & (kLanes - 1), wv = threadIdx.x / kLanes;
-  if (lane == 0) wsum[wv] = __popcll(mask);
-  __syncthreads();
-  if (w == 0) return;
-  int64_t k = offsets[blockIdx.x] + __popcll(mask & ((1ull << lane) - 1ull));
-  for (int j = 0; j < wv; ++j) k += wsum[j];
-  if (k >= capacity) return;
-  if (ndim == 3) {
-    const int nxy = d.nx * d.ny;
-    int32_t* e = out + 6 * k;
-    e[0] = inst;
-    e[1] = c;
-    e[2] = s / nxy;
-    e[3] = (s % nxy) / d.nx;
-    e[4] = s % d.nx;
-    e[5] = w;
-  } else {
-    int32_t* e = out + 4 * k;
-    e[0] = inst;
-    e[1] = s / d.nx;
-    e[2] = s % d.nx;
-    e[3] = w;
+  const int lane = threadIdx.x & (kLanes - 1);
+  const int first =
+      (blockIdx.x * (kChunk / kLanes) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kScatterChunks;
+  const bool have = lane < kScatterChunks && first + lane < nblocks;
+  const int64_t o = have ? offsets[first + lane] : 0;
+  const int64_t o1 = have ? (first + lane + 1 < nblocks ? offsets[first + lane + 1] : *total) : 0;
+  for (unsigned long long todo = __ballot(have && o1 > o && o < capacity); todo; todo &= todo - 1) {
+    const int j = __ffsll((long long)todo) - 1;
+    const CoreChunk ch(g, wind, cstride, first + j, lane);
+    int64_t at = __shfl((long long)o, j, kLanes);
+    int32_t w[kChunkLoads];
+#pragma unroll
+    for (int q = 0; q < kChunkLoads; ++q) w[q] = ch.load(q);
+#pragma unroll
+    for (int q = 0; q < kChunkLoads; ++q) {
+      const unsigned long long mask = __ballot(w[q] != 0);
+      const int64_t k = at + __popcll(mask & ((1ull << lane) - 1ull));
+      at += __popcll(mask);
+      if (w[q] == 0 || k >= capacity) continue;
+      const int s = ch.s0 + q * kLanes;
+      if (ndim == 3) {
+        const int nxy = ch.d.nx * ch.d.ny;
+        int32_t* e = out + 6 * k;
+        e[0] = ch.inst;
+        e[1] = ch.c;
+        e[2] = s / nxy;
+        e[3] = (s % nxy) / ch.d.nx;
+        e[4] = s % ch.d.nx;
+        e[5] = w[q];
+      } else {
+        int32_t* e = out + 4 * k;
+        e[0] = ch.inst;
+        e[1] = s / ch.d.nx;
+        e[2] = s % ch.d.nx;
+        e[3] = w[q];
+      }
+    }
   }
 }
 
@@ -435,14 +504,16 @@ hipError_t launch_vortex_cores(const int32_t* winding, const LaunchGeom& g, int 
                                int64_t* counts, int32_t* out, int64_t capacity, int64_t* total, hipStream_t st) {
   if (g.nchunks == 0) return hipSuccess;
   const int nblocks = (ndim == 3 ? 3 : 1) * g.nchunks;
-  hipLaunchKernelGGL(k_core_count, dim3(nblocks), dim3(kChunk), 0, st, winding, g, component_stride, counts);
+  const auto blocks = [&](int per) { return dim3((nblocks + per * (kChunk / kLanes) - 1) / (per * (kChunk / kLanes))); };
+  hipLaunchKernelGGL(k_core_count, blocks(kCountChunks), dim3(kChunk), 0, st, winding, g, nblocks, component_stride,
+                     counts);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_core_scan, dim3(1), dim3(kScanThreads), 0, st, counts, nblocks, total);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_core_scatter, dim3(nblocks), dim3(kChunk), 0, st, winding, g, ndim, component_stride, counts,
-                     out, capacity);
+  hipLaunchKernelGGL(k_core_scatter, blocks(kScatterChunks), dim3(kChunk), 0, st, winding, g, nblocks, ndim,
+                     component_stride, counts, total, out, capacity);
   return hipGetLastError();
 }
 
