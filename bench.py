@@ -35,18 +35,17 @@ sys.path.insert(0, ROOT)
 
 # Algorithmic work per site-update, counted from the per-site formulas.
 # Flops count add/sub/mul as 1 and fma as 2 in the per-site formulas of
-# qlg_math.hpp; the three sincos, two reciprocal square roots and two
-# reciprocals of each self-interaction are not counted.  One U: coefficients 178
-# (psi, n, F, the phases and the rotation's blocks), then 288 per 5-vector a and b
-# (singlet 84, frame phases 24, d^T 58, diagonal 30, d 58, recombination 34), the count of
-# the FP64 form; the FP32 form adds the singlet correction to x in a separate step (10 more
-# per 5-vector, not counted).
-FLOPS_U = 754          # one application of U (coefficients 178 + 2 x 288 per 5-vector)
-FLOPS_IPRIME = 85      # one I' (two collides 2 x 40 + its share of the exact 1/256 per step, 5)
+# qlg_math.hpp, as their FP64 form evaluates them; the sine and cosine series of the three
+# angles are not counted.  One U: coefficients 212 (psi, n, F, the phases and the rotation's
+# 5x5 matrix: 41 additions, 71 multiplications, 50 fmas), then 242 per 5-vector a and b
+# (18 additions, 4 multiplications, 110 fmas); the FP32 form adds its corrections to x in a
+# separate step (not counted).
+FLOPS_U = 696          # one application of U (coefficients 212 + 2 x 242 per 5-vector)
+FLOPS_IPRIME = 45      # one I' (two collides 2 x 20 + its share of the one scale factor per step, 5)
 FLOPS_PER_SITE_STEP = {d: 4 * d * (FLOPS_U + FLOPS_IPRIME) for d in (1, 2, 3)}
 # plain split: one U (theta = eps^2) and the 4 d I' of a step
 FLOPS_PER_SITE_STEP_PLAIN = {d: FLOPS_U + 4 * d * FLOPS_IPRIME for d in (1, 2, 3)}
-# HBM passes per step: 1D and 2D one fused pass, 3D a z pass and a y-x pass
+# HBM passes per step: 1D and 2D one fused pass, 3D a z pass and a y-x pass (line passes: one per axis)
 PASSES_PER_STEP = {1: 1, 2: 1, 3: 2}
 # HBM bytes per site per pass: read + write of 10 complex amplitudes
 BYTES_PER_SITE_PASS = {"c64": 2 * 10 * 8, "c128": 2 * 10 * 16}
@@ -61,8 +60,8 @@ PREROLL_S = 0.2        # untimed steps right before each clock start, at least t
 # --pmc WRITE_SIZE runs (KiB per dispatch, median over the dispatches of that plan), each scaled
 # by what the same counter reads for a 256 MiB device copy in the same run (FETCH_SIZE: x2.000,
 # WRITE_SIZE: x1.000).  Valid only for the kernel sources it was measured on.
-KERNEL_SOURCES = ["paper_1907_12834_amd/csrc/qlg_math.hpp", "paper_1907_12834_amd/csrc/qlg_kernels.hip",
-                  "paper_1907_12834_amd/csrc/qlg_internal.hpp"]
+KERNEL_SOURCES = ["paper_1907_12834_amd/csrc/qlg_math.hpp", "paper_1907_12834_amd/csrc/qlg_lanes.hpp",
+                  "paper_1907_12834_amd/csrc/qlg_kernels.hip", "paper_1907_12834_amd/csrc/qlg_internal.hpp"]
 TRAFFIC = {"sources_sha256_16": "6983e25ef22ca4b8", "fetch_scale": 262144.0 / 131088.5, "write_scale": 1.0,
            "kib": {}}
 
@@ -422,7 +421,11 @@ def main():
     achieved_tflops = flops_launch / (kern_ms * 1e-3) / 1e12 if kern_ms > 0 else None
     # 2D and 3D plans with qubit_split 1 run the y (and z) half over two launches: twice the passes
     ysplit = ndim >= 2 and m["tuning"]["qubit_split"] == 1
-    bytes_launch = BYTES_PER_SITE_PASS[args.dtype] * L * PASSES_PER_STEP[ndim] * (2 if ysplit else 1)
+    # an autotuned plan of eight rows is the one of line passes, one launch per axis: the bands tried
+    # on lattices of these sizes are taller
+    lines = ndim >= 2 and not args.plan and m["tuning"]["tile_rows"] == 8
+    passes = ndim if lines else PASSES_PER_STEP[ndim] * (2 if ysplit else 1)
+    bytes_launch = BYTES_PER_SITE_PASS[args.dtype] * L * passes
     hbm_gbs = bytes_launch / (kern_ms * 1e-3) / 1e9 if kern_ms > 0 else None
     # the roofline that bounds this launch: flops per algorithmic byte against the ridge point
     intensity = flops_launch / bytes_launch
@@ -430,6 +433,9 @@ def main():
     if ndim == 1:
         kernel = ("k_step1d", "k_step1d_pair", "k_step1d_lanes")[m["tuning"]["qubit_split"]]
         key = "%s/S%d" % (kernel, S)
+    elif lines:
+        kernel = "k_line_x, k_line_yz (one launch per axis)"
+        key = "k_line"
     elif ndim == 2:
         kernel = "k_step2d (the two halves of the y half)" if ysplit else "k_step2d"
         key = "k_step2d/rows%d%s" % (m["tuning"]["tile_rows"], "/ysplit" if ysplit else "")

@@ -18,7 +18,6 @@ struct alignas(2 * sizeof(T)) cx {
   T re, im;
 };
 
-template <typename T> QLG_HD cx<T> mk(T r, T i) { return cx<T>{r, i}; }
 template <typename T> QLG_HD cx<T> operator+(cx<T> a, cx<T> b) { return {a.re + b.re, a.im + b.im}; }
 template <typename T> QLG_HD cx<T> operator-(cx<T> a, cx<T> b) { return {a.re - b.re, a.im - b.im}; }
 template <typename T> QLG_HD cx<T> operator*(cx<T> a, cx<T> b) {
@@ -29,10 +28,6 @@ template <typename T> QLG_HD cx<T> conj(cx<T> a) { return {a.re, -a.im}; }
 // conj(a) * b
 template <typename T> QLG_HD cx<T> cmulc(cx<T> a, cx<T> b) {
   return {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re};
-}
-// acc + a * b
-template <typename T> QLG_HD cx<T> cfma(cx<T> a, cx<T> b, cx<T> acc) {
-  return {acc.re + a.re * b.re - a.im * b.im, acc.im + a.re * b.im + a.im * b.re};
 }
 // c ? x : y, component-wise (a select of values, never of addresses)
 template <typename T> QLG_HD cx<T> sel(bool c, cx<T> x, cx<T> y) {
@@ -98,30 +93,6 @@ QLG_HD void sincos_t(double x, double* s, double* c) {
     sincos(x, s, c);
   }
 }
-// sin x, cos x and sin(x)/x for |x| <= 1/16 by the short series of sincos_t (sin(x)/x is
-// 1 + x^2 ps, the polynomial of the sine before its final multiply-add): no branch, and
-// no division for sin(x)/x.
-QLG_HD void sincos_short(float x, float* s, float* c, float* sx) {
-  const float x2 = x * x;
-  const float ps = -1.0f / 6 + x2 * (1.0f / 120);
-  *sx = 1.0f + x2 * ps;
-  *s = x * *sx;
-  *c = 1.0f + x2 * (-0.5f + x2 * (1.0f / 24 + x2 * (-1.0f / 720)));
-}
-QLG_HD void sincos_short(double x, double* s, double* c, double* sx) {
-  const double x2 = x * x;
-  double ps = 1.0 / 362880.0, pc = 1.0 / 40320.0;
-  ps = fma(x2, ps, -1.0 / 5040.0);
-  pc = fma(x2, pc, -1.0 / 720.0);
-  ps = fma(x2, ps, 1.0 / 120.0);
-  pc = fma(x2, pc, 1.0 / 24.0);
-  ps = fma(x2, ps, -1.0 / 6.0);
-  pc = fma(x2, pc, -0.5);
-  *sx = fma(x2, ps, 1.0);
-  *s = fma(x * x2, ps, x);
-  *c = fma(x2, pc, 1.0);
-}
-
 // Whether p holds on every active lane of the wavefront (the host build: p itself).  A
 // branch on it is uniform: no execution-mask changes, both sides never run.
 QLG_HD bool all_lanes(bool p) {
@@ -135,31 +106,9 @@ QLG_HD bool all_lanes(bool p) {
 QLG_HD float sqrt_t(float x) { return sqrtf(x); }
 QLG_HD double sqrt_t(double x) { return sqrt(x); }
 
-// 1/sqrt(x) for x > 0 and 1/x for x != 0 (normal): the hardware approximations
-// (about one ulp) in FP32; in FP64 the hardware estimate refined by two Newton
-// steps, each of which squares its relative error (y <- y + y (1 - x y^2) / 2 and
-// y <- y + y (1 - x y)), to within a few ulp of the exact value (the host build
-// divides).
-QLG_HD float rsqrt_t(float x) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return __builtin_amdgcn_rsqf(x);
-#else
-  return 1.0f / sqrtf(x);
-#endif
-}
-QLG_HD double rsqrt_t(double x) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const double r = fma(-(x * y), y, 1.0);
-    y = fma(0.5 * y, r, y);
-  }
-  return y;
-#else
-  return 1.0 / sqrt(x);
-#endif
-}
+// 1/x for x != 0 (normal): the hardware approximation (about one ulp) in FP32; in FP64 the hardware
+// estimate refined by two Newton steps, each of which squares its relative error
+// (y <- y + y (1 - x y)), to within a few ulp of the exact value (the host build divides).
 QLG_HD float rcp_t(float x) {
 #if defined(__HIP_DEVICE_COMPILE__)
   return __builtin_amdgcn_rcpf(x);
@@ -243,8 +192,6 @@ QLG_HD void unphase_by(cx<T> (&a)[5], cx<T> (&b)[5], T f) {
 // ---------------------------------------------------------------------------
 struct Consts {
   static constexpr double r6 = 2.449489742783178098197284;    // sqrt(6)
-  static constexpr double r32 = 1.224744871391589049098642;   // sqrt(3/2)
-  static constexpr double r38 = 0.6123724356957945245493210;  // sqrt(3/8)
 };
 
 // What the state carries after one application of `potential`: the rotation leaves it in the
