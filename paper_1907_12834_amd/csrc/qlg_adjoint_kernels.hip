@@ -290,6 +290,15 @@ __global__ __launch_bounds__(kChunk) void k_sub_vjp(const cx<T>* __restrict__ z,
 // ---------------------------------------------------------------------------
 // Interleaved split: recompute and pull-back as line passes
 // ---------------------------------------------------------------------------
+// One launch per axis and step for the recompute and one for the pull-back, the state and the
+// cotangent in registers through four substeps.  With a launch per y substep (each read the
+// cotangent of three sites and a record and wrote the cotangent), a persistent kernel for the four x
+// substeps and the derivative in the frame of F a reverse step of 512^2 took 278 us in complex64,
+// 355 in complex128, of 64^2 in complex128 64; now 172, 223 and 39.  Bound by the FP64 derivative (1060
+// instructions per substep; 256 registers, so two wavefronts per SIMD: 52 % of the issue rate at
+// 512^2) and by the records' traffic.  Records copied to LDS a substep ahead gained nothing (512^2
+// complex64 180 -> 186 us, complex128 229 -> 227).
+//
 // Along x a wavefront takes one window of the lines laid end to end (line_slot); along y or z a
 // workgroup takes W neighbouring columns of one window, turned in LDS (as k_line_yz).  pre[i] is the
 // first window of instance i, pre[nbatch] their number; both are read through the constant address
@@ -349,14 +358,14 @@ __device__ __forceinline__ LineTile line_tile_yz(const LaunchGeom& g, const int*
 template <int W>
 struct TileElem {
   int er, ec;
-  int64_t at;
+  int at;          // site
   bool store;
   __device__ __forceinline__ TileElem(const LineTile& t) {
     er = threadIdx.x / W;
     ec = threadIdx.x % W;
     const LineSlot l = line_slot(t.window, er, t.n, t.nlines);
     const int x = t.gx + ec;
-    at = t.d.off + (l.line * t.pstride + l.at * t.rstride + (x < t.d.nx ? x : t.d.nx - 1));
+    at = l.line * t.pstride + l.at * t.rstride + (x < t.d.nx ? x : t.d.nx - 1);
     store = l.own && x < t.d.nx;
   }
 };
@@ -433,7 +442,7 @@ __global__ __launch_bounds__(kLanes * W) void k_recompute_yz(const cx<T>* __rest
   {
     cx<T> v[10];
 #pragma unroll
-    for (int p = 0; p < 10; ++p) v[p] = in[e.at + p * t.d.stride];
+    for (int p = 0; p < 10; ++p) v[p] = in[t.d.off + e.at + p * t.d.stride];
 #pragma unroll
     for (int p = 0; p < 10; ++p) buf[p][e.er][e.ec] = v[p];
   }
@@ -458,7 +467,7 @@ __global__ __launch_bounds__(kLanes * W) void k_recompute_yz(const cx<T>* __rest
   __syncthreads();
   if (e.store) {
 #pragma unroll
-    for (int p = 0; p < 10; ++p) out[e.at + p * t.d.stride] = buf[p][e.er][e.ec];
+    for (int p = 0; p < 10; ++p) out[t.d.off + e.at + p * t.d.stride] = buf[p][e.er][e.ec];
   }
 }
 
@@ -524,14 +533,18 @@ void k_adjoint_yz(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>
                   double* __restrict__ part) {
   constexpr int W = kAdjCols;
   __shared__ cx<double> buf[10][kLanes][W + 1];
+  // this thread's site through the substeps, whose registers are all taken (with it and its places
+  // in LDS spilled to scratch 13 registers per lane: 512^2 71 -> 68 us a launch without)
+  __shared__ volatile int keep[kLanes * W];
   const int lane = threadIdx.x & (kLanes - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = xcd_contiguous_block(blockIdx.x, gridDim.x);
   const LineTile t = line_tile_yz<W>(g, pre, grp, zp != 0);
-  const TileElem<W> e(t);
   {
+    const TileElem<W> e(t);
+    keep[threadIdx.x] = e.store ? e.at : -1;
     cx<double> v[10];
 #pragma unroll
-    for (int p = 0; p < 10; ++p) v[p] = lin[e.at + p * t.d.stride];
+    for (int p = 0; p < 10; ++p) v[p] = lin[t.d.off + e.at + p * t.d.stride];
 #pragma unroll
     for (int p = 0; p < 10; ++p) buf[p][e.er][e.ec] = v[p];
   }
@@ -553,9 +566,15 @@ void k_adjoint_yz(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>
   }
   store_dg(dg, le.own, lane, part + 3 * ((int64_t)grp * W + wv));
   __syncthreads();
-  if (e.store) {
+  // the thread number made opaque, so that its ten places in LDS are not kept through the substeps
+  unsigned tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  tid &= kLanes * W - 1;
+  const int at = keep[tid];
+  if (at >= 0) {
+    cx<double>* dst = lout + t.d.off + at;
 #pragma unroll
-    for (int p = 0; p < 10; ++p) lout[e.at + p * t.d.stride] = buf[p][e.er][e.ec];
+    for (int p = 0; p < 10; ++p) dst[p * t.d.stride] = buf[p][tid / W][tid % W];
   }
 }
 

@@ -690,11 +690,20 @@ void k_step2d(StepArgs<T> A) {
 // ---------------------------------------------------------------------------
 // A wavefront takes a window of 64 slots of the lines along the axis, 56 of them its own and 4 halo on
 // each side (four I' of radius one; line_slot), and runs the axis' four substeps in registers with
-// lane moves: no row pipeline, so a launch lasts four substeps where a band of R rows lasts R + 8 of them.  A step
-// is one launch per axis (z, y, x), the state read and written once per launch: twice (three
-// times) the HBM traffic of a band launch, for 64/56 of the arithmetic instead of
+// lane moves: no row pipeline, so a launch lasts four substeps where a band of R rows lasts R + 8 of
+// them.  A step is one launch per axis (z, y, x), the state read and written once per launch: twice
+// (three times) the HBM traffic of a band launch, for 64/56 of the arithmetic instead of
 // 64/56 (R + 8)/R in the row pipeline.  For lattices that cannot give every SIMD a tall band, and
-// where the extra traffic stays in the caches (qlg_api.cpp chooses).
+// where the extra traffic stays in the caches (qlg_api.cpp chooses, with the times of both).
+//
+// Bounds: on the smallest lattices the chain of one wavefront (64^2: 2200 instructions, about five
+// cycles each); on large ones the vector instructions (256^3 complex64 issues them at the SIMDs'
+// rate); between them the rounds of wavefronts and their loads and stores, during which nothing
+// computes (611 x 347 complex128: 14 us of instructions in a 26 us launch).  Held against that and
+// slower: two sites per lane (a tenth fewer instructions: 512^2 complex128 63 -> 82 us a step, 256^3
+// complex64 3.16 -> 3.67 ms), complex128 in 128 registers for a fourth wavefront per SIMD (1024^2
+// 211 -> 267 us), complex64 in 96 for a fifth (512^2 45.8 -> 46.4), persistent wavefronts that load
+// the next window ahead (512^2 complex128 64 -> 84 us).
 
 // Four substeps [U] I' with the axis along the lanes (plain split: U before the first one, in the
 // launch that applies the step's single U).

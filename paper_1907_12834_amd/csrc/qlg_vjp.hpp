@@ -22,6 +22,9 @@
 //   dL/dn += Re(c'(n) s_x conj(w)),   dL/dg2 += Re(dc/dg2 s_x conj(w)).
 // Finally lambda_psi += 2 dL/dn psi + 2 sum_nu dL/dF_nu f_nu psi and
 // lambda_a = P^H m_a + lambda_psi, lambda_b = P^H m_b + lambda_psi.
+//
+// About 1000 vector instructions, where the derivative in the frame of F (Euler angles, d(beta), the
+// divided differences of each m) took 1525.
 #pragma once
 
 #include "qlg_math.hpp"
