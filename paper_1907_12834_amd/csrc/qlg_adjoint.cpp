@@ -47,8 +47,8 @@ void adjoint_lines(const qlg_params* p, int cols, int64_t* x, int64_t (&yz)[2]) 
     const int64_t nx = p->nx[i], ny = p->ndim >= 2 ? p->ny[i] : 1, nz = p->ndim == 3 ? p->nz[i] : 1;
     const int64_t ncol = (nx + cols - 1) / cols;
     *x += qlg::line_windows(nx, ny * nz);
-    if (p->ndim >= 2) yz[0] += ncol * qlg::line_windows(ny, nz);
-    if (p->ndim == 3) yz[1] += ncol * qlg::line_windows(nz, ny);
+    if (p->ndim >= 2) yz[0] += qlg::line_groups(ny, nz, ncol);
+    if (p->ndim == 3) yz[1] += qlg::line_groups(nz, ny, ncol);
   }
 }
 

@@ -305,11 +305,8 @@ __global__ __launch_bounds__(kChunk) void k_sub_vjp(const cx<T>* __restrict__ z,
 // space (scalar loads).
 struct LineTile {
   InstDesc d;
-  uint32_t window;   // of the instance
-  int n, nlines;     // extent along the lines, number of lines (y, z: of one column)
-  int rstride;       // sites between neighbours along the line
-  int pstride;       // y, z: sites between planes
-  int gx;            // y, z: first column of the group
+  int t;             // x: window, y and z: group of the instance
+  int n;             // extent along the lines
 };
 __device__ __forceinline__ int line_instance(const LaunchGeom& g, const int* pre_g, int w, InstDesc* d, int* t) {
   typedef const __attribute__((address_space(4))) int32_t* CInt;
@@ -332,26 +329,26 @@ __device__ __forceinline__ int line_instance(const LaunchGeom& g, const int* pre
 }
 __device__ __forceinline__ LineTile line_tile_x(const LaunchGeom& g, const int* pre, int w) {
   LineTile r;
-  int t;
-  line_instance(g, pre, w, &r.d, &t);
-  r.window = t;
+  line_instance(g, pre, w, &r.d, &r.t);
   r.n = r.d.nx;
-  r.nlines = r.d.ny * r.d.nz;
   return r;
 }
-template <int W>
-__device__ __forceinline__ LineTile line_tile_yz(const LaunchGeom& g, const int* pre, int grp, bool zp) {
-  LineTile r;
-  int t;
-  line_instance(g, pre, grp, &r.d, &t);
-  const int ncol = (r.d.nx + W - 1) / W;
-  r.window = t / ncol;
-  r.gx = t % ncol * W;
+struct LineTileYz : LineTile {
+  bool zp;
+  int rstride, pstride;   // sites between neighbours along the line, and between planes
+};
+__device__ __forceinline__ LineTileYz line_tile_yz(const LaunchGeom& g, const int* pre, int grp, bool zp) {
+  LineTileYz r;
+  line_instance(g, pre, grp, &r.d, &r.t);
+  r.zp = zp;
   r.n = zp ? r.d.nz : r.d.ny;
   r.rstride = zp ? r.d.nx * r.d.ny : r.d.nx;
   r.pstride = zp ? r.d.nx : r.d.nx * r.d.ny;
-  r.nlines = zp ? r.d.ny : r.d.nz;
   return r;
+}
+template <int W>
+__device__ __forceinline__ LineRun line_run(const LineTileYz& t) {
+  return LineRun(t.t, t.n, t.zp ? t.d.ny : t.d.nz, (t.d.nx + W - 1) / W);
 }
 // This thread's element of a group's window, 64 slots x W columns, for the loads and stores that run
 // along x.
@@ -360,12 +357,13 @@ struct TileElem {
   int er, ec;
   int at;          // site
   bool store;
-  __device__ __forceinline__ TileElem(const LineTile& t) {
+  __device__ __forceinline__ TileElem(const LineTileYz& t, const LineRun& run) {
     er = threadIdx.x / W;
     ec = threadIdx.x % W;
-    const LineSlot l = line_slot(t.window, er, t.n, t.nlines);
-    const int x = t.gx + ec;
-    at = l.line * t.pstride + l.at * t.rstride + (x < t.d.nx ? x : t.d.nx - 1);
+    int plane, col;
+    const LineSlot l = run.slot(er, t.n, &plane, &col);
+    const int x = col * W + ec;
+    at = plane * t.pstride + l.at * t.rstride + (x < t.d.nx ? x : t.d.nx - 1);
     store = l.own && x < t.d.nx;
   }
 };
@@ -376,12 +374,14 @@ struct LaneElem {
   bool own;
   int rec;         // place in a record
   int pot;         // site
-  __device__ __forceinline__ LaneElem(const LineTile& t, int lane, int wv) {
-    const LineSlot l = line_slot(t.window, lane, t.n, t.nlines);
-    const int x = t.gx + wv < t.d.nx ? t.gx + wv : t.d.nx - 1;
-    own = l.own && t.gx + wv < t.d.nx;
-    rec = (l.line * t.d.nx + x) * t.n + l.at;
-    pot = l.line * t.pstride + l.at * t.rstride + x;
+  __device__ __forceinline__ LaneElem(const LineTileYz& t, const LineRun& run, int lane, int wv) {
+    int plane, col;
+    const LineSlot l = run.slot(lane, t.n, &plane, &col);
+    int x = col * W + wv;
+    own = l.own && x < t.d.nx;
+    if (x >= t.d.nx) x = t.d.nx - 1;
+    rec = (plane * t.d.nx + x) * t.n + l.at;
+    pot = plane * t.pstride + l.at * t.rstride + x;
   }
 };
 
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(kChunk) void k_recompute_x(const cx<T>* __restrict_
   const int w = xcd_contiguous_block(blockIdx.x, gridDim.x) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (w >= nwaves) return;
   const LineTile t = line_tile_x(g, pre, w);
-  const LineSlot l = line_slot(t.window, threadIdx.x & (kLanes - 1), t.n, t.nlines);
+  const LineSlot l = line_slot(t.t, threadIdx.x & (kLanes - 1), t.n, t.d.ny * t.d.nz);
   const int s = l.line * t.n + l.at;
   cx<T> a[5], b[5];
   load_site(in, t.d, s, a, b);
@@ -437,8 +437,9 @@ __global__ __launch_bounds__(kLanes * W) void k_recompute_yz(const cx<T>* __rest
                                                             const double* __restrict__ pot, double mu, double theta) {
   __shared__ cx<T> buf[10][kLanes][W + 1];
   const int lane = threadIdx.x & (kLanes - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const LineTile t = line_tile_yz<W>(g, pre, xcd_contiguous_block(blockIdx.x, gridDim.x), zp != 0);
-  const TileElem<W> e(t);
+  const LineTileYz t = line_tile_yz(g, pre, xcd_contiguous_block(blockIdx.x, gridDim.x), zp != 0);
+  const LineRun run = line_run<W>(t);
+  const TileElem<W> e(t, run);
   {
     cx<T> v[10];
 #pragma unroll
@@ -453,7 +454,7 @@ __global__ __launch_bounds__(kLanes * W) void k_recompute_yz(const cx<T>* __rest
     a[m] = buf[m][lane][wv];
     b[m] = buf[5 + m][lane][wv];
   }
-  const LaneElem<W> le(t, lane, wv);
+  const LaneElem<W> le(t, run, lane, wv);
   T ext = T(0);
   if constexpr (kExt) ext = T(theta) * T((pot ? pot[t.d.psi_off / 5 + le.pot] : 0.0) + mu);
   recompute_substeps<T, kExt>(a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
@@ -514,7 +515,7 @@ void k_adjoint_x(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>*
   if (w >= nwaves) return;
   const int lane = threadIdx.x & (kLanes - 1);
   const LineTile t = line_tile_x(g, pre, w);
-  const LineSlot l = line_slot(t.window, lane, t.n, t.nlines);
+  const LineSlot l = line_slot(t.t, lane, t.n, t.d.ny * t.d.nz);
   const int s = l.line * t.n + l.at;
   cx<double> la[5], lb[5];
   load_site(lin, t.d, s, la, lb);
@@ -538,9 +539,10 @@ void k_adjoint_yz(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>
   __shared__ volatile int keep[kLanes * W];
   const int lane = threadIdx.x & (kLanes - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = xcd_contiguous_block(blockIdx.x, gridDim.x);
-  const LineTile t = line_tile_yz<W>(g, pre, grp, zp != 0);
+  const LineTileYz t = line_tile_yz(g, pre, grp, zp != 0);
+  const LineRun run = line_run<W>(t);
   {
-    const TileElem<W> e(t);
+    const TileElem<W> e(t, run);
     keep[threadIdx.x] = e.store ? e.at : -1;
     cx<double> v[10];
 #pragma unroll
@@ -555,7 +557,7 @@ void k_adjoint_yz(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>
     la[m] = buf[m][lane][wv];
     lb[m] = buf[5 + m][lane][wv];
   }
-  const LaneElem<W> le(t, lane, wv);
+  const LaneElem<W> le(t, run, lane, wv);
   const double ext = theta * ((pot ? pot[t.d.psi_off / 5 + le.pot] : 0.0) + mu);
   double dg[3] = {0.0, 0.0, 0.0};
   adjoint_substeps(la, lb, rec, rstep, t.d, le.rec, theta, g0, g1, g2, ext, dg);
@@ -590,7 +592,7 @@ __global__ void k_line_prefix(LaunchGeom g, int rec_cols, int* __restrict__ pre)
     p[i] = acc;
     const InstDesc d = g.inst[i];
     const uint32_t nx = d.nx, ny = d.ny, nz = d.nz, ncol = (nx + cols - 1) / cols;
-    acc += q == 0 ? line_windows(nx, ny * nz) : q & 1 ? ncol * line_windows(ny, nz) : ncol * line_windows(nz, ny);
+    acc += q == 0 ? line_windows(nx, ny * nz) : q & 1 ? line_groups(ny, nz, ncol) : line_groups(nz, ny, ncol);
   }
   p[g.nbatch] = acc;
 }

@@ -337,8 +337,8 @@ qlg_status build_tiles(qlg_ctx* c) {
       const int64_t ncol = (d.nx + W - 1) / W;
       for (int q = 0; q < 3; ++q) d.line[q] = c->nline[q];
       c->nline[0] += (int32_t)((qlg::line_windows<int64_t>(d.nx, (int64_t)d.ny * d.nz) + qlg::kLineTileRows - 1) / qlg::kLineTileRows);
-      c->nline[1] += (int32_t)(ncol * qlg::line_windows<int64_t>(d.ny, d.nz));
-      if (c->p.ndim == 3) c->nline[2] += (int32_t)(ncol * qlg::line_windows<int64_t>(d.nz, d.ny));
+      c->nline[1] += (int32_t)qlg::line_groups<int64_t>(d.ny, d.nz, ncol);
+      if (c->p.ndim == 3) c->nline[2] += (int32_t)qlg::line_groups<int64_t>(d.nz, d.ny, ncol);
     } else if (c->p.ndim == 3) {
       d.tile_begin_z = (int32_t)t2i_z.size();
       tiles_z(d.nx, d.nz, c->eff.tile_rows, &d.ntx_z, &d.ntz);

@@ -49,6 +49,18 @@ constexpr I line_windows(I n, I nlines) {
   const I v = kLanes - 2 * kLineHalo;
   return (nlines * line_slots(n) - 2 * kLineHalo + v - 1) / v;
 }
+// Along y and z a column group's lines (one per plane) are one run of lines.  Where that run leaves
+// more than half of a window empty, several neighbouring column groups share a run: how many, and the
+// launch's groups for ncol column groups.
+template <typename I>
+constexpr I line_fold(I n, I nplanes) {
+  return nplanes > 32 || nplanes * line_slots(n) > 32 ? 1 : kLanes / (nplanes * line_slots(n));
+}
+template <typename I>
+constexpr I line_groups(I n, I nplanes, I ncol) {
+  const I f = line_fold(n, nplanes);
+  return (ncol + f - 1) / f * line_windows<I>(n, nplanes * f);
+}
 
 struct LaunchGeom {
   const InstDesc* inst;        // device [nbatch]

@@ -821,13 +821,13 @@ __global__ __launch_bounds__(kLanes * kLineCols<T>) void k_line_yz(StepArgs<T> A
   const int n = zp ? d.nz : d.ny;   // extent along the lines
   const int rstride = zp ? d.nx * d.ny : d.nx, pstride = zp ? d.nx : d.nx * d.ny;
   const int t = grp - d.line[zp ? 2 : 1];
-  const int ncol = (d.nx + W - 1) / W, nlines = zp ? d.ny : d.nz;
-  const int gx = t % ncol, window = t / ncol;
+  const LineRun run(t, n, zp ? d.ny : d.nz, (d.nx + W - 1) / W);
   // loads and stores: this thread's element of the window, slot er, column ec
   const int er = threadIdx.x / W, ec = threadIdx.x % W;
-  const int ex = gx * W + ec < d.nx ? gx * W + ec : d.nx - 1;
-  const LineSlot le = line_slot(window, er, n, nlines);
-  const int64_t es = d.off + (le.line * pstride + le.at * rstride + ex);
+  int eplane, ecol;
+  const LineSlot le = run.slot(er, n, &eplane, &ecol);
+  const int ex = ecol * W + ec;
+  const int64_t es = d.off + (eplane * pstride + le.at * rstride + (ex < d.nx ? ex : d.nx - 1));
   {
     const cx<T>* src = A.in + es;
     cx<T> v[10];
@@ -846,9 +846,10 @@ __global__ __launch_bounds__(kLanes * kLineCols<T>) void k_line_yz(StepArgs<T> A
   }
   T ext = T(0);
   if constexpr (kExt) {
-    const LineSlot l = line_slot(window, lane, n, nlines);
-    const int x = gx * W + wv < d.nx ? gx * W + wv : d.nx - 1;
-    ext = ext_angle(A, d, l.line * pstride + l.at * rstride + x);
+    int plane, col;
+    const LineSlot l = run.slot(lane, n, &plane, &col);
+    const int x = col * W + wv;
+    ext = ext_angle(A, d, plane * pstride + l.at * rstride + (x < d.nx ? x : d.nx - 1));
   }
   line_substeps<T, kExt>(A, a, b, ext);
   // each wavefront writes back the column it read
@@ -858,7 +859,7 @@ __global__ __launch_bounds__(kLanes * kLineCols<T>) void k_line_yz(StepArgs<T> A
     buf[5 + m][lane][wv] = b[m];
   }
   __syncthreads();
-  if (le.own && gx * W + ec < d.nx) {
+  if (le.own && ex < d.nx) {
     cx<T>* dst = A.out + es;
 #pragma unroll
     for (int p = 0; p < 10; ++p) dst[p * d.stride] = buf[p][er][ec];

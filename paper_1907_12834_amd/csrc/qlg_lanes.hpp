@@ -156,4 +156,25 @@ __device__ __forceinline__ LineSlot line_slot(uint32_t window, int lane, int n, 
   return s;
 }
 
+// Group t of a pass along y or z over the runs of column groups (line_fold): which run and window,
+// and a slot's plane and column group.
+struct LineRun {
+  int fold, nplanes, first, window;
+  __device__ __forceinline__ LineRun(int t, int n, int planes, int ncol) {
+    nplanes = planes;
+    fold = (int)line_fold((uint32_t)n, (uint32_t)planes);
+    const uint32_t runs = fold == 1 ? (uint32_t)ncol : (uint32_t)(ncol + fold - 1) / (uint32_t)fold;
+    const uint32_t w = (uint32_t)t / runs;
+    window = (int)w;
+    first = (int)((uint32_t)t - w * runs) * fold;   // the run's first column group
+  }
+  __device__ __forceinline__ LineSlot slot(int i, int n, int* plane, int* col) const {
+    const LineSlot l = line_slot(window, i, n, nplanes * fold);
+    const int j = fold == 1 ? 0 : (int)((uint32_t)l.line / (uint32_t)nplanes);
+    *plane = l.line - j * nplanes;
+    *col = first + j;
+    return l;
+  }
+};
+
 }  // namespace qlg

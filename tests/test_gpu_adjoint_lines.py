@@ -65,3 +65,11 @@ def test_lines_laid_end_to_end(shape, dtype):
     """Windows that hold the ends of two or more lines along x, y and z."""
     psi = qi.random_field(shape, seed=63, scale=0.4).astype(np.complex64).astype(np.complex128)
     _check(psi, 0.3, 3, 2, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("shape", [(1, 150), (2, 77), (7, 33), (24, 17), (1, 2, 50), (2, 1, 41)], ids=str)
+def test_short_lines_of_several_columns(shape, dtype):
+    """Runs of more than one column group along y and z, the last one with columns past the lattice."""
+    psi = qi.random_field(shape, seed=64, scale=0.4).astype(np.complex64).astype(np.complex128)
+    _check(psi, 0.3, 3, 2, dtype)

@@ -121,3 +121,17 @@ def test_lines_laid_end_to_end(shapes, dtype):
         assert rel_l2(got.cpu().numpy(), ref) <= tol
         ov = 0.3 ** (q.ndim - 2) * np.vdot(ref[0] + ref[1], prev[0] + prev[1])
         assert abs(o["overlap"] - ov) <= tol * abs(ov)
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("shapes", [[(2, 150), (7, 77), (24, 9)], [(1, 2, 61), (2, 1, 41), (3, 2, 30)]], ids=str)
+def test_short_lines_of_several_columns(shapes, dtype):
+    """Runs of more than one column group along y and z, with a potential."""
+    qs = _qubits(shapes, 111)
+    Vs = [np.random.default_rng(5 + i).normal(size=s) for i, s in enumerate(shapes)]
+    lat = _lattice(shapes, dtype)
+    lat.set_potential([torch.from_numpy(V) for V in Vs], 0.2)
+    lat.set_qubits([torch.from_numpy(q) for q in qs])
+    lat.step(3)
+    for q, V, got in zip(qs, Vs, lat.get_qubits()):
+        assert rel_l2(got.cpu().numpy(), _oracle(q, 3, "interleaved", V, 0.2)) <= (1e-12 if dtype == "c128" else 1e-5)
