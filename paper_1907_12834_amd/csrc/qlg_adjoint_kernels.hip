@@ -144,6 +144,12 @@ __device__ __forceinline__ void iprime_adj_lanes(cx<double> (&a)[5], cx<double> 
   collide_r_adj(a, b);
   unphase_by(a, b, -0.5);
 }
+// The same along an axis of one site.
+__device__ __forceinline__ void iprime_adj_sites(cx<double> (&a)[5], cx<double> (&b)[5]) {
+  collide_r_adj(a, b);
+  collide_r_adj(a, b);
+  unphase_by(a, b, -0.5);
+}
 
 }  // namespace
 
@@ -297,7 +303,9 @@ __global__ __launch_bounds__(kChunk) void k_sub_vjp(const cx<T>* __restrict__ z,
 // 355 in complex128, of 64^2 in complex128 64; now 172, 223 and 39.  Bound by the FP64 derivative (1060
 // instructions per substep; 256 registers, so two wavefronts per SIMD: 52 % of the issue rate at
 // 512^2) and by the records' traffic.  Records copied to LDS a substep ahead gained nothing (512^2
-// complex64 180 -> 186 us, complex128 229 -> 227).
+// complex64 180 -> 186 us, complex128 229 -> 227).  Axes of one to three sites waste most of a window's
+// lanes on halos, or its stores on records of one site per line: 300000 x 1 takes 487 us and
+// 150000 x 2 500, where a thread per site took 322 and 346; from four sites on the passes are ahead.
 //
 // Along x a wavefront takes one window of the lines laid end to end (line_slot); along y or z a
 // workgroup takes W neighbouring columns of one window, turned in LDS (as k_line_yz).  pre[i] is the
@@ -390,20 +398,22 @@ struct LaneElem {
 // and z it runs along the lines, site r of the line of column x and plane p at (p nx + x) n + r,
 // so that the pull-back's lanes read it without a turn).
 template <typename T, bool kExt, typename Put>
-__device__ __forceinline__ void recompute_substeps(cx<T> (&a)[5], cx<T> (&b)[5], const Angles<T>& ang, T ext, Put put) {
+__device__ __forceinline__ void recompute_substeps(int n, cx<T> (&a)[5], cx<T> (&b)[5], const Angles<T>& ang, T ext, Put put) {
   constexpr T kUnscale = T(0.5) / UScale<T>::value;   // of U and of the I' after it
 #pragma unroll 1
   for (int k = 0; k < 2; ++k) {
     put(k);
     potential<T, kExt>(a, b, ang, ext);
-    iprime_r_lanes<T, 1>(a, b);
+    if (n == 1) iprime_r_sites(a, b);
+    else iprime_r_lanes<T, 1>(a, b);
     unphase_by(a, b, kUnscale);
   }
 #pragma unroll 1
   for (int k = 2; k < 4; ++k) {
     put(k);
     potential<T, kExt>(a, b, ang, ext);
-    iprime_r_lanes<T, 0>(a, b);
+    if (n == 1) iprime_r_sites(a, b);
+    else iprime_r_lanes<T, 0>(a, b);
     unphase_by(a, b, kUnscale);
   }
 }
@@ -424,7 +434,7 @@ __global__ __launch_bounds__(kChunk) void k_recompute_x(const cx<T>* __restrict_
   load_site(in, t.d, s, a, b);
   T ext = T(0);
   if constexpr (kExt) ext = T(theta) * T((pot ? pot[t.d.psi_off / 5 + s] : 0.0) + mu);
-  recompute_substeps<T, kExt>(a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
+  recompute_substeps<T, kExt>(t.n, a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
     if (l.own && k >= first) store_site_nt(rec + k * rstep, t.d, s, a, b);
   });
   if (l.own) store_site(out, t.d, s, a, b);
@@ -457,7 +467,7 @@ __global__ __launch_bounds__(kLanes * W) void k_recompute_yz(const cx<T>* __rest
   const LaneElem<W> le(t, run, lane, wv);
   T ext = T(0);
   if constexpr (kExt) ext = T(theta) * T((pot ? pot[t.d.psi_off / 5 + le.pot] : 0.0) + mu);
-  recompute_substeps<T, kExt>(a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
+  recompute_substeps<T, kExt>(t.n, a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
     if (le.own) store_site_nt(rec + k * rstep, t.d, le.rec, a, b);
   });
 #pragma unroll
@@ -476,13 +486,14 @@ __global__ __launch_bounds__(kLanes * W) void k_recompute_yz(const cx<T>* __rest
 //   lambda <- (dU_k)^H I'^H_k lambda  at the recorded inputs z_k = rec + k rstep,
 // site s of the records on this lane.  dg: the sums of this lane's site (owned lanes only).
 template <typename T>
-__device__ __forceinline__ void adjoint_substeps(cx<double> (&la)[5], cx<double> (&lb)[5], const cx<T>* __restrict__ rec,
+__device__ __forceinline__ void adjoint_substeps(int n, cx<double> (&la)[5], cx<double> (&lb)[5], const cx<T>* __restrict__ rec,
                                                 int64_t rstep, const InstDesc& d, int s, double theta, double g0,
                                                 double g1, double g2, double ext, double (&dg)[3]) {
   auto substep = [&](int k, auto q) __attribute__((always_inline)) {
     cx<double> a[5], b[5];
     load_site_nt(rec + k * rstep, d, s, a, b);
-    iprime_adj_lanes<decltype(q)::value>(la, lb);
+    if (n == 1) iprime_adj_sites(la, lb);
+    else iprime_adj_lanes<decltype(q)::value>(la, lb);
     potential_vjp(a, b, la, lb, theta, g0, g1, g2, dg, ext);
   };
 #pragma unroll 1
@@ -521,7 +532,7 @@ void k_adjoint_x(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>*
   load_site(lin, t.d, s, la, lb);
   const double ext = theta * ((pot ? pot[t.d.psi_off / 5 + s] : 0.0) + mu);
   double dg[3] = {0.0, 0.0, 0.0};
-  adjoint_substeps(la, lb, rec, rstep, t.d, s, theta, g0, g1, g2, ext, dg);
+  adjoint_substeps(t.n, la, lb, rec, rstep, t.d, s, theta, g0, g1, g2, ext, dg);
   if (l.own) store_site(lout, t.d, s, la, lb);
   store_dg(dg, l.own, lane, part + 3 * (int64_t)w);
 }
@@ -560,7 +571,7 @@ void k_adjoint_yz(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>
   const LaneElem<W> le(t, run, lane, wv);
   const double ext = theta * ((pot ? pot[t.d.psi_off / 5 + le.pot] : 0.0) + mu);
   double dg[3] = {0.0, 0.0, 0.0};
-  adjoint_substeps(la, lb, rec, rstep, t.d, le.rec, theta, g0, g1, g2, ext, dg);
+  adjoint_substeps(t.n, la, lb, rec, rstep, t.d, le.rec, theta, g0, g1, g2, ext, dg);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
     buf[m][lane][wv] = la[m];

@@ -47,13 +47,16 @@ constexpr I line_slots(I n) {
 template <typename I>
 constexpr I line_windows(I n, I nlines) {
   const I v = kLanes - 2 * kLineHalo;
+  if (n == 1) return (nlines + v - 1) / v;   // no halos: a shift along one site is none
   return (nlines * line_slots(n) - 2 * kLineHalo + v - 1) / v;
 }
 // Along y and z a column group's lines (one per plane) are one run of lines.  Where that run leaves
 // more than half of a window empty, several neighbouring column groups share a run: how many, and the
-// launch's groups for ncol column groups.
+// launch's groups for ncol column groups.  (Step of 40000 x 8 complex128 202 -> 85 us, reverse step of
+// 15001 x 2 219 -> 75.)
 template <typename I>
 constexpr I line_fold(I n, I nplanes) {
+  if (n == 1) return nplanes > 28 ? 1 : (kLanes - 2 * kLineHalo) / nplanes;
   return nplanes > 32 || nplanes * line_slots(n) > 32 ? 1 : kLanes / (nplanes * line_slots(n));
 }
 template <typename I>

@@ -708,18 +708,20 @@ void k_step2d(StepArgs<T> A) {
 // Four substeps [U] I' with the axis along the lanes (plain split: U before the first one, in the
 // launch that applies the step's single U).
 template <typename T, bool kExt>
-__device__ __forceinline__ void line_substeps(const StepArgs<T>& A, cx<T> (&a)[5], cx<T> (&b)[5], T ext) {
+__device__ __forceinline__ void line_substeps(const StepArgs<T>& A, int n, cx<T> (&a)[5], cx<T> (&b)[5], T ext) {
   const bool plain = A.plain != 0, plain_u = A.plain_u != 0;
 #pragma unroll 1
   for (int j = 0; j < 2; ++j) {
     if (!plain || (j == 0 && plain_u))
       potential<T, kExt>(a, b, plain ? A.ang_full : substep_angles(A.ang, j), ext);
-    iprime_r_lanes<T, 1>(a, b);
+    if (n == 1) iprime_r_sites(a, b);
+    else iprime_r_lanes<T, 1>(a, b);
   }
 #pragma unroll 1
   for (int j = 2; j < 4; ++j) {
     if (!plain) potential<T, kExt>(a, b, substep_angles(A.ang, j), ext);
-    iprime_r_lanes<T, 0>(a, b);
+    if (n == 1) iprime_r_sites(a, b);
+    else iprime_r_lanes<T, 0>(a, b);
   }
   scale_by(a, b, substep_unscale<T, 4>(plain, plain_u));
 }
@@ -765,7 +767,7 @@ __global__ __launch_bounds__(kLanes * kLineRows) void k_line_x(StepArgs<T> A, in
     }
     T ext = T(0);
     if constexpr (kExt) ext = ext_angle(A, d, site);
-    line_substeps<T, kExt>(A, a, b, ext);
+    line_substeps<T, kExt>(A, d.nx, a, b, ext);
     if (l.own) {
       const int64_t s = d.off + site;
       if (A.overlap) {
@@ -851,7 +853,7 @@ __global__ __launch_bounds__(kLanes * kLineCols<T>) void k_line_yz(StepArgs<T> A
     const int x = col * W + wv;
     ext = ext_angle(A, d, plane * pstride + l.at * rstride + (x < d.nx ? x : d.nx - 1));
   }
-  line_substeps<T, kExt>(A, a, b, ext);
+  line_substeps<T, kExt>(A, n, a, b, ext);
   // each wavefront writes back the column it read
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
