@@ -37,10 +37,10 @@ sys.path.insert(0, ROOT)
 # Flops count add/sub/mul as 1 and fma as 2 in the per-site formulas of
 # qlg_math.hpp, as their FP64 form evaluates them; the sine and cosine series of the three
 # angles are not counted.  One U: coefficients 212 (psi, n, F, the phases and the rotation's
-# 5x5 matrix: 41 additions, 71 multiplications, 50 fmas), then 242 per 5-vector a and b
-# (18 additions, 4 multiplications, 110 fmas); the FP32 form adds its corrections to x in a
-# separate step (not counted).
-FLOPS_U = 696          # one application of U (coefficients 212 + 2 x 242 per 5-vector)
+# 5x5 matrix: 41 additions, 71 multiplications, 50 fmas), then 250 per 5-vector a and b
+# (26 additions, 24 multiplications, 100 fmas); the FP32 form sums all corrections before it
+# adds them to x (not counted).
+FLOPS_U = 712          # one application of U (coefficients 212 + 2 x 250 per 5-vector)
 FLOPS_IPRIME = 45      # one I' (two collides 2 x 20 + its share of the one scale factor per step, 5)
 FLOPS_PER_SITE_STEP = {d: 4 * d * (FLOPS_U + FLOPS_IPRIME) for d in (1, 2, 3)}
 # plain split: one U (theta = eps^2) and the 4 d I' of a step
@@ -63,18 +63,7 @@ PREROLL_S = 0.2        # untimed steps right before each clock start, at least t
 KERNEL_SOURCES = ["paper_1907_12834_amd/csrc/qlg_math.hpp", "paper_1907_12834_amd/csrc/qlg_lanes.hpp",
                   "paper_1907_12834_amd/csrc/qlg_kernels.hip", "paper_1907_12834_amd/csrc/qlg_internal.hpp"]
 TRAFFIC = {"sources_sha256_16": "87792ad99b1d3406", "fetch_scale": 262144.0 / 131088.5, "write_scale": 1.0,
-           "kib": {
-               # 1D two-soliton lattice, L = 16384: the two-lane kernel at 2 steps per pass
-               "1d_two_soliton_scattering/c64/interleaved": {"k_step1d_lanes/S2": (718.5, 1280.0)},
-               # 2D 2048^2 vortex pair (bands of rows, the autotuned plan of each)
-               "2d_vortex_pair/c128/interleaved": {"k_step2d/rows76": (365634.8, 655360.0)},
-               "2d_vortex_pair/c64/interleaved": {"k_step2d/rows38": (200473.7, 328336.9)},
-               "2d_vortex_pair/c64/plain": {"k_step2d/rows38": (205039.0, 332587.8)},
-               # 3D cubes: one step = z pass + y-x pass (sums of the two)
-               "3d_vortex_lines/c64/interleaved": {"k_step3d/rows64": (737379.1 + 744016.1,
-                                                                       1310720.0 + 1314819.3)},
-               "3d_vortex_lines_512/c128/interleaved": {"k_step3d/rows128": (11141294.3 + 11251150.9,
-                                                                             20971520.0 + 20971520.0)}}}
+           "kib": {}}   # none measured on the present sources
 
 
 def parse():

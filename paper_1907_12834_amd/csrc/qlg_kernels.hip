@@ -813,8 +813,13 @@ __global__ __launch_bounds__(kLanes * kLineRows) void k_line_x(StepArgs<T> A, in
 // and turned in LDS; rows are padded by one element, so that neither side has bank conflicts.
 template <typename T>
 constexpr int kLineCols = 64 / (int)sizeof(cx<T>);
+//
+// In FP64 w_apply keeps the state beside its corrections: 174 registers, four too many for a third
+// wavefront per SIMD.  The budget set here takes 168 and spills two (1024^2 227 -> 225 us a step, 128^3
+// 807 -> 790, 256^3 6000 -> 5950; 512^2 61.9 -> 62.3).
 template <typename T, bool kExt>
-__global__ __launch_bounds__(kLanes * kLineCols<T>) void k_line_yz(StepArgs<T> A, int nbatch) {
+__global__ __launch_bounds__(kLanes * kLineCols<T>) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 2)))
+void k_line_yz(StepArgs<T> A, int nbatch) {
   constexpr int W = kLineCols<T>;
   __shared__ cx<T> buf[10][kLanes][W + 1];
   const bool zp = A.zpass != 0;

@@ -131,10 +131,10 @@ QLG_HD double rcp_t(double x) {
 template <typename T>
 struct Angles {
   T tg0, tg1, tg25;
-  // U may be evaluated on the state scaled by an exact power of two s (the
-  // fused kernels defer the 1/4 of each I'): then tg0 and tg25 carry 1/s^2 and
-  // fs = 1/s^2 brings F back to its true scale, so that W, a function of
-  // theta n, theta F, the direction of F and (v v^H)/n only, is unchanged.
+  // U may be evaluated on the state scaled in modulus by an exact power of two s (the
+  // fused kernels defer the factors of each I' and U): then tg0 and tg25 carry 1/s^2 and
+  // fs = 1/s^2 brings theta F back to its true scale, so that W, a function of
+  // theta n, theta F and (v v^H)/n only, is unchanged.
   T fs = T(1);
 };
 
@@ -180,24 +180,22 @@ QLG_HD void unphase_by(cx<T> (&a)[5], cx<T> (&b)[5], T f) {
 // Frozen-field self-interaction U(theta) applied to x = a and x = b:
 //   x <- exp(-i th g0 n) R P x,
 //   P = I + (exp(-i th g2 n/5) - 1) v v^H / n,   v_m = (-1)^m conj(psi_{-m}),
-//   R = exp(-i th g1 F.f) = Phi d(beta) diag(exp(-i phi k)) d(beta)^T Phi^*,
-// with psi = a + b, n = |psi|^2, F_nu = psi^H f_nu psi, phi = th g1 |F|,
-// F = |F| (sin b cos al, sin b sin al, cos b), Phi = diag(exp(-i al m)) and
-// d(beta) the real spin-2 rotation exp(-i beta f_y).
+//   R = exp(-i th g1 F.f), a spin-2 rotation (Rot2),
+// with psi = a + b, n = |psi|^2, F_nu = psi^H f_nu psi.
 //
 // Every factor is applied as "identity + small correction": the corrections
-// use e^{-i x} - 1 = -2 sin^2(x/2) - 2i sin(x/2) cos(x/2), so the part of the
-// state that the identity carries is never rounded and the norm error per
-// application is second order in the phase angles.
+// use e^{-i x} - 1 = -2 sin^2(x/2) - 2i sin(x/2) cos(x/2) and R - I, and are summed
+// apart from the state, which is rounded when they are added to it (w_apply): once
+// per application in FP32, twice in FP64.
 // ---------------------------------------------------------------------------
 struct Consts {
   static constexpr double r6 = 2.449489742783178098197284;    // sqrt(6)
 };
 
-// What the state carries after one application of `potential`: the rotation leaves it in the
-// sums and differences of the m, -m pairs, and in FP64 the factor 1/2 of the way back is left
-// to the deferred scale of the step (exact).  FP32 adds its correction to x once instead (see
-// w_apply) and keeps the scale.
+// What the state carries after one application of `potential`: the rotation's correction comes
+// in the sums and differences of the m, -m pairs, and in FP64 the factor 1/2 of the way back is
+// left to the deferred scale of the step (exact): 2 y is added to twice the correction.  FP32 adds
+// its corrections to x once instead (see w_apply) and keeps the scale.
 template <typename T>
 struct UScale {
   static constexpr int value = sizeof(T) == 8 ? 2 : 1;
@@ -427,13 +425,14 @@ QLG_HD void w_coefficients(const cx<T> (&a)[5], const cx<T> (&b)[5], const Angle
 // x <- UScale exp(-i th g0 n) R P x for one 5-vector x (a or b).
 //
 // With E = exp(-i th g0 n), R commutes with it and E P x = x + mu0 x + cs (v^H x) v (cs holds
-// E): y = E P x is formed in one pass, then R y = y + (R - I) y through the pairs' sums and
-// differences.  In FP32 the corrections mu0 x, the singlet's and the rotation's are summed
-// first and added to x once, so the full-magnitude value is rounded a single time per
-// application; rounding it after each factor made the FP32 qubit norm drift systematically
-// (6e-5 over 20000 steps of the 1D two-soliton run, against 9e-7 with one rounding).  In FP64
-// that drift is some 1e9 times smaller: the sums and differences start from y's, and the pairs
-// come back as S + T and S - T, twice their value (UScale).
+// E): with y = E P x, R y = y + (R - I) y, the second term through the pairs' sums and
+// differences.  The corrections (mu0 x and the singlet's; the rotation's) are each summed from small
+// terms and added to the state last, so the full-magnitude value is rounded in FP64 twice per
+// application (y, and the result): an RMS error of 6.6e-17 of the state, where sums that start from
+// the state and round it at each multiply-add (20 instructions per vector fewer, 3 to 7 % of a
+// step) made 1.6e-16 and the frame of F 9.1e-17.  In FP32 all corrections are added to x at once:
+// rounding it after each factor made the FP32 qubit norm drift systematically (6e-5 over 20000
+// steps of the 1D two-soliton run, against 9e-7 with one rounding).
 template <typename T>
 QLG_HD void w_apply(cx<T> (&x)[5], const WCoef<T>& W) {
   const cx<T>* p = W.p;
@@ -455,12 +454,11 @@ QLG_HD void w_apply(cx<T> (&x)[5], const WCoef<T>& W) {
   s = msub(p[1], x[3], s);
   s = mac(p[0], x[4], s);
   const cx<T> tt = mul(W.cs, s);
-  // e = mu0 x + tt v, v_m = (-1)^m conj(psi_{-m}); in FP64 y = x + e
+  // e = mu0 x + tt v, v_m = (-1)^m conj(psi_{-m}); y = x + e
   constexpr bool kOnce = sizeof(T) == 4;
   auto corr = [&](cx<T> xm, cx<T> vm, bool neg) {
     const cx<T> v = neg ? cx<T>{-vm.re, vm.im} : cx<T>{vm.re, -vm.im};
-    if constexpr (kOnce) return mac(tt, v, mul(W.mu0, xm));
-    else return mac(tt, v, mac(W.mu0, xm, xm));
+    return mac(tt, v, mul(W.mu0, xm));
   };
   cx<T> e[5], y[5];
   e[0] = corr(x[0], p[4], false);
@@ -469,12 +467,12 @@ QLG_HD void w_apply(cx<T> (&x)[5], const WCoef<T>& W) {
   e[3] = corr(x[3], p[1], true);
   e[4] = corr(x[4], p[0], false);
 #pragma unroll
-  for (int m = 0; m < 5; ++m) y[m] = kOnce ? x[m] + e[m] : e[m];
+  for (int m = 0; m < 5; ++m) y[m] = x[m] + e[m];
   const cx<T> s2 = y[0] + y[4], t2 = y[0] - y[4], s1 = y[1] + y[3], t1 = y[1] - y[3], x0 = y[2];
   const cx<T> z{T(0), T(0)};
   // the rows of a pair take their terms in the same order, so that s == +-t stays so exactly
   // (a component that is zero and has no source stays zero)
-  cx<T> S2 = imac(M.st22i, t2, kOnce ? z : s2), T2 = imac(M.ts22i, s2, kOnce ? z : t2);
+  cx<T> S2 = imac(M.st22i, t2, z), T2 = imac(M.ts22i, s2, z);
   S2 = rmac(M.ss22, s2, S2);
   T2 = rmac(M.tt22, t2, T2);
   S2 = imac(M.ss21i, s1, S2);
@@ -483,7 +481,7 @@ QLG_HD void w_apply(cx<T> (&x)[5], const WCoef<T>& W) {
   T2 = rmac(M.ts21, s1, T2);
   S2 = rmac(M.s20, x0, S2);
   T2 = imac(M.t20i, x0, T2);
-  cx<T> S1 = imac(M.st11i, t1, kOnce ? z : s1), T1 = imac(M.ts11i, s1, kOnce ? z : t1);
+  cx<T> S1 = imac(M.st11i, t1, z), T1 = imac(M.ts11i, s1, z);
   S1 = rmac(M.ss11, s1, S1);
   T1 = rmac(M.tt11, t1, T1);
   S1 = imac(M.ss12i, s2, S1);
@@ -492,7 +490,7 @@ QLG_HD void w_apply(cx<T> (&x)[5], const WCoef<T>& W) {
   T1 = rmac(M.ts12, s2, T1);
   S1 = imac(M.s10i, x0, S1);
   T1 = rmac(M.t10, x0, T1);
-  cx<T> X0 = rmac(M.x00, x0, kOnce ? e[2] : x0 + x0);
+  cx<T> X0 = rmac(M.x00, x0, kOnce ? e[2] : z);
   X0 = rmac(M.x0s2, s2, X0);
   X0 = imac(M.x0t2i, t2, X0);
   X0 = imac(M.x0s1i, s1, X0);
@@ -505,11 +503,12 @@ QLG_HD void w_apply(cx<T> (&x)[5], const WCoef<T>& W) {
     x[3] = x[3] + rmac(h, S1 - T1, e[3]);
     x[2] = x[2] + X0;
   } else {
-    x[0] = S2 + T2;
-    x[4] = S2 - T2;
-    x[1] = S1 + T1;
-    x[3] = S1 - T1;
-    x[2] = X0;
+    const T h = T(2);
+    x[0] = rmac(h, y[0], S2 + T2);
+    x[4] = rmac(h, y[4], S2 - T2);
+    x[1] = rmac(h, y[1], S1 + T1);
+    x[3] = rmac(h, y[3], S1 - T1);
+    x[2] = rmac(h, y[2], X0);
   }
 }
 
