@@ -186,7 +186,7 @@ def measure(dtype, steps, warmup, workload="1d_two_soliton_scattering", split="i
     else:
         lat.autotune()
     lat.set_tuning(use_graph=True)
-    tuning = lat.tuning()
+    tuning = lat.plan()   # what runs
 
     # observables every OBS_EVERY steps are recorded on the device (no host round trip)
     # and decoded once at the end of the run, inside the timed region
@@ -317,7 +317,7 @@ def batched_ratio(steps):
     lat.set_psi(psis)
     lat.autotune()
     lat.set_tuning(use_graph=True)
-    plan = lat.tuning()
+    plan = lat.plan()
     # both runs replay captured graphs of `steps` steps: two untimed calls capture the graphs
     # for either starting copy, so the timed call only replays
     lat.step(steps)
@@ -421,9 +421,7 @@ def main():
     achieved_tflops = flops_launch / (kern_ms * 1e-3) / 1e12 if kern_ms > 0 else None
     # 2D and 3D plans with qubit_split 1 run the y (and z) half over two launches: twice the passes
     ysplit = ndim >= 2 and m["tuning"]["qubit_split"] == 1
-    # an autotuned plan of eight rows is the one of line passes, one launch per axis: the bands tried
-    # on lattices of these sizes are taller
-    lines = ndim >= 2 and not args.plan and m["tuning"]["tile_rows"] == 8
+    lines = m["tuning"]["line_passes"] == 1   # one launch per axis
     passes = ndim if lines else PASSES_PER_STEP[ndim] * (2 if ysplit else 1)
     bytes_launch = BYTES_PER_SITE_PASS[args.dtype] * L * passes
     hbm_gbs = bytes_launch / (kern_ms * 1e-3) / 1e9 if kern_ms > 0 else None

@@ -102,9 +102,10 @@ typedef struct qlg_obs {
  * library takes steps_per_pass and qubit_split (1D) or the band height (2D and 3D) from the
  * lattice's size; small 2D and 3D lattices then run one launch per axis ("line passes": z, y, x,
  * four substeps each, the axis along the lanes) instead of bands.  qlg_autotune times that form
- * too; a plan it keeps in that form reports tile_rows 8.  qlg_set_tuning with another
- * steps_per_pass, tile_rows or qubit_split than reported gives the plan as described here; one
- * that changes use_graph alone keeps the form.  All forms compute the same step. */
+ * too; if it keeps it, qlg_get_tuning reports the plan of bands that it would have kept otherwise.
+ * qlg_set_tuning gives the plan described here, whatever ran before; qlg_set_graph changes
+ * use_graph alone and keeps the form; qlg_get_plan says what runs.  All forms compute the same
+ * step. */
 typedef struct qlg_tuning {
   int32_t steps_per_pass; /* 1D: steps fused per HBM pass, 4 S halo sites per side of each
                              tile (1..7 with 64-site tiles, 1..3 with the 32-site tiles of
@@ -126,6 +127,14 @@ typedef struct qlg_tuning {
                              the HBM round trips (the state between the launches is the true
                              state; both forms give the same numbers) */
 } qlg_tuning;
+
+/* The plan that a context's steps run (qlg_get_plan). */
+typedef struct qlg_plan {
+  qlg_tuning tuning;      /* as launched; line_passes 1: tile_rows is the band height of the step
+                             that records the overlap in 3D, and nothing in 2D */
+  int32_t line_passes;    /* 1: line passes (one launch per axis) */
+  int32_t by_size;        /* 1: taken by the library from the lattice's size; 0: tuned or set */
+} qlg_plan;
 
 typedef struct qlg_ctx qlg_ctx;
 
@@ -268,18 +277,21 @@ qlg_status qlg_record_observables(qlg_ctx* ctx, double* rec_dev);
 qlg_status qlg_decode_records(qlg_ctx* ctx, const double* rec_host, int64_t nrec, qlg_obs* out_host);
 
 /* Plan control.  qlg_set_tuning returns QLG_ERR_ARG for a field out of the ranges
- * above (the context keeps its plan).  qlg_autotune times the candidate plans on the
+ * above (the context keeps its plan).  qlg_set_graph(ctx, use_graph) changes that field of the
+ * plan and nothing else.  qlg_autotune times the candidate plans on the
  * context's own lattice without changing its state and keeps the fastest; among plans
  * within 2 % of the fastest it prefers fewer launches, then qubit_split 0, 1, 2, then
  * taller bands.  Chosen plans are kept for the process, keyed by device, dtype, ndim,
  * split, batched or not and the total site count rounded up to a power of two; a new
  * context with the same key starts from that plan.  When the environment variable
  * QLG_TUNE_CACHE names a file, qlg_autotune also appends the plan to it as a text line
- * "key steps_per_pass tile_rows use_graph qubit_split" (key ending in "|lines" for a plan of
- * line passes), and qlg_init takes the last in-range line with its key from the file before
+ * "key steps_per_pass tile_rows use_graph qubit_split" (key ending in "|lines" for line passes,
+ * with the plan of bands that qlg_get_tuning reports), and qlg_init takes the last in-range line with its key from the file before
  * the process's own record. */
 qlg_status qlg_set_tuning(qlg_ctx* ctx, const qlg_tuning* tuning);
 qlg_status qlg_get_tuning(const qlg_ctx* ctx, qlg_tuning* tuning);
+qlg_status qlg_set_graph(qlg_ctx* ctx, int32_t use_graph);
+qlg_status qlg_get_plan(const qlg_ctx* ctx, qlg_plan* plan);
 qlg_status qlg_autotune(qlg_ctx* ctx);
 
 /* Kernel timing.  qlg_set_timing(ctx, 1) starts (and resets) it: every

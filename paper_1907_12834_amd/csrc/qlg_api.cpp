@@ -122,7 +122,7 @@ ScratchLayout scratch_layout(const Layout& L, int nbatch) {
 // qlg_set_tuning), or a plan of bands / of line passes (2D and 3D; 1D: kBands).
 enum class Form { kAuto, kBands, kLines };
 struct Plan {
-  qlg_tuning t;
+  qlg_tuning t;   // kLines: the plan of bands to report beside it
   Form form;
 };
 
@@ -169,7 +169,8 @@ struct qlg_ctx {
   int32_t* d_chunk2inst = nullptr;
   int32_t* d_tile2inst_z = nullptr;   // 3D z pass
   int32_t ntiles = 0, ntiles_z = 0, nline[3] = {0, 0, 0};
-  qlg_tuning tuning{1, 32, 0, 0};  // as set, tuned or the default; qlg_get_tuning's answer
+  qlg_tuning tuning{1, 32, 0, 0};  // as set, tuned or the default; qlg_get_tuning's answer and, but
+                                   // for use_graph, not what runs unless form is kBands
   Form form = Form::kAuto;
   qlg_tuning eff{1, 32, 0, 0};     // what the launches use (build_tiles)
   bool lines = false;              // 2D and 3D: steps run as line passes
@@ -319,7 +320,7 @@ qlg_status build_tiles(qlg_ctx* c) {
   } else {
     c->eff = c->tuning;
     c->lines = c->form == Form::kLines && lines_fit(c);
-    if (c->lines) c->eff.tile_rows = qlg::kLineTileRows;
+    if (c->lines) c->eff.tile_rows = qlg::kLineTileRows, c->eff.qubit_split = 0;
   }
   const int W = qlg::line_cols(c->p.dtype);
   c->nline[0] = c->nline[1] = c->nline[2] = 0;
@@ -551,7 +552,7 @@ void tune_file_store(const std::string& key, const Plan& p) {
 
 extern "C" {
 
-int32_t qlg_version(void) { return 10200; }
+int32_t qlg_version(void) { return 10300; }
 
 const char* qlg_status_string(qlg_status s) {
   switch (s) {
@@ -945,11 +946,15 @@ qlg_status qlg_set_tuning(qlg_ctx* c, const qlg_tuning* t) {
   if (const char* why = tuning_error(c, n)) return fail(c, QLG_ERR_ARG, why);
   if (c->p.ndim == 1) n.tile_rows = 0;
   n.use_graph = n.use_graph ? 1 : 0;
-  // a call that changes nothing but use_graph keeps the launch form
-  if (n.steps_per_pass != c->tuning.steps_per_pass || n.tile_rows != c->tuning.tile_rows ||
-      n.qubit_split != c->tuning.qubit_split)
-    c->form = Form::kBands;
+  c->form = Form::kBands;
   c->tuning = n;
+  return build_tiles(c);
+}
+
+qlg_status qlg_set_graph(qlg_ctx* c, int32_t use_graph) {
+  qlg_status s = check_ctx(c);
+  if (s) return s;
+  c->tuning.use_graph = use_graph ? 1 : 0;
   return build_tiles(c);
 }
 
@@ -957,6 +962,15 @@ qlg_status qlg_get_tuning(const qlg_ctx* c, qlg_tuning* t) {
   if (!c || !t) return QLG_ERR_ARG;
   if (c->broken) return QLG_ERR_STATE;
   *t = c->tuning;
+  return QLG_OK;
+}
+
+qlg_status qlg_get_plan(const qlg_ctx* c, qlg_plan* p) {
+  if (!c || !p) return QLG_ERR_ARG;
+  if (c->broken) return QLG_ERR_STATE;
+  p->tuning = c->eff;
+  p->line_passes = c->lines ? 1 : 0;
+  p->by_size = c->form == Form::kAuto ? 1 : 0;
   return QLG_OK;
 }
 
@@ -1043,10 +1057,17 @@ qlg_status qlg_autotune(qlg_ctx* c) {
   (void)hipEventDestroy(e1);
   if (s) return s;
   if (per_step_ms.empty()) return fail(c, QLG_ERR_STATE, "autotune: no candidate plan");
-  const double best = *std::min_element(per_step_ms.begin(), per_step_ms.end());
-  Plan best_t = cand[0];
-  for (size_t k = 0; k < cand.size(); ++k)
-    if (per_step_ms[k] <= 1.02 * best) { best_t = cand[k]; break; }
+  // the first candidate of the range within 2 % of the range's fastest
+  auto pick = [&](size_t n) {
+    const double best = *std::min_element(per_step_ms.begin(), per_step_ms.begin() + n);
+    size_t k = 0;
+    while (per_step_ms[k] > 1.02 * best) ++k;
+    return k;
+  };
+  const size_t k = pick(cand.size());
+  Plan best_t = cand[k];
+  // line passes (the last candidate): beside the form, the bands that would have been kept
+  if (best_t.form == Form::kLines) best_t.t = cand[pick(cand.size() - 1)].t;
   c->tuning = best_t.t;
   c->form = best_t.form;
   c->tuned = true;

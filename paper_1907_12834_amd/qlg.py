@@ -28,7 +28,7 @@ STATIC_SCRATCH_BYTES = 16 << 20   # QLG_STATIC_SCRATCH_BYTES
 EXPORTED = [
     "qlg_version", "qlg_query_sizes", "qlg_init", "qlg_init_static", "qlg_set_psi", "qlg_get_psi", "qlg_set_qubits",
     "qlg_get_qubits", "qlg_set_potential", "qlg_fields", "qlg_vorticity", "qlg_find_vortices", "qlg_step", "qlg_observables", "qlg_record_observables", "qlg_decode_records",
-    "qlg_set_tuning", "qlg_get_tuning",
+    "qlg_set_tuning", "qlg_get_tuning", "qlg_set_graph", "qlg_get_plan",
     "qlg_autotune", "qlg_set_timing", "qlg_last_kernel_ms", "qlg_adjoint_query",
     "qlg_forward_record", "qlg_objective_grad", "qlg_adjoint_step", "qlg_set_psi_adjoint",
     "qlg_inject_device_error", "qlg_status_string", "qlg_last_error", "qlg_destroy",
@@ -65,6 +65,10 @@ class Tuning(ctypes.Structure):
                 ("use_graph", ctypes.c_int32), ("qubit_split", ctypes.c_int32)]
 
 
+class Plan(ctypes.Structure):
+    _fields_ = [("tuning", Tuning), ("line_passes", ctypes.c_int32), ("by_size", ctypes.c_int32)]
+
+
 class QLGError(RuntimeError):
     def __init__(self, status: int, where: str, detail: str = ""):
         self.status = status
@@ -98,6 +102,8 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         "qlg_decode_records": (i32, [vp, vp, i64, P(Obs)]),
         "qlg_set_tuning": (i32, [vp, P(Tuning)]),
         "qlg_get_tuning": (i32, [vp, P(Tuning)]),
+        "qlg_set_graph": (i32, [vp, i32]),
+        "qlg_get_plan": (i32, [vp, P(Plan)]),
         "qlg_autotune": (i32, [vp]),
         "qlg_set_timing": (i32, [vp, i32]),
         "qlg_last_kernel_ms": (i32, [vp, P(dbl), P(i64)]),
@@ -411,13 +417,26 @@ class Lattice:
 
     def set_tuning(self, steps_per_pass: Optional[int] = None, tile_rows: Optional[int] = None,
                    use_graph: Optional[bool] = None, qubit_split: Optional[int] = None):
-        """Set the launch plan (qlg_tuning in include/qlg.h); fields left None keep their value."""
+        """Set the launch plan (qlg_tuning in include/qlg.h); fields left None keep the value that
+        tuning() reports.  use_graph alone keeps whatever runs, only replayed from a graph or not."""
+        if steps_per_pass is None and tile_rows is None and qubit_split is None:
+            if use_graph is not None:
+                self._check(lib().qlg_set_graph(self.ctx, int(use_graph)), "qlg_set_graph")
+            return
         cur = self.tuning()
         t = Tuning(steps_per_pass if steps_per_pass is not None else cur["steps_per_pass"],
                    tile_rows if tile_rows is not None else cur["tile_rows"],
                    int(use_graph) if use_graph is not None else cur["use_graph"],
                    int(qubit_split) if qubit_split is not None else cur["qubit_split"])
         self._check(lib().qlg_set_tuning(self.ctx, ctypes.byref(t)), "qlg_set_tuning")
+
+    def plan(self) -> dict:
+        """What the steps run (qlg_plan in include/qlg.h)."""
+        p = Plan()
+        self._check(lib().qlg_get_plan(self.ctx, ctypes.byref(p)), "qlg_get_plan")
+        t = p.tuning
+        return {"steps_per_pass": t.steps_per_pass, "tile_rows": t.tile_rows, "use_graph": t.use_graph,
+                "qubit_split": t.qubit_split, "line_passes": p.line_passes, "by_size": p.by_size}
 
     def autotune(self) -> dict:
         self._check(lib().qlg_autotune(self.ctx), "qlg_autotune")
