@@ -31,6 +31,7 @@ struct Sizes {
   int nrec = 4;        // recorded self-interaction inputs per step (nsub, or 1 for the plain split)
   int64_t nchunks = 0; // 256-site chunks of the per-site kernels
   int64_t nx = 0, nrecg[2] = {0, 0}, nadjg[2] = {0, 0};   // x windows, y and z groups of the line passes
+  int64_t nthin[2] = {0, 0};                              // y and z windows of the thin axes
   int64_t nparts = 0;  // dg partials (3 doubles each) of one step's reverse sweep
   int64_t part_steps = 1;  // steps whose dg partials are kept before they are summed
   size_t off_zrec = 0, off_y = 0, off_lam = 0, off_part = 0, off_xpre = 0, off_acc = 0, off_red = 0;
@@ -40,15 +41,18 @@ struct Sizes {
 
 size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
-// x windows, and y and z groups of `cols` columns, of the line passes
-void adjoint_lines(const qlg_params* p, int cols, int64_t* x, int64_t (&yz)[2]) {
-  *x = yz[0] = yz[1] = 0;
+// x windows, y and z groups of `cols` columns and thin y and z windows of the line passes
+void adjoint_lines(const qlg_params* p, int cols, int64_t* x, int64_t (&yz)[2], int64_t (&thin)[2]) {
+  *x = yz[0] = yz[1] = thin[0] = thin[1] = 0;
   for (int i = 0; i < p->nbatch; ++i) {
     const int64_t nx = p->nx[i], ny = p->ndim >= 2 ? p->ny[i] : 1, nz = p->ndim == 3 ? p->nz[i] : 1;
     const int64_t ncol = (nx + cols - 1) / cols;
     *x += qlg::line_windows(nx, ny * nz);
-    if (p->ndim >= 2) yz[0] += qlg::line_groups(ny, nz, ncol);
-    if (p->ndim == 3) yz[1] += qlg::line_groups(nz, ny, ncol);
+    const int64_t n[2] = {ny, nz}, planes[2] = {nz, ny};
+    for (int q = 0; q < p->ndim - 1; ++q) {
+      if (n[q] <= qlg::kThinAxis) thin[q] += qlg::thin_windows(n[q], nx * planes[q]);
+      else yz[q] += qlg::line_groups(n[q], planes[q], ncol);
+    }
   }
 }
 
@@ -76,12 +80,12 @@ qlg_status sizes_for(const qlg_params* p, int64_t nsteps, int32_t K, Sizes* s) {
   // counts them (every extent of the instance, 1D to 3D)
   const int64_t nchunks = adjoint_chunks(p);
   s->nchunks = nchunks;
-  adjoint_lines(p, qlg::line_cols(p->dtype), &s->nx, s->nrecg);
-  adjoint_lines(p, qlg::kAdjCols, &s->nx, s->nadjg);
+  adjoint_lines(p, qlg::line_cols(p->dtype), &s->nx, s->nrecg, s->nthin);
+  adjoint_lines(p, qlg::kAdjCols, &s->nx, s->nadjg, s->nthin);
   // a step's dg partials: per chunk for the substeps of the plain split, per wavefront of the line
   // passes (x, then y, then z) for the interleaved split
   s->nparts = p->split == QLG_SPLIT_PLAIN ? s->nsub * nchunks
-                                         : s->nx + qlg::kAdjCols * (s->nadjg[0] + s->nadjg[1]);
+                                         : s->nx + s->nthin[0] + s->nthin[1] + qlg::kAdjCols * (s->nadjg[0] + s->nadjg[1]);
   size_t o = 0;
   // inputs of every self-interaction of one checkpoint segment: [K][nrec] state copies
   s->off_zrec = o;  o += up256((size_t)K * (size_t)s->nrec * s->copy);
@@ -91,8 +95,8 @@ qlg_status sizes_for(const qlg_params* p, int64_t nsteps, int32_t K, Sizes* s) {
   // per segment), one step for the plain split (summed per step)
   s->part_steps = p->split == QLG_SPLIT_PLAIN ? 1 : K;
   s->off_part = o;
-  // (at least what a partial per 64-site wavefront of every y and z substep and per 56 sites of every
-  // row would take)
+  // (at least a partial per 64 sites of every y and z substep and per 56 sites of every row: the
+  // workspace is never smaller than that of one wavefront per 64 sites and substep)
   int64_t rows = 0;
   for (int i = 0; i < p->nbatch; ++i)
     rows += (p->nx[i] + qlg::kValid2D - 1) / qlg::kValid2D * (p->ndim >= 2 ? p->ny[i] : 1) * (p->ndim == 3 ? p->nz[i] : 1);
@@ -228,9 +232,10 @@ qlg_status qlg_adjoint_step(qlg_ctx* ctx, int64_t nsteps, int32_t K, const void*
   // 32-bit group numbers, and 32-bit slots (56 per window)
   const int64_t lim = INT32_MAX;
   if (!plain && (std::max({s.nrecg[0], s.nrecg[1], qlg::kAdjCols * s.nadjg[0], qlg::kAdjCols * s.nadjg[1]}) > lim ||
-                 s.nx > UINT32_MAX / qlg::kLanes))
+                 std::max({s.nx, s.nthin[0], s.nthin[1]}) > UINT32_MAX / qlg::kLanes))
     return qlg::ctx_fail(ctx, QLG_ERR_ARG, "lattice too large for the adjoint's tile tables");
-  const qlg::LineCounts lines{(int)s.nx, {(int)s.nrecg[0], (int)s.nrecg[1]}, {(int)s.nadjg[0], (int)s.nadjg[1]}};
+  const qlg::LineCounts lines{(int)s.nx, {(int)s.nrecg[0], (int)s.nrecg[1]}, {(int)s.nadjg[0], (int)s.nadjg[1]},
+                              {(int)s.nthin[0], (int)s.nthin[1]}};
   const double theta = p.eps * p.eps / (4.0 * nd);
   const double theta_u = plain ? p.eps * p.eps : theta;
   // substep k of a step acts along z, y, x in that order (the last axis of each dimension first)
@@ -343,7 +348,7 @@ qlg_status qlg_adjoint_step(qlg_ctx* ctx, int64_t nsteps, int32_t K, const void*
                                   theta_u, p.g0, p.g1, p.g2, v.ext, pj, str);
           if (e != hipSuccess) return qlg::ctx_hip(ctx, e, "adjoint line pass");
           lc = 1 - lc;
-          pj += 3 * (axis == 0 ? s.nx : qlg::kAdjCols * s.nadjg[axis - 1]);
+          pj += 3 * (axis == 0 ? s.nx : s.nthin[axis - 1] + qlg::kAdjCols * s.nadjg[axis - 1]);
         }
       }
       for (int k = plain ? nsub - 1 : -1; k >= 0; --k) {

@@ -125,21 +125,21 @@ __device__ __forceinline__ void collide_r_adj(cx<double> (&a)[5], cx<double> (&b
   }
 }
 
-// lambda <- I'^H_{x,q} lambda with the axis along the lanes: q from the next lane, C^H, q from the
+// lambda <- I'^H_{q} lambda with the axis along the lanes: q from the next site, C^H, q from the
 // one before, C^H (the order of iprime_adj_site), the factors of the two C^H divided out.
 // Q = 1: qubit b moves; Q = 0: qubit a.
-template <int Q>
-__device__ __forceinline__ void iprime_adj_lanes(cx<double> (&a)[5], cx<double> (&b)[5]) {
+template <int Q, typename Shift>
+__device__ __forceinline__ void iprime_adj_lanes(const Shift& sh, cx<double> (&a)[5], cx<double> (&b)[5]) {
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    if (Q) b[m] = from_next_lane(b[m]);
-    else   a[m] = from_next_lane(a[m]);
+    if (Q) b[m] = sh.next(b[m]);
+    else   a[m] = sh.next(a[m]);
   }
   collide_r_adj(a, b);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    if (Q) b[m] = from_prev_lane(b[m]);
-    else   a[m] = from_prev_lane(a[m]);
+    if (Q) b[m] = sh.prev(b[m]);
+    else   a[m] = sh.prev(a[m]);
   }
   collide_r_adj(a, b);
   unphase_by(a, b, -0.5);
@@ -150,6 +150,32 @@ __device__ __forceinline__ void iprime_adj_sites(cx<double> (&a)[5], cx<double> 
   collide_r_adj(a, b);
   unphase_by(a, b, -0.5);
 }
+
+// How a pass reads its neighbours along the axis: LaneShift along y and z of more than kThinAxis sites.
+// one(): an axis of one site, without any.
+// The same along x, of any extent.
+struct LaneShiftX : LaneShift {
+  int n;
+  __device__ __forceinline__ bool one() const { return n == 1; }
+};
+// Lanes by number: the rings of a thin axis.
+struct RingShift {
+  int n, up, down;   // extent, lanes of the next site and of the one before, in bytes
+  __device__ __forceinline__ bool one() const { return n == 1; }
+  static __device__ __forceinline__ float read(float v, int lane) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(lane, __float_as_int(v)));
+  }
+  static __device__ __forceinline__ double read(double v, int lane) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_ds_bpermute(lane, (int)(unsigned)u);
+    const unsigned hi = (unsigned)__builtin_amdgcn_ds_bpermute(lane, (int)(unsigned)(u >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+  }
+  template <typename T>
+  __device__ __forceinline__ cx<T> next(cx<T> v) const { return cx<T>{read(v.re, up), read(v.im, up)}; }
+  template <typename T>
+  __device__ __forceinline__ cx<T> prev(cx<T> v) const { return cx<T>{read(v.re, down), read(v.im, down)}; }
+};
 
 }  // namespace
 
@@ -303,9 +329,8 @@ __global__ __launch_bounds__(kChunk) void k_sub_vjp(const cx<T>* __restrict__ z,
 // 355 in complex128, of 64^2 in complex128 64; now 172, 223 and 39.  Bound by the FP64 derivative (1060
 // instructions per substep; 256 registers, so two wavefronts per SIMD: 52 % of the issue rate at
 // 512^2) and by the records' traffic.  Records copied to LDS a substep ahead gained nothing (512^2
-// complex64 180 -> 186 us, complex128 229 -> 227).  Axes of one to three sites waste most of a window's
-// lanes on halos, or its stores on records of one site per line: 300000 x 1 takes 487 us and
-// 150000 x 2 500, where a thread per site took 322 and 346; from four sites on the passes are ahead.
+// complex64 180 -> 186 us, complex128 229 -> 227).  Along y and z axes of up to kThinAxis sites the
+// windows are others (ThinTile).
 //
 // Along x a wavefront takes one window of the lines laid end to end (line_slot); along y or z a
 // workgroup takes W neighbouring columns of one window, turned in LDS (as k_line_yz).  pre[i] is the
@@ -397,23 +422,24 @@ struct LaneElem {
 // out = z_4.  rec + k rstep receives z_k, k >= first (along x a record is a state copy; along y
 // and z it runs along the lines, site r of the line of column x and plane p at (p nx + x) n + r,
 // so that the pull-back's lanes read it without a turn).
-template <typename T, bool kExt, typename Put>
-__device__ __forceinline__ void recompute_substeps(int n, cx<T> (&a)[5], cx<T> (&b)[5], const Angles<T>& ang, T ext, Put put) {
+template <typename T, bool kExt, typename Shift, typename Put>
+__device__ __forceinline__ void recompute_substeps(const Shift& sh, cx<T> (&a)[5], cx<T> (&b)[5], const Angles<T>& ang, T ext,
+                                                  Put put) {
   constexpr T kUnscale = T(0.5) / UScale<T>::value;   // of U and of the I' after it
 #pragma unroll 1
   for (int k = 0; k < 2; ++k) {
     put(k);
     potential<T, kExt>(a, b, ang, ext);
-    if (n == 1) iprime_r_sites(a, b);
-    else iprime_r_lanes<T, 1>(a, b);
+    if (sh.one()) iprime_r_sites(a, b);
+    else iprime_r_lanes<T, 1>(a, b, sh);
     unphase_by(a, b, kUnscale);
   }
 #pragma unroll 1
   for (int k = 2; k < 4; ++k) {
     put(k);
     potential<T, kExt>(a, b, ang, ext);
-    if (n == 1) iprime_r_sites(a, b);
-    else iprime_r_lanes<T, 0>(a, b);
+    if (sh.one()) iprime_r_sites(a, b);
+    else iprime_r_lanes<T, 0>(a, b, sh);
     unphase_by(a, b, kUnscale);
   }
 }
@@ -434,7 +460,7 @@ __global__ __launch_bounds__(kChunk) void k_recompute_x(const cx<T>* __restrict_
   load_site(in, t.d, s, a, b);
   T ext = T(0);
   if constexpr (kExt) ext = T(theta) * T((pot ? pot[t.d.psi_off / 5 + s] : 0.0) + mu);
-  recompute_substeps<T, kExt>(t.n, a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
+  recompute_substeps<T, kExt>(LaneShiftX{{}, t.n}, a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
     if (l.own && k >= first) store_site_nt(rec + k * rstep, t.d, s, a, b);
   });
   if (l.own) store_site(out, t.d, s, a, b);
@@ -469,7 +495,7 @@ void k_recompute_yz(const cx<T>* __restrict__ in, cx<T>* __restrict__ out,
   const LaneElem<W> le(t, run, lane, wv);
   T ext = T(0);
   if constexpr (kExt) ext = T(theta) * T((pot ? pot[t.d.psi_off / 5 + le.pot] : 0.0) + mu);
-  recompute_substeps<T, kExt>(t.n, a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
+  recompute_substeps<T, kExt>(LaneShift{}, a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
     if (le.own) store_site_nt(rec + k * rstep, t.d, le.rec, a, b);
   });
 #pragma unroll
@@ -487,15 +513,16 @@ void k_recompute_yz(const cx<T>* __restrict__ in, cx<T>* __restrict__ out,
 // The pull-back through one axis: for k = 3, ..., 0 (qubits a, a, b, b),
 //   lambda <- (dU_k)^H I'^H_k lambda  at the recorded inputs z_k = rec + k rstep,
 // site s of the records on this lane.  dg: the sums of this lane's site (owned lanes only).
-template <typename T>
-__device__ __forceinline__ void adjoint_substeps(int n, cx<double> (&la)[5], cx<double> (&lb)[5], const cx<T>* __restrict__ rec,
-                                                int64_t rstep, const InstDesc& d, int s, double theta, double g0,
-                                                double g1, double g2, double ext, double (&dg)[3]) {
+template <typename T, typename Shift>
+__device__ __forceinline__ void adjoint_substeps(const Shift& sh, cx<double> (&la)[5], cx<double> (&lb)[5],
+                                                const cx<T>* __restrict__ rec, int64_t rstep, const InstDesc& d, int s,
+                                                double theta, double g0, double g1, double g2, double ext,
+                                                double (&dg)[3]) {
   auto substep = [&](int k, auto q) __attribute__((always_inline)) {
     cx<double> a[5], b[5];
     load_site_nt(rec + k * rstep, d, s, a, b);
-    if (n == 1) iprime_adj_sites(la, lb);
-    else iprime_adj_lanes<decltype(q)::value>(la, lb);
+    if (sh.one()) iprime_adj_sites(la, lb);
+    else iprime_adj_lanes<decltype(q)::value>(sh, la, lb);
     potential_vjp(a, b, la, lb, theta, g0, g1, g2, dg, ext);
   };
 #pragma unroll 1
@@ -534,7 +561,7 @@ void k_adjoint_x(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>*
   load_site(lin, t.d, s, la, lb);
   const double ext = theta * ((pot ? pot[t.d.psi_off / 5 + s] : 0.0) + mu);
   double dg[3] = {0.0, 0.0, 0.0};
-  adjoint_substeps(t.n, la, lb, rec, rstep, t.d, s, theta, g0, g1, g2, ext, dg);
+  adjoint_substeps(LaneShiftX{{}, t.n}, la, lb, rec, rstep, t.d, s, theta, g0, g1, g2, ext, dg);
   if (l.own) store_site(lout, t.d, s, la, lb);
   store_dg(dg, l.own, lane, part + 3 * (int64_t)w);
 }
@@ -573,7 +600,7 @@ void k_adjoint_yz(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>
   const LaneElem<W> le(t, run, lane, wv);
   const double ext = theta * ((pot ? pot[t.d.psi_off / 5 + le.pot] : 0.0) + mu);
   double dg[3] = {0.0, 0.0, 0.0};
-  adjoint_substeps(t.n, la, lb, rec, rstep, t.d, le.rec, theta, g0, g1, g2, ext, dg);
+  adjoint_substeps(LaneShift{}, la, lb, rec, rstep, t.d, le.rec, theta, g0, g1, g2, ext, dg);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
     buf[m][lane][wv] = la[m];
@@ -593,8 +620,77 @@ void k_adjoint_yz(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>
   }
 }
 
+// Axes of up to kThinAxis sites along y or z: a wavefront takes 64 / n whole lines without halos, in site
+// order (x, then the planes), lane at * (64 / n) + l holding site `at` of line l: loads, stores and
+// records (here a state copy) run along x as they lie, without a turn in LDS, and the neighbours are the
+// other lanes of a ring, read through the LDS crossbar.  In windows with halos and columns turned in LDS
+// two or three sites of ten or eleven slots were their own, and lines of one site were stored one by one;
+// a reverse step took (us, complex64 / complex128; in brackets with one thread per site and substep)
+// 300000 x 1 496 / 536 (340 / 422), now 190 / 245; 150000 x 2 517 / 593 (367 / 461), 190 / 244;
+// 100000 x 3 457 / 525 (384 / 501), 213 / 279; 400 x 400 x 2 701 / 782 (588 / 749), 301 / 388.  From four
+// sites on the halos' windows are ahead of a thread per site (75000 x 4 348 / 389; 385 / 503).
+struct ThinTile : LineTileYz {
+  int s;
+  bool own;
+  RingShift ring;
+  __device__ __forceinline__ ThinTile(const LineTileYz& t, int lane) : LineTileYz(t) {
+    const int per = kLanes / n, at0 = lane / per, l = lane - at0 * per;
+    const bool in = at0 < n;   // three sites: lane 63 holds none
+    const int at = in ? at0 : 0;
+    const uint32_t nlines = (uint32_t)d.sites / (uint32_t)n, line0 = (uint32_t)this->t * (uint32_t)per + (uint32_t)l;
+    own = in && line0 < nlines;
+    const uint32_t line = line0 < nlines ? line0 : nlines - 1u;
+    const uint32_t plane = line / (uint32_t)d.nx;   // of the planes of one site along the axis
+    s = zp ? (int)line + at * rstride : (int)plane * pstride + at * rstride + (int)(line - plane * (uint32_t)d.nx);
+    ring.n = n;
+    ring.up = 4 * (in ? (at + 1 == n ? 0 : at + 1) * per + l : lane);
+    ring.down = 4 * (in ? (at == 0 ? n - 1 : at - 1) * per + l : lane);
+  }
+};
+
+template <typename T, bool kExt>
+__global__ __launch_bounds__(kChunk) void k_recompute_thin(const cx<T>* __restrict__ in, cx<T>* __restrict__ out,
+                                                          cx<T>* __restrict__ rec, int64_t rstep, LaunchGeom g,
+                                                          const int* __restrict__ pre, int nwaves, int zp,
+                                                          Angles<T> ang, const double* __restrict__ pot, double mu,
+                                                          double theta) {
+  constexpr int kWaves = kChunk / kLanes;
+  const int w = xcd_contiguous_block(blockIdx.x, gridDim.x) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (w >= nwaves) return;
+  const ThinTile t(line_tile_yz(g, pre, w, zp != 0), threadIdx.x & (kLanes - 1));
+  cx<T> a[5], b[5];
+  load_site(in, t.d, t.s, a, b);
+  T ext = T(0);
+  if constexpr (kExt) ext = T(theta) * T((pot ? pot[t.d.psi_off / 5 + t.s] : 0.0) + mu);
+  recompute_substeps<T, kExt>(t.ring, a, b, ang, ext, [&](int k) __attribute__((always_inline)) {
+    if (t.own) store_site_nt(rec + k * rstep, t.d, t.s, a, b);
+  });
+  if (t.own) store_site(out, t.d, t.s, a, b);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kChunk) __attribute__((amdgpu_waves_per_eu(2)))
+void k_adjoint_thin(const cx<T>* __restrict__ rec, int64_t rstep, const cx<double>* __restrict__ lin,
+                    cx<double>* __restrict__ lout, LaunchGeom g, const int* __restrict__ pre, int nwaves, int zp,
+                    double theta, double g0, double g1, double g2, const double* __restrict__ pot, double mu,
+                    double* __restrict__ part) {
+  constexpr int kWaves = kChunk / kLanes;
+  const int w = xcd_contiguous_block(blockIdx.x, gridDim.x) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (w >= nwaves) return;
+  const int lane = threadIdx.x & (kLanes - 1);
+  const ThinTile t(line_tile_yz(g, pre, w, zp != 0), lane);
+  cx<double> la[5], lb[5];
+  load_site(lin, t.d, t.s, la, lb);
+  const double ext = theta * ((pot ? pot[t.d.psi_off / 5 + t.s] : 0.0) + mu);
+  double dg[3] = {0.0, 0.0, 0.0};
+  adjoint_substeps(t.ring, la, lb, rec, rstep, t.d, t.s, theta, g0, g1, g2, ext, dg);
+  if (t.own) store_site(lout, t.d, t.s, la, lb);
+  store_dg(dg, t.own, lane, part + 3 * (int64_t)w);
+}
+
 // The instance tables of the line passes, one after the other (nbatch + 1 entries each): x windows, y
-// and z groups of the recompute (rec_cols columns), y and z groups of the pull-back (kAdjCols).
+// and z groups of the recompute (rec_cols columns), y and z groups of the pull-back (kAdjCols), y and z
+// windows of thin axes.  Along y and z an instance has either groups or windows.
 __global__ void k_line_prefix(LaunchGeom g, int rec_cols, int* __restrict__ pre) {
   const int q = threadIdx.x;
   if (q >= kLinePrefixes) return;
@@ -605,7 +701,10 @@ __global__ void k_line_prefix(LaunchGeom g, int rec_cols, int* __restrict__ pre)
     p[i] = acc;
     const InstDesc d = g.inst[i];
     const uint32_t nx = d.nx, ny = d.ny, nz = d.nz, ncol = (nx + cols - 1) / cols;
-    acc += q == 0 ? line_windows(nx, ny * nz) : q & 1 ? line_groups(ny, nz, ncol) : line_groups(nz, ny, ncol);
+    const uint32_t n = q & 1 ? ny : nz, planes = q & 1 ? nz : ny;
+    if (q == 0) acc += line_windows(nx, ny * nz);
+    else if (n <= kThinAxis) acc += q >= 5 ? thin_windows(n, nx * planes) : 0u;
+    else acc += q >= 5 ? 0u : line_groups(n, planes, ncol);
   }
   p[g.nbatch] = acc;
 }
@@ -853,6 +952,17 @@ hipError_t launch_recompute(int dtype, int axis, const void* in, void* out, void
                            rstep, first, g, p, n.x, ang, ext.V, ext.mu, theta);
       return;
     }
+    if (const int nt = n.thin[axis - 1]) {
+      const dim3 grid((nt + kWaves - 1) / kWaves), block(kChunk);
+      const int* pt = pre + (4 + axis) * (g.nbatch + 1);
+      if (ext.on())
+        hipLaunchKernelGGL((k_recompute_thin<T, true>), grid, block, 0, st, (const cx<T>*)in, (cx<T>*)out, (cx<T>*)rec,
+                           rstep, g, pt, nt, axis == 2 ? 1 : 0, ang, ext.V, ext.mu, theta);
+      else
+        hipLaunchKernelGGL((k_recompute_thin<T, false>), grid, block, 0, st, (const cx<T>*)in, (cx<T>*)out, (cx<T>*)rec,
+                           rstep, g, pt, nt, axis == 2 ? 1 : 0, ang, ext.V, ext.mu, theta);
+    }
+    if (n.rec[axis - 1] == 0) return;
     const dim3 grid(n.rec[axis - 1]), block(kLanes * W);
     if (ext.on())
       hipLaunchKernelGGL((k_recompute_yz<T, W, true>), grid, block, 0, st, (const cx<T>*)in, (cx<T>*)out, (cx<T>*)rec,
@@ -879,9 +989,15 @@ hipError_t launch_adjoint(int dtype, int axis, const void* rec, size_t rec_bytes
                          part);
       return;
     }
-    hipLaunchKernelGGL(k_adjoint_yz<T>, dim3(n.adj[axis - 1]), dim3(kLanes * kAdjCols), 0, st, (const cx<T>*)rec, rstep,
-                       (const cx<double>*)lam_in, (cx<double>*)lam_out, g, pre + (2 + axis) * (g.nbatch + 1),
-                       axis == 2 ? 1 : 0, theta, g0, g1, g2, ext.V, ext.mu, part);
+    const int nt = n.thin[axis - 1], zp = axis == 2 ? 1 : 0;
+    if (nt)
+      hipLaunchKernelGGL(k_adjoint_thin<T>, dim3((nt + kWaves - 1) / kWaves), dim3(kChunk), 0, st, (const cx<T>*)rec, rstep,
+                         (const cx<double>*)lam_in, (cx<double>*)lam_out, g, pre + (4 + axis) * (g.nbatch + 1), nt, zp,
+                         theta, g0, g1, g2, ext.V, ext.mu, part);
+    if (n.adj[axis - 1])
+      hipLaunchKernelGGL(k_adjoint_yz<T>, dim3(n.adj[axis - 1]), dim3(kLanes * kAdjCols), 0, st, (const cx<T>*)rec, rstep,
+                         (const cx<double>*)lam_in, (cx<double>*)lam_out, g, pre + (2 + axis) * (g.nbatch + 1), zp, theta,
+                         g0, g1, g2, ext.V, ext.mu, part + 3 * (int64_t)nt);
   };
   if (dtype == 0) go(0.0f);
   else go(0.0);

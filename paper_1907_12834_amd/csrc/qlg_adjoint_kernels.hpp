@@ -17,23 +17,26 @@ hipError_t launch_sub_vjp(int dtype, const void* z, void* lam, const LaunchGeom&
                           double g1, double g2, const ExtPot& ext, double* part, double* acc, hipStream_t st);
 // Interleaved split: line passes (one axis, 0 = x, 1 = y, 2 = z, of one step per launch).
 constexpr int kAdjCols = 4;        // columns per y or z group of the pull-back (complex128: 64 bytes)
-constexpr int kLinePrefixes = 5;   // instance tables of nbatch + 1 ints each (launch_line_prefix)
+constexpr int kLinePrefixes = 7;   // instance tables of nbatch + 1 ints each (launch_line_prefix)
 struct LineCounts {
   int x;         // x windows (wavefronts)
   int rec[2];    // y, z groups of the recompute (line_cols(dtype) columns of a window)
   int adj[2];    // y, z groups of the pull-back (kAdjCols columns)
+  int thin[2];   // y, z windows of the instances whose axis has at most kThinAxis sites (no groups)
 };
 // The recompute of one axis: z_0 = in, z_{k+1} = I'_k U(z_k), out = z_4; rec + k rec_bytes receives
-// z_k for k >= first (x: as a state copy; y and z: along the lines, first = 0 always).
+// z_k for k >= first (x, and y and z of up to kThinAxis sites: as a state copy; other y and z: along
+// the lines; first = 0 but for x).
 hipError_t launch_recompute(int dtype, int axis, const void* in, void* out, void* rec, size_t rec_bytes, int first,
                             const LaunchGeom& g, const LineCounts& n, const int* pre, double tg0, double tg1,
                             double tg25, const ExtPot& ext, double theta, hipStream_t st);
 // The pull-back through one axis at the records of the same layout; dg partials per wavefront into
-// part[n.x][3] (x) or part[kAdjCols n.adj[axis - 1]][3] (no accumulation).
+// part[n.x][3] (x) or part[n.thin[axis - 1] + kAdjCols n.adj[axis - 1]][3] (no accumulation).
 hipError_t launch_adjoint(int dtype, int axis, const void* rec, size_t rec_bytes, const void* lam_in, void* lam_out,
                           const LaunchGeom& g, const LineCounts& n, const int* pre, double theta, double g0, double g1,
                           double g2, const ExtPot& ext, double* part, hipStream_t st);
-// pre[kLinePrefixes][nbatch + 1]: the instances' first x window, y and z group (device table)
+// pre[kLinePrefixes][nbatch + 1]: the instances' first x window, y and z groups and thin windows
+// (device table)
 hipError_t launch_line_prefix(int dtype, const LaunchGeom& g, int* pre, hipStream_t st);
 // acc[0..2] += sum of nparts consecutive 3-vectors of part (fixed order)
 hipError_t launch_dg_accumulate(const double* part, int nparts, double* acc, hipStream_t st);

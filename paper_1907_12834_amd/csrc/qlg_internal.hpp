@@ -52,8 +52,7 @@ constexpr I line_windows(I n, I nlines) {
 }
 // Along y and z a column group's lines (one per plane) are one run of lines.  Where that run leaves
 // more than half of a window empty, several neighbouring column groups share a run: how many, and the
-// launch's groups for ncol column groups.  (Step of 40000 x 8 complex128 202 -> 85 us, reverse step of
-// 15001 x 2 219 -> 75.)
+// launch's groups for ncol column groups.  (Step of 40000 x 8 complex128 202 -> 85 us.)
 template <typename I>
 constexpr I line_fold(I n, I nplanes) {
   if (n == 1) return nplanes > 28 ? 1 : (kLanes - 2 * kLineHalo) / nplanes;
@@ -63,6 +62,15 @@ template <typename I>
 constexpr I line_groups(I n, I nplanes, I ncol) {
   const I f = line_fold(n, nplanes);
   return (ncol + f - 1) / f * line_windows<I>(n, nplanes * f);
+}
+
+// The adjoint's passes along y and z over axes of up to kThinAxis sites hold whole lines, without halos,
+// as rings of lanes: the windows (wavefronts) of nlines lines of n sites.
+constexpr int kThinAxis = 3;
+template <typename I>
+constexpr I thin_windows(I n, I nlines) {
+  const I lines = kLanes / n;
+  return (nlines + lines - 1) / lines;
 }
 
 struct LaunchGeom {

@@ -61,21 +61,30 @@ __device__ __forceinline__ double wave_sum(double v) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// 2i I'_{x,q}: S_q C S_q^T C by collide_r, with lanes along x (the factor 1/(2i) is left to
+// Neighbours along the axis on the neighbouring lanes.
+struct LaneShift {
+  __device__ __forceinline__ bool one() const { return false; }
+  template <typename T>
+  __device__ __forceinline__ cx<T> next(cx<T> v) const { return from_next_lane(v); }
+  template <typename T>
+  __device__ __forceinline__ cx<T> prev(cx<T> v) const { return from_prev_lane(v); }
+};
+
+// 2i I'_q: S_q C S_q^T C by collide_r, with the axis along the lanes (the factor 1/(2i) is left to
 // the caller).  Q = 1: qubit b (the paper's qubit 2) moves; Q = 0: qubit a (qubit 1).
-template <typename T, int Q>
-__device__ __forceinline__ void iprime_r_lanes(cx<T> (&a)[5], cx<T> (&b)[5]) {
+template <typename T, int Q, typename Shift = LaneShift>
+__device__ __forceinline__ void iprime_r_lanes(cx<T> (&a)[5], cx<T> (&b)[5], const Shift& sh = Shift{}) {
   collide_r(a, b);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {   // S^T: q(x) <- q(x + 1)
-    if (Q) b[m] = from_next_lane(b[m]);
-    else   a[m] = from_next_lane(a[m]);
+    if (Q) b[m] = sh.next(b[m]);
+    else   a[m] = sh.next(a[m]);
   }
   collide_r(a, b);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {   // S: q(x) <- q(x - 1)
-    if (Q) b[m] = from_prev_lane(b[m]);
-    else   a[m] = from_prev_lane(a[m]);
+    if (Q) b[m] = sh.prev(b[m]);
+    else   a[m] = sh.prev(a[m]);
   }
 }
 
@@ -147,7 +156,7 @@ struct LineSlot {
   bool own;   // a site this lane computes
 };
 // Lines of one site have no neighbours (iprime_r_sites): a window takes 56 of them, where with halos
-// of their own it held seven (reverse step of 300 x 300 x 1 398 -> 255 us).
+// of their own it held seven.
 __device__ __forceinline__ LineSlot line_slot(uint32_t window, int lane, int n, int nlines) {
   if (n == 1) {
     const int line = (int)(window * kLineStride) + lane - kLineHalo;
