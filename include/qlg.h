@@ -286,8 +286,8 @@ qlg_status qlg_decode_records(qlg_ctx* ctx, const double* rec_host, int64_t nrec
  * context with the same key starts from that plan.  When the environment variable
  * QLG_TUNE_CACHE names a file, qlg_autotune also appends the plan to it as a text line
  * "key steps_per_pass tile_rows use_graph qubit_split" (key ending in "|lines" for line passes,
- * with the plan of bands that qlg_get_tuning reports), and qlg_init takes the last in-range line with its key from the file before
- * the process's own record. */
+ * with the plan of bands that qlg_get_tuning reports), and qlg_init takes the last in-range
+ * line with its key from the file before the process's own record. */
 qlg_status qlg_set_tuning(qlg_ctx* ctx, const qlg_tuning* tuning);
 qlg_status qlg_get_tuning(const qlg_ctx* ctx, qlg_tuning* tuning);
 qlg_status qlg_set_graph(qlg_ctx* ctx, int32_t use_graph);

@@ -256,6 +256,25 @@ bool lines_fit(const qlg_ctx* c) {
   return slots < most;
 }
 
+// The height of bands whose tiles cost least in rounds of one tile per SIMD (a band of r rows takes
+// r + 8 through the y half and r through the x half).  In FP64 a round costs the same whether another
+// runs beside it or not.  In FP32 one wavefront leaves a SIMD's issue slots half empty: two take 1.3
+// times as long as one (2048^2: 4.3 us a row alone, 6.0 in pairs; 9.0, 10.6 and 13.8 for three to five),
+// so a pair of rounds counts 18 and one alone 13 (2048^2: 38 rows in 500 us, where the count of single
+// rounds took 76 rows and 687).
+int band_rows(const qlg_ctx* c) {
+  const int64_t nsimd = std::max<int64_t>(simd_count(), 1);
+  const bool c64 = c->p.dtype == QLG_C64;
+  int64_t best = 0;
+  int rows = kMinTileRows;
+  for (int r = kMaxTileRows; r >= kMinTileRows; --r) {
+    const int64_t rounds = (band_tiles(c, r) + nsimd - 1) / nsimd;
+    const int64_t cost = (c64 ? rounds / 2 * 18 + rounds % 2 * 13 : rounds) * (2 * r + 8);
+    if (!best || cost < best) { best = cost; rows = r; }
+  }
+  return rows;
+}
+
 // The launch form, band height, 1D steps per pass and qubit split of a context for which neither
 // qlg_autotune nor qlg_set_tuning has chosen.  The lines are where the measured times per step
 // cross on MI355X (1024 SIMDs; us, complex128 / complex64):
@@ -272,12 +291,7 @@ bool lines_fit(const qlg_ctx* c) {
 //     14570 / 9010 against 15230 / 8530.  Plain split (a seventh of the arithmetic): 512^2 40 / 26
 //     against 55 / 44; 1100^2 209 / 79 against 120 / 72; 80^3 102 / 59 against 127 / 80; 110^3
 //     316 / 123 against 228 / 123.
-// Larger lattices run bands, of the height whose tiles cost least in rounds of one tile per SIMD
-// (a band of r rows takes r + 8 through the y half and r through the x half).  In FP64 a round costs
-// the same whether another runs beside it or not.  In FP32 one wavefront leaves a SIMD's issue
-// slots half empty: two take 1.3 times as long as one (2048^2: 4.3 us a row alone, 6.0 in pairs; 9.0,
-// 10.6 and 13.8 for three to five), so a pair of rounds counts 18 and one alone 13 (2048^2: 38 rows in
-// 500 us, where the count of single rounds took 76 rows and 687).
+// Larger lattices run bands, of the height that band_rows gives.
 void auto_plan(qlg_ctx* c) {
   c->eff = c->tuning;
   c->lines = false;
@@ -299,17 +313,8 @@ void auto_plan(qlg_ctx* c) {
   const int64_t sites = c->L.psi_elems / 5;
   const bool c64 = c->p.dtype == QLG_C64, plain = c->p.split == QLG_SPLIT_PLAIN;
   const int64_t most = plain ? (c64 ? 1100000 : 700000) : c->p.ndim == 2 ? 2500000 : int64_t(1) << 25;
-  if (sites <= most && lines_fit(c)) {
-    c->lines = true;
-    c->eff.tile_rows = qlg::kLineTileRows;
-    return;
-  }
-  int64_t best = 0;
-  for (int r = kMaxTileRows; r >= kMinTileRows; --r) {
-    const int64_t rounds = (band_tiles(c, r) + nsimd - 1) / nsimd;
-    const int64_t cost = (c64 ? rounds / 2 * 18 + rounds % 2 * 13 : rounds) * (2 * r + 8);
-    if (!best || cost < best) { best = cost; c->eff.tile_rows = r; }
-  }
+  c->lines = sites <= most && lines_fit(c);
+  if (!c->lines) c->eff.tile_rows = band_rows(c);
 }
 
 // Rebuild the wave-tile tables for the current plan.
@@ -320,8 +325,13 @@ qlg_status build_tiles(qlg_ctx* c) {
   } else {
     c->eff = c->tuning;
     c->lines = c->form == Form::kLines && lines_fit(c);
-    if (c->lines) c->eff.tile_rows = qlg::kLineTileRows, c->eff.qubit_split = 0;
+    if (c->lines) c->eff.qubit_split = 0;
   }
+  // The tile table of a plan of line passes: in 2D that of k_line_x's overlap partials, in 3D that of
+  // the bands that run the y and x axes of a step which records the overlap (bands of eight rows take
+  // each row twice through the y half: steps one by one of 256^3 7360 us in complex128 and 4090 in
+  // complex64, now 6070 and 3510; of 128^3 1055 and 600, now 950 and 515).
+  if (c->lines) c->eff.tile_rows = c->p.ndim == 3 ? band_rows(c) : qlg::kLineTileRows;
   const int W = qlg::line_cols(c->p.dtype);
   c->nline[0] = c->nline[1] = c->nline[2] = 0;
   for (int i = 0; i < c->p.nbatch; ++i) {

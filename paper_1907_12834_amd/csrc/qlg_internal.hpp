@@ -118,9 +118,9 @@ hipError_t launch_step2d(int dtype, bool plain, bool overlap, int tile_rows, boo
                          double tg0, double tg1, double tg25, const ExtPot& ext, double* ovpart,
                          hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // One axis of a 2D or 3D step as a line pass (axis 0 = x, 1 = y, 2 = z): the four substeps along
-// it, from in to out (not in place).  Needs the 8-row tile table and the groups of the plan of
-// line passes.  plain_u: this pass applies the plain split's U; prev (may equal out): as above, for
-// an x pass that records the overlap.
+// it, from in to out (not in place).  Needs the groups of the plan of line passes and, for the
+// overlap, the tile table of 8-row bands.  plain_u: this pass applies the plain split's U; prev (may
+// equal out): as above, for an x pass that records the overlap.
 constexpr int kLineTileRows = 8;                                             // windows of an x group
 constexpr int line_cols(int dtype) { return dtype == 0 ? 8 : 4; }            // columns of a y or z group
 hipError_t launch_line(int dtype, int axis, bool plain, bool overlap, bool plain_u, double full_factor, const void* in,
