@@ -403,15 +403,22 @@ QLG_HD void w_coefficients(const cx<T> (&a)[5], const cx<T> (&b)[5], const Angle
   const T x0 = kExt ? fma_t(ang.tg0, n, ext) : ang.tg0 * n;   // density phase
   const T x2 = ang.tg25 * n;                                  // singlet phase
 
-  // exp(-i x) - 1 = x (x c - i s) with c = (cos x - 1)/x^2, s = sin(x)/x.  When every angle of
-  // every lane is small (the usual case) all take short series without a branch per lane.
+  // exp(-i x) - 1 = x (x c - i s) with c = (cos x - 1)/x^2, s = sin(x)/x.  A site whose angles are
+  // small (the usual case) takes the short series whatever the other sites of its wavefront take: its
+  // result must not depend on the tile it lies in.  One test per wavefront keeps the branches out of
+  // the usual path.
   Series<T> f;
-  if (__builtin_expect(all_lanes(fmax(fabs(x0), fabs(x2)) <= T(0.125) && hh <= T(1.0 / 256.0)), 1)) {
+  const auto short_series = [&]() {
     phase_series(x0 * x0, &f.c0, &f.s0);
     phase_series(x2 * x2, &f.c2, &f.s2);
     half_angle_series(hh, &f.ch, &f.sh);
+  };
+  const bool small = fmax(fabs(x0), fabs(x2)) <= T(0.125) && hh <= T(1.0 / 256.0);
+  if (__builtin_expect(all_lanes(small), 1)) {
+    short_series();
   } else {
     f = general_series(x0, x2, hh);
+    if (small) short_series();
   }
   W.mu0 = cx<T>{x0 * x0 * f.c0, -(x0 * f.s0)};
   // singlet coefficient (exp(-i x2) - 1) / n = th g2/5 (x2 c - i s): no division by n, so empty or
