@@ -181,6 +181,7 @@ struct qlg_ctx {
   // bookkeeping
   int64_t step_count = 0;
   bool has_overlap = false;
+  int ov_tiles = 0;              // tiles that recorded the overlap (0: the whole tile table)
   bool norm0_valid = false;
   bool broken = false;
   std::string err;
@@ -397,6 +398,16 @@ bool pass_returns(const qlg_ctx* c, bool overlap) {
   return c->p.ndim == 2 && (c->lines || c->eff.qubit_split == 1);
 }
 
+// The tiles that a 1D pass of `steps` steps launches, 0 for the whole tile table.  The table is that of
+// the plan's steps per pass; a pass of fewer steps (a call's last, or every one of a loop of single
+// steps) has wider tiles, and a single lattice launches only those that hold sites of their own (us a
+// single step, complex128 / complex64: 50000 sites 15.9 / 11.5 -> 8.7 / 7.6, 100000
+// 17.5 / 12.5 -> 13.6 / 10.0).  A batch launches all, each instance's last ones empty.
+int pass_tiles_1d(const qlg_ctx* c, int steps) {
+  if (c->p.ndim != 1 || c->p.nbatch != 1 || c->eff.qubit_split == 1) return 0;
+  return tiles_1d(c->nx[0], steps, c->eff.qubit_split);
+}
+
 // One pass of the fused step from `in` to `out` (1D: `steps` steps; 2D: one step).
 // 3D, and 2D with the y half split (qubit_split 1): one step as several launches that
 // alternate between `in` and `out`, ending in `in`: 3D the z pass (one launch, or two with
@@ -409,7 +420,7 @@ bool pass_returns(const qlg_ctx* c, bool overlap) {
 hipError_t launch_pass(qlg_ctx* c, int steps, bool overlap, void* in, void* out, hipEvent_t ev0 = nullptr,
                        hipEvent_t ev1 = nullptr, bool keep_state = false) {
   const double th = angle_scale(c);
-  const LaunchGeom g = c->geom();
+  LaunchGeom g = c->geom();
   double* ov = c->sc(c->S.ov_part);
   const bool plain = c->p.split == QLG_SPLIT_PLAIN;
   const double tg0 = th * c->p.g0, tg1 = th * c->p.g1, tg25 = th * c->p.g2 / 5.0;
@@ -417,9 +428,11 @@ hipError_t launch_pass(qlg_ctx* c, int steps, bool overlap, void* in, void* out,
   ext.theta = th;
   const int rows = c->eff.tile_rows;
   const int dt = c->p.dtype;
-  if (c->p.ndim == 1)
+  if (c->p.ndim == 1) {
+    if (const int t = pass_tiles_1d(c, steps)) g.ntiles = t;
     return qlg::launch_step1d(dt, steps, c->eff.qubit_split, plain, overlap, in, out, g, tg0, tg1, tg25, ext,
                               ov, c->stream, ev0, ev1);
+  }
   const double ff = c->p.ndim == 2 ? 8.0 : 12.0;
   // A 3D step over four launches overwrites `in` (the state before the step) with its second
   // launch, so a step that records the overlap with that state runs as two launches.  Both
@@ -740,7 +753,7 @@ static qlg_status enqueue_record(qlg_ctx* c, double* rec, bool reference) {
   if (e != hipSuccess) return hip_check(c, e, "observables kernel");
   const double* ov = (!reference && c->has_overlap) ? c->sc(c->S.ov_part) : nullptr;
   const double* ref = (!reference && c->norm0_valid) ? c->sc(c->S.norm0) : nullptr;
-  e = qlg::launch_record(g, c->sc(c->S.obs_part), ov, ref, rec, c->step_count, c->stream);
+  e = qlg::launch_record(g, c->sc(c->S.obs_part), ov, c->ov_tiles, ref, rec, c->step_count, c->stream);
   return e == hipSuccess ? QLG_OK : hip_check(c, e, "observables record kernel");
 }
 
@@ -907,6 +920,7 @@ qlg_status qlg_step(qlg_ctx* c, int64_t nsteps) {
   }
   c->step_count += nsteps;
   c->has_overlap = true;
+  c->ov_tiles = pass_tiles_1d(c, (int)((nsteps - 1) % S) + 1);
   return QLG_OK;
 }
 

@@ -136,9 +136,10 @@ hipError_t launch_get_qubits(int dtype, const void* state, void* qb, const Launc
 hipError_t launch_observables(int dtype, int ndim, const void* state, const LaunchGeom& g, double g0,
                               double g1, double g2, const ExtPot& ext, double* part, hipStream_t st);
 // Per-instance record rec[nbatch][kRecord] from the chunk partials, the per-tile
-// overlap partials (ovpart may be null) and a reference record (ref may be null).
-hipError_t launch_record(const LaunchGeom& g, const double* part, const double* ovpart, const double* ref,
-                         double* rec, int64_t step, hipStream_t st);
+// overlap partials (ovpart may be null; ov_tiles > 0: of one instance's first tiles only) and a
+// reference record (ref may be null).
+hipError_t launch_record(const LaunchGeom& g, const double* part, const double* ovpart, int ov_tiles,
+                         const double* ref, double* rec, int64_t step, hipStream_t st);
 
 // Host checks of a parameter block shared by every entry point that takes one (no
 // device call, no allocation); *msg receives a static description of the failure.

@@ -1042,7 +1042,7 @@ __global__ __launch_bounds__(kChunk) void k_observables(const cx<T>* __restrict_
 // instead of 8 no faster).
 constexpr int kRecordThreads = 960;
 __global__ __launch_bounds__(kRecordThreads) void k_reduce_record(LaunchGeom g, const double* __restrict__ part,
-                                                                 const double* __restrict__ ovpart,
+                                                                 const double* __restrict__ ovpart, int ov_tiles,
                                                                  const double* __restrict__ ref,
                                                                  double* __restrict__ rec, double step) {
   static_assert(kRecordThreads % kNObs == 0 && kRecordThreads % 2 == 0 && kRecordThreads / kLanes >= kNObs + 2,
@@ -1056,8 +1056,9 @@ __global__ __launch_bounds__(kRecordThreads) void k_reduce_record(LaunchGeom g, 
   for (int64_t c = threadIdx.x; c < (int64_t)d.nchunks * kNObs; c += kRecordThreads) v += p[c];
   if (ovpart) {
     const double* q = ovpart + 2 * (int64_t)d.tile_begin;
+    const int64_t n = ov_tiles > 0 ? ov_tiles : (int64_t)d.ntx * d.nty * d.nz;
 #pragma unroll 8
-    for (int64_t t = threadIdx.x; t < 2 * (int64_t)d.ntx * d.nty * d.nz; t += kRecordThreads) o += q[t];
+    for (int64_t t = threadIdx.x; t < 2 * n; t += kRecordThreads) o += q[t];
   }
   red[0][threadIdx.x] = v;
   red[1][threadIdx.x] = o;
@@ -1281,9 +1282,9 @@ hipError_t launch_observables(int dtype, int ndim, const void* state, const Laun
   return hipGetLastError();
 }
 
-hipError_t launch_record(const LaunchGeom& g, const double* part, const double* ovpart, const double* ref,
-                         double* rec, int64_t step, hipStream_t st) {
-  hipLaunchKernelGGL(k_reduce_record, dim3(g.nbatch), dim3(kRecordThreads), 0, st, g, part, ovpart, ref, rec,
+hipError_t launch_record(const LaunchGeom& g, const double* part, const double* ovpart, int ov_tiles,
+                         const double* ref, double* rec, int64_t step, hipStream_t st) {
+  hipLaunchKernelGGL(k_reduce_record, dim3(g.nbatch), dim3(kRecordThreads), 0, st, g, part, ovpart, ov_tiles, ref, rec,
                      (double)step);
   return hipGetLastError();
 }
