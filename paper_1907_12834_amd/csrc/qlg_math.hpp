@@ -240,14 +240,31 @@ QLG_HD void half_angle_series(double y, double* c, double* s) {
   *s = fma(y, ps, 1.0);
 }
 
-// The same for any arguments: (c, s) of x0 and x2 through their half angles (cos x - 1 =
-// -2 sin^2(x/2) without cancellation), and (ch, sh) from hh = h^2.  Not inlined: the library
-// routines' constants would otherwise be hoisted out of the substep loops of every kernel,
-// into registers that the usual path needs (the pull-back spilled 40 of them per wavefront).
+// (c, s) of the density and singlet phases x0 and x2 and (ch, sh) of the half rotation, hh = h^2, for
+// small angles.
 template <typename T>
 struct Series {
   T c0, s0, c2, s2, ch, sh;
 };
+template <typename T>
+QLG_HD bool small_angles(T x0, T x2, T hh) {
+  return fmax(fabs(x0), fabs(x2)) <= T(0.125) && hh <= T(1.0 / 256.0);
+}
+template <typename T>
+QLG_HD Series<T> short_series(T x0, T x2, T hh) {
+  Series<T> r;
+  phase_series(x0 * x0, &r.c0, &r.s0);
+  phase_series(x2 * x2, &r.c2, &r.s2);
+  half_angle_series(hh, &r.ch, &r.sh);
+  return r;
+}
+
+// The same for any arguments: small angles by the short series, whatever the other sites of the
+// wavefront hold (a site's result must not depend on the tile it lies in); others through their half
+// angles (cos x - 1 = -2 sin^2(x/2) without cancellation).  Not inlined: the library routines' constants
+// would otherwise be hoisted out of the substep loops of every kernel, into registers that the usual path
+// needs (the pull-back spilled 40 of them per wavefront); nor is the choice per site, which there cost 1D
+// complex64 runs 2 %.
 template <typename T>
 __host__ __device__ __attribute__((noinline)) inline Series<T> general_series(T x0, T x2, T hh) {
   auto phase = [](T x, T* c, T* s) {
@@ -262,6 +279,7 @@ __host__ __device__ __attribute__((noinline)) inline Series<T> general_series(T 
     *c = T(-0.5) * sc * sc;
     *s = sc * cn;
   };
+  if (small_angles(x0, x2, hh)) return short_series(x0, x2, hh);
   Series<T> r;
   phase(x0, &r.c0, &r.s0);
   phase(x2, &r.c2, &r.s2);
@@ -403,23 +421,10 @@ QLG_HD void w_coefficients(const cx<T> (&a)[5], const cx<T> (&b)[5], const Angle
   const T x0 = kExt ? fma_t(ang.tg0, n, ext) : ang.tg0 * n;   // density phase
   const T x2 = ang.tg25 * n;                                  // singlet phase
 
-  // exp(-i x) - 1 = x (x c - i s) with c = (cos x - 1)/x^2, s = sin(x)/x.  A site whose angles are
-  // small (the usual case) takes the short series whatever the other sites of its wavefront take: its
-  // result must not depend on the tile it lies in.  One test per wavefront keeps the branches out of
-  // the usual path.
-  Series<T> f;
-  const auto short_series = [&]() {
-    phase_series(x0 * x0, &f.c0, &f.s0);
-    phase_series(x2 * x2, &f.c2, &f.s2);
-    half_angle_series(hh, &f.ch, &f.sh);
-  };
-  const bool small = fmax(fabs(x0), fabs(x2)) <= T(0.125) && hh <= T(1.0 / 256.0);
-  if (__builtin_expect(all_lanes(small), 1)) {
-    short_series();
-  } else {
-    f = general_series(x0, x2, hh);
-    if (small) short_series();
-  }
+  // exp(-i x) - 1 = x (x c - i s) with c = (cos x - 1)/x^2, s = sin(x)/x.  When every angle of
+  // every lane is small (the usual case) all take short series without a branch per lane.
+  const Series<T> f = __builtin_expect(all_lanes(small_angles(x0, x2, hh)), 1) ? short_series(x0, x2, hh)
+                                                                               : general_series(x0, x2, hh);
   W.mu0 = cx<T>{x0 * x0 * f.c0, -(x0 * f.s0)};
   // singlet coefficient (exp(-i x2) - 1) / n = th g2/5 (x2 c - i s): no division by n, so empty or
   // denormal sites stay finite; times exp(-i x0) = 1 + mu0

@@ -111,23 +111,15 @@ QLG_HD void potential_vjp(const cx<double> (&a)[5], const cx<double> (&b)[5], cx
   auto pj_series = [](double y) {   // y = phi^2 <= 1/64: first omitted term y^5/6227020800 (1e-19)
     return fma(y, fma(y, fma(y, fma(y, 1.0 / 39916800.0, -1.0 / 362880.0), 1.0 / 5040.0), -1.0 / 120.0), 1.0 / 6.0);
   };
-  // by the site's own angles, as in w_coefficients
-  const auto short_series = [&]() {
-    phase_series(x0 * x0, &f.c0, &f.s0);
-    phase_series(x2 * x2, &f.c2, &f.s2);
-    half_angle_series(hh, &f.ch, &f.sh);
+  if (__builtin_expect(all_lanes(fmax(fabs(x0), fabs(x2)) <= 0.1 && hh <= 1.0 / 256.0), 1)) {
+    f = short_series(x0, x2, hh);
     pd = pd_series(x2 * x2);
     pj = pj_series(4.0 * hh);
-  };
-  const bool small = fmax(fabs(x0), fabs(x2)) <= 0.1 && hh <= 1.0 / 256.0;
-  if (__builtin_expect(all_lanes(small), 1)) {
-    short_series();
-  } else {
+  } else {   // each by the site's own angles
     f = general_series(x0, x2, hh);
     const double y2 = x2 * x2;
-    pd = fabs(x2) < 0.1 ? pd_series(y2) : (f.s2 - fma(y2, f.c2, 1.0)) * rcp_t(y2);
+    pd = fabs(x2) <= 0.1 ? pd_series(y2) : (f.s2 - fma(y2, f.c2, 1.0)) * rcp_t(y2);
     pj = hh <= 1.0 / 256.0 ? pj_series(4.0 * hh) : (1.0 - f.sh * f.ch) * rcp_t(4.0 * hh);
-    if (small) short_series();
   }
   const cx<double> mu0{x0 * x0 * f.c0, -(x0 * f.s0)};
   const cx<double> cs{kappa * x2 * f.c2, -(kappa * f.s2)};        // c(n)
