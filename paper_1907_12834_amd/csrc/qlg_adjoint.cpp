@@ -229,11 +229,12 @@ qlg_status qlg_adjoint_step(qlg_ctx* ctx, int64_t nsteps, int32_t K, const void*
   const hipStream_t str = v.stream;
   const int nd = p.ndim, dt = p.dtype, nsub = s.nsub, nrec = s.nrec;
   int* xpre = (int*)(W + s.off_xpre);
-  // 32-bit group numbers, and 32-bit slots (56 per window)
-  const int64_t lim = INT32_MAX;
-  if (!plain && (std::max({s.nrecg[0], s.nrecg[1], qlg::kAdjCols * s.nadjg[0], qlg::kAdjCols * s.nadjg[1]}) > lim ||
-                 std::max({s.nx, s.nthin[0], s.nthin[1]}) > UINT32_MAX / qlg::kLanes))
-    return qlg::ctx_fail(ctx, QLG_ERR_ARG, "lattice too large for the adjoint's tile tables");
+  // 32-bit slots (56 per window) and partial numbers, and the threads of a launch
+  const int rec_threads = qlg::kLanes * qlg::line_cols(dt), adj_threads = qlg::kLanes * qlg::kAdjCols;
+  if (!plain && !(qlg::launch_fits(std::max({s.nx, s.nthin[0], s.nthin[1]}), qlg::kLanes) &&
+                  qlg::launch_fits(std::max(s.nrecg[0], s.nrecg[1]), rec_threads) &&
+                  qlg::launch_fits(std::max(s.nadjg[0], s.nadjg[1]), adj_threads)))
+    return qlg::ctx_fail(ctx, QLG_ERR_ARG, "lattice too large for the adjoint's launches");
   const qlg::LineCounts lines{(int)s.nx, {(int)s.nrecg[0], (int)s.nrecg[1]}, {(int)s.nadjg[0], (int)s.nadjg[1]},
                               {(int)s.nthin[0], (int)s.nthin[1]}};
   const double theta = p.eps * p.eps / (4.0 * nd);

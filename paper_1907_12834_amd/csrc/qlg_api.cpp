@@ -246,15 +246,18 @@ int64_t band_tiles(const qlg_ctx* c, int rows) {
   return t;
 }
 
-// Whether the line passes' 32-bit slot numbers hold every instance's lines.
+// Whether the line passes' 32-bit slot numbers hold every instance's lines, and a launch its groups.
 bool lines_fit(const qlg_ctx* c) {
-  const int64_t most = int64_t(1) << 31;
-  int64_t slots = 0;
+  const int cols = qlg::line_cols(c->p.dtype);
+  int64_t slots = 0, total[3] = {0, 0, 0}, g[3];
   for (const auto& d : c->L.inst) {
     slots += std::max({qlg::line_slots<int64_t>(d.nx) * d.ny * d.nz, qlg::line_slots<int64_t>(d.ny) * d.nx * d.nz,
                        qlg::line_slots<int64_t>(d.nz) * d.nx * d.ny});
+    qlg::line_launch_groups(d.nx, d.ny, d.nz, cols, g);
+    for (int q = 0; q < c->p.ndim; ++q) total[q] += g[q];
   }
-  return slots < most;
+  return slots < int64_t(1) << 31 && qlg::launch_fits(total[0], qlg::kLanes * qlg::kLineTileRows) &&
+         qlg::launch_fits(std::max(total[1], total[2]), qlg::kLanes * cols);
 }
 
 // The height of bands whose tiles cost least in rounds of one tile per SIMD (a band of r rows takes
@@ -333,7 +336,6 @@ qlg_status build_tiles(qlg_ctx* c) {
   // each row twice through the y half: steps one by one of 256^3 7360 us in complex128 and 4090 in
   // complex64, now 6070 and 3510; of 128^3 1055 and 600, now 950 and 515).
   if (c->lines) c->eff.tile_rows = c->p.ndim == 3 ? band_rows(c) : qlg::kLineTileRows;
-  const int W = qlg::line_cols(c->p.dtype);
   c->nline[0] = c->nline[1] = c->nline[2] = 0;
   for (int i = 0; i < c->p.nbatch; ++i) {
     InstDesc& d = c->L.inst[i];
@@ -346,11 +348,10 @@ qlg_status build_tiles(qlg_ctx* c) {
     }
     for (int64_t k = 0; k < (int64_t)d.ntx * d.nty * d.nz; ++k) t2i.push_back(i);
     if (c->lines) {
-      const int64_t ncol = (d.nx + W - 1) / W;
+      int64_t groups[3];
+      qlg::line_launch_groups(d.nx, d.ny, d.nz, qlg::line_cols(c->p.dtype), groups);
       for (int q = 0; q < 3; ++q) d.line[q] = c->nline[q];
-      c->nline[0] += (int32_t)((qlg::line_windows<int64_t>(d.nx, (int64_t)d.ny * d.nz) + qlg::kLineTileRows - 1) / qlg::kLineTileRows);
-      c->nline[1] += (int32_t)qlg::line_groups<int64_t>(d.ny, d.nz, ncol);
-      if (c->p.ndim == 3) c->nline[2] += (int32_t)qlg::line_groups<int64_t>(d.nz, d.ny, ncol);
+      for (int q = 0; q < c->p.ndim; ++q) c->nline[q] += (int32_t)groups[q];
     } else if (c->p.ndim == 3) {
       d.tile_begin_z = (int32_t)t2i_z.size();
       tiles_z(d.nx, d.nz, c->eff.tile_rows, &d.ntx_z, &d.ntz);

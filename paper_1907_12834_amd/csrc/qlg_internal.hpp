@@ -64,6 +64,19 @@ constexpr I line_groups(I n, I nplanes, I ncol) {
   return (ncol + f - 1) / f * line_windows<I>(n, nplanes * f);
 }
 
+// The groups of one instance's x, y and z line launches: kLineTileRows windows along x, one window of
+// `cols` columns along y and z.
+constexpr int kLineTileRows = 8;
+inline void line_launch_groups(int64_t nx, int64_t ny, int64_t nz, int cols, int64_t (&groups)[3]) {
+  const int64_t ncol = (nx + cols - 1) / cols;
+  groups[0] = (line_windows<int64_t>(nx, ny * nz) + kLineTileRows - 1) / kLineTileRows;
+  groups[1] = line_groups<int64_t>(ny, nz, ncol);
+  groups[2] = line_groups<int64_t>(nz, ny, ncol);
+}
+// A launch holds fewer than 2^32 threads.  (A y group's columns past a lattice of one to three columns
+// are threads too: 1 x 24000 x 24000 would take 5.3e9 in complex64.)
+constexpr bool launch_fits(int64_t workgroups, int threads) { return workgroups <= int64_t(UINT32_MAX) / threads; }
+
 // The adjoint's passes along y and z over axes of up to kThinAxis sites hold whole lines, without halos,
 // as rings of lanes: the windows (wavefronts) of nlines lines of n sites.
 constexpr int kThinAxis = 3;
@@ -121,7 +134,6 @@ hipError_t launch_step2d(int dtype, bool plain, bool overlap, int tile_rows, boo
 // it, from in to out (not in place).  Needs the groups of the plan of line passes and, for the
 // overlap, the tile table of 8-row bands.  plain_u: this pass applies the plain split's U; prev (may
 // equal out): as above, for an x pass that records the overlap.
-constexpr int kLineTileRows = 8;                                             // windows of an x group
 constexpr int line_cols(int dtype) { return dtype == 0 ? 8 : 4; }            // columns of a y or z group
 hipError_t launch_line(int dtype, int axis, bool plain, bool overlap, bool plain_u, double full_factor, const void* in,
                        void* out, const void* prev, const LaunchGeom& g, double tg0, double tg1, double tg25,
