@@ -326,7 +326,7 @@ __global__ __launch_bounds__(kChunk) void k_sub_vjp(const cx<T>* __restrict__ z,
 // cotangent in registers through four substeps.  With a launch per y substep (each read the
 // cotangent of three sites and a record and wrote the cotangent), a persistent kernel for the four x
 // substeps and the derivative in the frame of F a reverse step of 512^2 took 278 us in complex64,
-// 355 in complex128, of 64^2 in complex128 64; now 172, 223 and 39.  Bound by the FP64 derivative (1060
+// 355 in complex128, of 64^2 in complex128 64; now 172, 227 and 39.  Bound by the FP64 derivative (1060
 // instructions per substep; 256 registers, so two wavefronts per SIMD: 52 % of the issue rate at
 // 512^2) and by the records' traffic.  Records copied to LDS a substep ahead gained nothing (512^2
 // complex64 180 -> 186 us, complex128 229 -> 227).  Along y and z axes of up to kThinAxis sites the

@@ -283,18 +283,18 @@ int band_rows(const qlg_ctx* c) {
 // qlg_autotune nor qlg_set_tuning has chosen.  The lines are where the measured times per step
 // cross on MI355X (1024 SIMDs; us, complex128 / complex64):
 //   1D: a lattice that leaves SIMDs idle buys time with redundant work, as many steps per pass and
-//     lanes per site as keep one wavefront per SIMD (1024 sites: 4.5 / 4.1 with the two-lane kernel
-//     at 3 steps per pass against 7.4 / 7.1 at one step; 16384: 5.1 / 4.6 at 2); with two
-//     wavefronts per SIMD 4 steps of the one-lane kernel (65536: 9.1 / 7.0 against 12.1 / 9.5),
-//     beyond that 2 (524288: 48.7 / 30.0; 1: 50.2 / 31.0, 3: 54.3 / 34.0).
+//     lanes per site as keep one wavefront per SIMD (1024 sites: 4.2 / 3.7 with the two-lane kernel
+//     at 3 steps per pass against 6.7 / 6.4 at one step; 16384: 4.7 / 4.2 at 2, 7.2 / 6.6); with two
+//     wavefronts per SIMD 4 steps of the one-lane kernel (65536: 9.8 / 6.6 against 12.0 / 9.0),
+//     beyond that 2 (524288: 54.2 / 32.5; 1: 54.8 / 33.9, 3: 60.4 / 36.0).
 //   2D and 3D: line passes finish a launch in four substeps, a band only after its rows, but read
-//     and write the state once per axis.  Interleaved, lines against the best bands: 64^2 17 / 17
-//     against 100 / 95; 1024^2 215 / 130 against 267 / 174; 1448^2 420 / 255 against 438 / 292;
-//     1700^2 573 / 374 against 590 / 370; 2048^2 836 / 515 against 800 / 485; 3D, where bands take
-//     two passes too, 64^3 110 / 82 against 182 / 174, 256^3 5200 / 3160 against 5770 / 3240; 360^3
-//     14570 / 9010 against 15230 / 8530.  Plain split (a seventh of the arithmetic): 512^2 40 / 26
-//     against 55 / 44; 1100^2 209 / 79 against 120 / 72; 80^3 102 / 59 against 127 / 80; 110^3
-//     316 / 123 against 228 / 123.
+//     and write the state once per axis.  Interleaved, lines against the best bands: 64^2 16 / 16
+//     against 105 / 94; 1024^2 228 / 133 against 273 / 179; 1448^2 438 / 262 against 466 / 300;
+//     1700^2 606 / 362 against 617 / 357; 2048^2 881 / 508 against 870 / 498; 3D, where bands take
+//     two passes too, 64^3 115 / 80 against 191 / 172, 256^3 5490 / 3160 against 5680 / 3110; 360^3
+//     14960 / 8720 against 16300 / 8740.  Plain split (a seventh of the arithmetic): 512^2 39 / 25
+//     against 55 / 43; 1100^2 206 / 75 against 116 / 76; 80^3 93 / 55 against 133 / 82; 110^3
+//     323 / 121 against 234 / 119.
 // Larger lattices run bands, of the height that band_rows gives.
 void auto_plan(qlg_ctx* c) {
   c->eff = c->tuning;

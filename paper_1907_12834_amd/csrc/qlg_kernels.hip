@@ -696,11 +696,11 @@ void k_step2d(StepArgs<T> A) {
 // 64/56 (R + 8)/R in the row pipeline.  For lattices that cannot give every SIMD a tall band, and
 // where the extra traffic stays in the caches (qlg_api.cpp chooses, with the times of both).
 //
-// Bounds: on the smallest lattices the chain of one wavefront (64^2: 2200 instructions, about five
-// cycles each); on large ones the vector instructions (256^3 complex64 issues them at the SIMDs'
+// Bounds: on the smallest lattices the chain of one wavefront (64^2: 2200 to 2400 instructions, about
+// five cycles each); on large ones the vector instructions (256^3 complex64 issues them at the SIMDs'
 // rate); between them the rounds of wavefronts and their loads and stores, during which nothing
-// computes (611 x 347 complex128: 14 us of instructions in a 26 us launch).  Held against that and
-// slower: two sites per lane (a tenth fewer instructions: 512^2 complex128 63 -> 82 us a step, 256^3
+// computes (611 x 347 complex128: 15 us of instructions in a 29 us launch).  Held against that and
+// slower, when complex128 took 20 instructions per self-interaction and vector less: two sites per lane (a tenth fewer instructions: 512^2 complex128 63 -> 82 us a step, 256^3
 // complex64 3.16 -> 3.67 ms), complex128 in 128 registers for a fourth wavefront per SIMD (1024^2
 // 211 -> 267 us), complex64 in 96 for a fifth (512^2 45.8 -> 46.4), persistent wavefronts that load
 // the next window ahead (512^2 complex128 64 -> 84 us).

@@ -148,7 +148,8 @@ __device__ __forceinline__ int xcd_contiguous_block(int b, int nblocks) {
 // or just below a multiple of 56 the latter are fewer, and the line's slots are that multiple.  Time
 // per step with windows that begin with each line, and with these (us, complex128 / complex64): 64^3
 // 131 / 93, 109 / 82; 50 x 70 x 90 135 / 95, 127 / 90; 128^3 785 / 525, 700 / 435; 256^3 5360 / 3365,
-// 5200 / 3170; 1024^2 215 / 140, 215 / 132; the reverse step of 64^3 368 in complex64, 290.
+// 5200 / 3170; 1024^2 215 / 140, 215 / 132; the reverse step of 64^3 368 in complex64, 290.  (Those of
+// complex128 before w_apply kept the state apart from its corrections; now 115, 127, 710, 5490 and 228.)
 constexpr int kLineStride = kLanes - 2 * kLineHalo;
 struct LineSlot {
   int line;   // its line (past the last one: any)

@@ -311,11 +311,11 @@ __host__ __device__ __attribute__((noinline)) inline Series<T> general_series(T 
 //
 // The self-interaction is what bounds the step kernels (vector instructions).  Building this
 // matrix once per site takes about as many as the frame of F (Euler angles, d(beta), the phases
-// of each m) that stood here before; applying it takes 50 multiply-adds and 8 to 18 additions
-// per 5-vector, where the frame took 138 instructions.  With collide_r (40 additions per I'
-// instead of 80) 20 steps of 2048^2 in complex128 went from 19.7 to 15.9 ms, in complex64 with
-// every component populated from 14.2 to 10.5 ms, 50 steps of 256 uneven 1D runs from 8.1 to
-// 6.4 ms.
+// of each m) that stood here before; applying R - I takes 50 multiplications and multiply-adds
+// and 16 additions per 5-vector (and 10 for the base it is added to), where the frame took 138
+// instructions.  With collide_r (40 additions per I' instead of 80) 20 steps of 2048^2 in complex128
+// went from 19.7 to 16.4 ms, in complex64 with every component populated from 14.2 to 10.9 ms,
+// 50 steps of 256 uneven 1D runs from 8.2 to 6.5 ms.
 template <typename T>
 struct Rot2 {
   T ss22, st22i, ss21i, st21, s20;
