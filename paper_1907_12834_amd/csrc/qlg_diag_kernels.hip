@@ -4,6 +4,8 @@
 //
 // Both read psi = a + b formed in the state's own precision (the value
 // qlg_get_psi returns) and work in FP64 from there.
+#include <algorithm>
+
 #include "qlg_diag.hpp"
 #include "qlg_math.hpp"
 
@@ -296,9 +298,11 @@ __global__ __launch_bounds__(kV3Threads) void k_vorticity3d(const cx<T>* __restr
 // ranked inside the chunk by wave ballots.  Chunk number k is chunk k % nchunks of
 // family k / nchunks, whose windings sit at (k / nchunks) * cstride.
 // A wavefront counts four chunks, the loads of all in flight together: a workgroup per chunk cost
-// 12.4 us for the 16384 of 2048^2, by the launch rate of workgroups; now 5.0 us.
-constexpr int kCountChunks = 4;     // chunks per wavefront
+// 12.4 us for the 16384 of 2048^2, by the launch rate of workgroups; now 5.0 us.  (kPer: one where few
+// chunks leave SIMDs without a wavefront.)
+constexpr int kCountChunks = 4;     // chunks per wavefront, at most
 constexpr int kScatterChunks = 8;
+constexpr int kFewChunks = 2048;    // up to here one: two wavefronts per SIMD
 constexpr int kChunkLoads = kChunk / kLanes;
 
 // Chunk number k: its instance, and the sites and windings of this lane, 64 apart.
@@ -321,19 +325,20 @@ struct CoreChunk {
   }
 };
 
+template <int kPer>
 __global__ __launch_bounds__(kChunk) void k_core_count(const int32_t* __restrict__ wind, LaunchGeom g, int nblocks,
                                                       int64_t cstride, int64_t* __restrict__ counts) {
   const int lane = threadIdx.x & (kLanes - 1);
-  const int first = (blockIdx.x * (kChunk / kLanes) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kCountChunks;
-  int32_t w[kCountChunks][kChunkLoads];
+  const int first = (blockIdx.x * (kChunk / kLanes) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kPer;
+  int32_t w[kPer][kChunkLoads];
 #pragma unroll
-  for (int j = 0; j < kCountChunks; ++j) {
+  for (int j = 0; j < kPer; ++j) {
     const CoreChunk ch(g, wind, cstride, first + j < nblocks ? first + j : nblocks - 1, lane);
 #pragma unroll
     for (int q = 0; q < kChunkLoads; ++q) w[j][q] = ch.load(q);
   }
 #pragma unroll
-  for (int j = 0; j < kCountChunks; ++j) {
+  for (int j = 0; j < kPer; ++j) {
     int n = 0;
 #pragma unroll
     for (int q = 0; q < kChunkLoads; ++q) n += __popcll(__ballot(w[j][q] != 0));
@@ -342,7 +347,7 @@ __global__ __launch_bounds__(kChunk) void k_core_count(const int32_t* __restrict
 }
 
 constexpr int kScanThreads = 1024;
-constexpr int kScanPer = 16;   // counts per thread
+constexpr int kScanPer = 16;   // counts per thread, at most
 
 // Inclusive scan over the lanes of a wavefront through DPP: shifts within the rows of 16 lanes, then
 // the last lane of row 0 into row 1, of row 2 into row 3, and of row 1 into rows 2 and 3.
@@ -362,20 +367,22 @@ __device__ __forceinline__ int wave_scan(int v) {
 // In place: counts[c] <- sum of counts[0..c), and *total <- the sum of all.  A wavefront scans
 // 16 x 64 counts, the 16 wavefronts' sums go through LDS: two barriers per 16384 counts (up to 256
 // each: 32 bits hold their sum), where a scan through LDS of 1024 at a time took 20 barriers for each
-// (31 us for 16384; now 5.8, with the counts read as they lie: sixteen in a row per thread, 18).
+// (31 us for 16384; now 5.8, with the counts read as they lie: sixteen in a row per thread, 18).  Up to
+// 1024 counts take one per thread (kPer), where sixteen would go to one wavefront (3.3 us; 2.1).
+template <int kPer>
 __global__ __launch_bounds__(kScanThreads) void k_core_scan(int64_t* __restrict__ counts, int nchunks,
                                                            int64_t* __restrict__ total) {
   constexpr int kW = kScanThreads / kLanes;
   __shared__ int wsum[kW];
   const int lane = threadIdx.x & (kLanes - 1), wv = threadIdx.x / kLanes;
   int64_t carry = 0;
-  for (int64_t base = 0; base < nchunks; base += kScanThreads * kScanPer) {
-    const int64_t i = base + wv * (kLanes * kScanPer) + lane;
-    int v[kScanPer], run = 0;
+  for (int64_t base = 0; base < nchunks; base += kScanThreads * kPer) {
+    const int64_t i = base + wv * (kLanes * kPer) + lane;
+    int v[kPer], run = 0;
 #pragma unroll
-    for (int j = 0; j < kScanPer; ++j) v[j] = i + j * kLanes < nchunks ? (int)counts[i + j * kLanes] : 0;
+    for (int j = 0; j < kPer; ++j) v[j] = i + j * kLanes < nchunks ? (int)counts[i + j * kLanes] : 0;
 #pragma unroll
-    for (int j = 0; j < kScanPer; ++j) {
+    for (int j = 0; j < kPer; ++j) {
       const int inc = wave_scan(v[j]);
       v[j] = run + inc - v[j];
       run += __builtin_amdgcn_readlane(inc, kLanes - 1);
@@ -389,33 +396,26 @@ __global__ __launch_bounds__(kScanThreads) void k_core_scan(int64_t* __restrict_
       carry += wsum[j];
     }
 #pragma unroll
-    for (int j = 0; j < kScanPer; ++j)
+    for (int j = 0; j < kPer; ++j)
       if (i + j * kLanes < nchunks) counts[i + j * kLanes] = at + v[j];
     __syncthreads();   // wsum is rewritten by the next counts
   }
   if (threadIdx.x == 0) *total = carry;
 }
 
-// A wavefront looks at eight chunks' offsets and reads the windings of those that hold cores (16384
-// chunks with few cores: 5.8 us; every chunk read by a workgroup of its own, 12.4).
+// A wavefront looks at the offsets of `per` chunks and reads the windings of those that hold cores, one
+// chunk after the other: eight on large lattices (16384 chunks with few cores: 5.8 us; every chunk read by
+// a workgroup of its own, 12.4), fewer where that would leave SIMDs without a wavefront (cores in every
+// chunk: 512^2 13.3 -> 3.7 us, 1024^2 13.5 -> 6.0).
 __global__ __launch_bounds__(kChunk) void k_core_scatter(const int32_t* __restrict__ wind, LaunchGeom g, int nblocks,
-                                                        int ndim, int64_t cstride,
+                                                        int per, int ndim, int64_t cstride,
                                                         const int64_t* __restrict__ offsets,
                                                         const int64_t* __restrict__ total,
                                                         int32_t* __restrict__ out, int64_t capacity) {
   const int lane = threadIdx.x & (kLanes - 1);
-  const int first =
-      (blockIdx.x * (kChunk / kLanes) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kScatterChunks;
-  const bool have = lane < kScatterChunks && first + lane < nblocks;
-  const int64_t o = have ? offsets[first + lane] : 0;
-  const int64_t o1 = have ? (first + lane + 1 < nblocks ? offsets[first + lane + 1] : *total) : 0;
-  for (unsigned long long todo = __ballot(have && o1 > o && o < capacity); todo; todo &= todo - 1) {
-    const int j = __ffsll((long long)todo) - 1;
-    const CoreChunk ch(g, wind, cstride, first + j, lane);
-    int64_t at = __shfl((long long)o, j, kLanes);
-    int32_t w[kChunkLoads];
-#pragma unroll
-    for (int q = 0; q < kChunkLoads; ++q) w[q] = ch.load(q);
+  const int first = (blockIdx.x * (kChunk / kLanes) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * per;
+  // writes the cores of a chunk, whose windings are w, from place `at` of the list on
+  const auto put = [&](const CoreChunk& ch, const int32_t (&w)[kChunkLoads], int64_t at) {
 #pragma unroll
     for (int q = 0; q < kChunkLoads; ++q) {
       const unsigned long long mask = __ballot(w[q] != 0);
@@ -440,6 +440,25 @@ __global__ __launch_bounds__(kChunk) void k_core_scatter(const int32_t* __restri
         e[3] = w[q];
       }
     }
+  };
+  int32_t w[kChunkLoads];
+  if (per == 1) {   // one chunk: its windings and its offset loaded together
+    if (first >= nblocks) return;
+    const CoreChunk ch(g, wind, cstride, first, lane);
+#pragma unroll
+    for (int q = 0; q < kChunkLoads; ++q) w[q] = ch.load(q);
+    put(ch, w, offsets[first]);
+    return;
+  }
+  const bool have = lane < per && first + lane < nblocks;
+  const int64_t o = have ? offsets[first + lane] : 0;
+  const int64_t o1 = have ? (first + lane + 1 < nblocks ? offsets[first + lane + 1] : *total) : 0;
+  for (unsigned long long todo = __ballot(have && o1 > o && o < capacity); todo; todo &= todo - 1) {
+    const int j = __ffsll((long long)todo) - 1;
+    const CoreChunk ch(g, wind, cstride, first + j, lane);
+#pragma unroll
+    for (int q = 0; q < kChunkLoads; ++q) w[q] = ch.load(q);
+    put(ch, w, __shfl((long long)o, j, kLanes));
   }
 }
 
@@ -505,15 +524,22 @@ hipError_t launch_vortex_cores(const int32_t* winding, const LaunchGeom& g, int 
   if (g.nchunks == 0) return hipSuccess;
   const int nblocks = (ndim == 3 ? 3 : 1) * g.nchunks;
   const auto blocks = [&](int per) { return dim3((nblocks + per * (kChunk / kLanes) - 1) / (per * (kChunk / kLanes))); };
-  hipLaunchKernelGGL(k_core_count, blocks(kCountChunks), dim3(kChunk), 0, st, winding, g, nblocks, component_stride,
-                     counts);
+  if (nblocks > kFewChunks)
+    hipLaunchKernelGGL(k_core_count<kCountChunks>, blocks(kCountChunks), dim3(kChunk), 0, st, winding, g, nblocks,
+                       component_stride, counts);
+  else
+    hipLaunchKernelGGL(k_core_count<1>, blocks(1), dim3(kChunk), 0, st, winding, g, nblocks, component_stride, counts);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_core_scan, dim3(1), dim3(kScanThreads), 0, st, counts, nblocks, total);
+  if (nblocks > kScanThreads)
+    hipLaunchKernelGGL(k_core_scan<kScanPer>, dim3(1), dim3(kScanThreads), 0, st, counts, nblocks, total);
+  else
+    hipLaunchKernelGGL(k_core_scan<1>, dim3(1), dim3(kScanThreads), 0, st, counts, nblocks, total);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_core_scatter, blocks(kScatterChunks), dim3(kChunk), 0, st, winding, g, nblocks, ndim,
-                     component_stride, counts, total, out, capacity);
+  const int per = std::min(kScatterChunks, 1 + (nblocks - 1) / kFewChunks);
+  hipLaunchKernelGGL(k_core_scatter, blocks(per), dim3(kChunk), 0, st, winding, g, nblocks, per, ndim, component_stride,
+                     counts, total, out, capacity);
   return hipGetLastError();
 }
 
