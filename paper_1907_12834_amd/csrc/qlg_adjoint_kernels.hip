@@ -116,13 +116,14 @@ __device__ __forceinline__ void load_site_nt(const cx<T>* __restrict__ st, const
 }
 
 // C^H times (1 - i), the adjoint of collide_r:  a' = a - i b,  b' = b - i a
+__device__ __forceinline__ void collide_r_adj(cx<double>& a, cx<double>& b) {
+  const cx<double> x = a, y = b;
+  a = cx<double>{x.re + y.im, x.im - y.re};
+  b = cx<double>{y.re + x.im, y.im - x.re};
+}
 __device__ __forceinline__ void collide_r_adj(cx<double> (&a)[5], cx<double> (&b)[5]) {
 #pragma unroll
-  for (int m = 0; m < 5; ++m) {
-    const cx<double> x = a[m], y = b[m];
-    a[m] = cx<double>{x.re + y.im, x.im - y.re};
-    b[m] = cx<double>{y.re + x.im, y.im - x.re};
-  }
+  for (int m = 0; m < 5; ++m) collide_r_adj(a[m], b[m]);
 }
 
 // lambda <- I'^H_{q} lambda with the axis along the lanes: q from the next site, C^H, q from the
@@ -248,26 +249,32 @@ __global__ __launch_bounds__(kChunk) void k_chain(const cx<T>* __restrict__ in, 
 __device__ __forceinline__ void iprime_adj_site(const cx<double>* __restrict__ in, const Site& r, int axis, int qb,
                                                 cx<double> (&oa)[5], cx<double> (&ob)[5]) {
   const int sm = neighbour(r, axis, -1), sp = neighbour(r, axis, +1);
-  cx<double> a0[5], b0[5], a1[5], b1[5], a2[5], b2[5];
-  load_site(in, r.d, sm, a0, b0);
-  load_site(in, r.d, r.s, a1, b1);
-  load_site(in, r.d, sp, a2, b2);
-  cx<double> wa[5], wb[5], va[5], vb[5];   // w(x), w(x-1)
+  // All loads of a thread are in flight before the first is used, the components one after the other: one
+  // component's result waits for its six loads only.  Left to itself the compiler takes the loads in groups,
+  // in 73 registers (a substep of 512^2 15.9 us, of 1024^2 82; so 13.8 and 73).
+  cx<double> z[5][6];   // a and b at x-1, x, x+1
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    wa[m] = sel(qb != 0, a1[m], a2[m]);
-    wb[m] = sel(qb != 0, b2[m], b1[m]);
-    va[m] = sel(qb != 0, a0[m], a1[m]);
-    vb[m] = sel(qb != 0, b1[m], b0[m]);
+    const cx<double>* p = in + r.d.off + m * r.d.stride;
+    const cx<double>* q = p + 5 * r.d.stride;
+    z[m][0] = p[sm];
+    z[m][1] = q[sm];
+    z[m][2] = p[r.s];
+    z[m][3] = q[r.s];
+    z[m][4] = p[sp];
+    z[m][5] = q[sp];
   }
-  collide_r_adj(wa, wb);
-  collide_r_adj(va, vb);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    oa[m] = sel(qb != 0, wa[m], va[m]);
-    ob[m] = sel(qb != 0, vb[m], wb[m]);
+    cx<double> wa = sel(qb != 0, z[m][2], z[m][4]), wb = sel(qb != 0, z[m][5], z[m][3]);   // w(x)
+    cx<double> va = sel(qb != 0, z[m][0], z[m][2]), vb = sel(qb != 0, z[m][3], z[m][1]);   // w(x-1)
+    collide_r_adj(wa, wb);
+    collide_r_adj(va, vb);
+    oa[m] = sel(qb != 0, wa, va);
+    ob[m] = sel(qb != 0, vb, wb);
+    collide_r_adj(oa[m], ob[m]);
   }
-  collide_r_adj(oa, ob);
   unphase_by(oa, ob, -0.5);
 }
 
