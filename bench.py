@@ -62,18 +62,18 @@ PREROLL_S = 0.2        # untimed steps right before each clock start, at least t
 # WRITE_SIZE: x1.000).  Valid only for the kernel sources it was measured on.
 KERNEL_SOURCES = ["paper_1907_12834_amd/csrc/qlg_math.hpp", "paper_1907_12834_amd/csrc/qlg_lanes.hpp",
                   "paper_1907_12834_amd/csrc/qlg_kernels.hip", "paper_1907_12834_amd/csrc/qlg_internal.hpp"]
-TRAFFIC = {"sources_sha256_16": "4472dfa9f75aecd6", "fetch_scale": 262144.0 / 131088.5, "write_scale": 1.0,
+TRAFFIC = {"sources_sha256_16": "92e097d770443316", "fetch_scale": 262144.0 / 131088.5, "write_scale": 1.0,
            "kib": {
                # 1D two-soliton lattice, L = 16384: the two-lane kernel at 2 steps per pass
-               "1d_two_soliton_scattering/c64/interleaved": {"k_step1d_lanes/S2": (714.5, 1280.0)},
+               "1d_two_soliton_scattering/c64/interleaved": {"k_step1d_lanes/S2": (716.0, 1280.0)},
                # 2D 2048^2 vortex pair (bands of rows)
-               "2d_vortex_pair/c128/interleaved": {"k_step2d/rows76": (365626.0, 655360.0)},
-               "2d_vortex_pair/c64/interleaved": {"k_step2d/rows38": (200475.0, 328237.0)},
-               "2d_vortex_pair/c64/plain": {"k_step2d/rows38": (204861.0, 332461.0)},
+               "2d_vortex_pair/c128/interleaved": {"k_step2d/rows76": (365640.0, 655360.0)},
+               "2d_vortex_pair/c64/interleaved": {"k_step2d/rows38": (200466.0, 328507.0)},
+               "2d_vortex_pair/c64/plain": {"k_step2d/rows38": (205615.0, 332958.0)},
                # 3D cubes: one step = z pass + y-x pass (sums of the two)
-               "3d_vortex_lines/c64/interleaved": {"k_step3d/rows64": (737397.0 + 744072.0,
-                                                                       1310720.0 + 1313990.0)},
-               "3d_vortex_lines_512/c128/interleaved": {"k_step3d/rows128": (11141300.0 + 11251100.0,
+               "3d_vortex_lines/c64/interleaved": {"k_step3d/rows64": (737398.0 + 744433.0,
+                                                                       1310720.0 + 1315890.0)},
+               "3d_vortex_lines_512/c128/interleaved": {"k_step3d/rows128": (11141300.0 + 11251700.0,
                                                                              20971520.0 + 20971520.0)}}}
 
 

@@ -451,8 +451,10 @@ __device__ __forceinline__ void recompute_substeps(const Shift& sh, cx<T> (&a)[5
   }
 }
 
+// (FP64: a budget for three wavefronts per SIMD, as k_line_yz.)
 template <typename T, bool kExt>
-__global__ __launch_bounds__(kChunk) void k_recompute_x(const cx<T>* __restrict__ in, cx<T>* __restrict__ out,
+__global__ __launch_bounds__(kChunk) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 1)))
+void k_recompute_x(const cx<T>* __restrict__ in, cx<T>* __restrict__ out,
                                                        cx<T>* __restrict__ rec, int64_t rstep, int first,
                                                        LaunchGeom g, const int* __restrict__ pre, int nwaves,
                                                        Angles<T> ang, const double* __restrict__ pot, double mu,
@@ -473,7 +475,7 @@ __global__ __launch_bounds__(kChunk) void k_recompute_x(const cx<T>* __restrict_
   if (l.own) store_site(out, t.d, s, a, b);
 }
 
-// FP64: a budget for three wavefronts per SIMD, as k_line_yz.
+// The same budget.
 template <typename T, int W, bool kExt>
 __global__ __launch_bounds__(kLanes * W) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 2)))
 void k_recompute_yz(const cx<T>* __restrict__ in, cx<T>* __restrict__ out,
@@ -656,7 +658,8 @@ struct ThinTile : LineTileYz {
 };
 
 template <typename T, bool kExt>
-__global__ __launch_bounds__(kChunk) void k_recompute_thin(const cx<T>* __restrict__ in, cx<T>* __restrict__ out,
+__global__ __launch_bounds__(kChunk) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 1)))
+void k_recompute_thin(const cx<T>* __restrict__ in, cx<T>* __restrict__ out,
                                                           cx<T>* __restrict__ rec, int64_t rstep, LaunchGeom g,
                                                           const int* __restrict__ pre, int nwaves, int zp,
                                                           Angles<T> ang, const double* __restrict__ pot, double mu,

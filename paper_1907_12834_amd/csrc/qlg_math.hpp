@@ -38,61 +38,6 @@ template <typename T> QLG_HD cx<T> rfma(T s, cx<T> a, cx<T> acc) {
   return {acc.re + s * a.re, acc.im + s * a.im};
 }
 
-// sin and cos of x.  The phase angles of U are small (|x| << 1 for any stable
-// time step), so |x| <= pi/4 is evaluated by the Taylor series itself, with
-// enough terms that the truncation (|x|^11/11! ~ 2e-9 in FP32, |x|^19/19! ~ 1e-19
-// in FP64 at |x| = pi/4) stays below the format's rounding; larger angles take
-// the library routine.  Below |x| = 1/16, where the angles of a typical step lie,
-// fewer terms reach the same bound: the first omitted terms are |x|^7/7! and
-// |x|^8/8! (FP32; < 1e-12 |x|) and |x|^11/11! and |x|^10/10! (FP64; < 1e-19 |x|).
-QLG_HD void sincos_t(float x, float* s, float* c) {
-  if (fabsf(x) <= 0.0625f) {
-    const float x2 = x * x;
-    *s = x * (1.0f + x2 * (-1.0f / 6 + x2 * (1.0f / 120)));
-    *c = 1.0f + x2 * (-0.5f + x2 * (1.0f / 24 + x2 * (-1.0f / 720)));
-  } else if (fabsf(x) <= 0.78539816f) {
-    const float x2 = x * x;
-    *s = x * (1.0f + x2 * (-1.0f / 6 + x2 * (1.0f / 120 + x2 * (-1.0f / 5040 + x2 * (1.0f / 362880)))));
-    *c = 1.0f + x2 * (-0.5f + x2 * (1.0f / 24 + x2 * (-1.0f / 720 + x2 * (1.0f / 40320 + x2 * (-1.0f / 3628800)))));
-  } else {
-    sincosf(x, s, c);
-  }
-}
-QLG_HD void sincos_t(double x, double* s, double* c) {
-  if (fabs(x) <= 0.0625) {
-    const double x2 = x * x;
-    double ps = 1.0 / 362880.0, pc = 1.0 / 40320.0;   // 1/9!, 1/8!
-    ps = fma(x2, ps, -1.0 / 5040.0);
-    pc = fma(x2, pc, -1.0 / 720.0);
-    ps = fma(x2, ps, 1.0 / 120.0);
-    pc = fma(x2, pc, 1.0 / 24.0);
-    ps = fma(x2, ps, -1.0 / 6.0);
-    pc = fma(x2, pc, -0.5);
-    *s = fma(x * x2, ps, x);
-    *c = fma(x2, pc, 1.0);
-  } else if (fabs(x) <= 0.7853981633974483) {
-    const double x2 = x * x;
-    double ps = 1.0 / 355687428096000.0, pc = 1.0 / 20922789888000.0;   // 1/17!, 1/16!
-    ps = fma(x2, ps, -1.0 / 1307674368000.0);    // 1/15!
-    pc = fma(x2, pc, -1.0 / 87178291200.0);      // 1/14!
-    ps = fma(x2, ps, 1.0 / 6227020800.0);        // 1/13!
-    pc = fma(x2, pc, 1.0 / 479001600.0);         // 1/12!
-    ps = fma(x2, ps, -1.0 / 39916800.0);         // 1/11!
-    pc = fma(x2, pc, -1.0 / 3628800.0);          // 1/10!
-    ps = fma(x2, ps, 1.0 / 362880.0);            // 1/9!
-    pc = fma(x2, pc, 1.0 / 40320.0);             // 1/8!
-    ps = fma(x2, ps, -1.0 / 5040.0);             // 1/7!
-    pc = fma(x2, pc, -1.0 / 720.0);              // 1/6!
-    ps = fma(x2, ps, 1.0 / 120.0);               // 1/5!
-    pc = fma(x2, pc, 1.0 / 24.0);                // 1/4!
-    ps = fma(x2, ps, -1.0 / 6.0);
-    pc = fma(x2, pc, -0.5);
-    *s = fma(x * x2, ps, x);
-    *c = fma(x2, pc, 1.0);
-  } else {
-    sincos(x, s, c);
-  }
-}
 // Whether p holds on every active lane of the wavefront (the host build: p itself).  A
 // branch on it is uniform: no execution-mask changes, both sides never run.
 QLG_HD bool all_lanes(bool p) {
@@ -103,12 +48,32 @@ QLG_HD bool all_lanes(bool p) {
 #endif
 }
 
+QLG_HD void sincos_t(float x, float* s, float* c) { sincosf(x, s, c); }
+QLG_HD void sincos_t(double x, double* s, double* c) { sincos(x, s, c); }
 QLG_HD float sqrt_t(float x) { return sqrtf(x); }
 QLG_HD double sqrt_t(double x) { return sqrt(x); }
 
-// 1/x for x != 0 (normal): the hardware approximation (about one ulp) in FP32; in FP64 the hardware
-// estimate refined by two Newton steps, each of which squares its relative error
-// (y <- y + y (1 - x y)), to within a few ulp of the exact value (the host build divides).
+// 1/sqrt(x) for x > 0 and 1/x for x != 0 (normal): the hardware approximations (about one ulp) in
+// FP32; in FP64 the hardware estimate refined by two Newton steps, each of which squares its relative
+// error (y <- y + y (1 - x y^2) / 2 and y <- y + y (1 - x y)), to within a few ulp of the exact value
+// (the host build divides).
+QLG_HD float rsqrt_t(float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_rsqf(x);
+#else
+  return 1.0f / sqrtf(x);
+#endif
+}
+QLG_HD double rsqrt_t(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) y = fma(0.5 * y, fma(-(x * y), y, 1.0), y);
+  return y;
+#else
+  return 1.0 / sqrt(x);
+#endif
+}
 QLG_HD float rcp_t(float x) {
 #if defined(__HIP_DEVICE_COMPILE__)
   return __builtin_amdgcn_rcpf(x);
@@ -206,13 +171,46 @@ QLG_HD double fma_t(double a, double b, double c) { return fma(a, b, c); }
 
 // (cos x - 1) / x^2 and sin(x) / x as polynomials in y = x^2, for |x| <= 1/8: the first omitted
 // terms are x^10/12! and x^10/11! in FP64 (2e-18 and 2e-17 at x = 1/8) and x^6/8! and x^6/7! in
-// FP32 (1e-10 and 8e-10).
-QLG_HD void phase_series(float y, float* c, float* s) {
-  *c = fma_t(y, fma_t(y, -1.0f / 720, 1.0f / 24), -0.5f);
-  *s = fma_t(y, fma_t(y, 1.0f / 120, -1.0f / 6), 1.0f);
+// FP32 (1e-10 and 8e-10).  kLong: with the terms that |x| <= pi/2 needs (the first omitted: x^22/24! and
+// x^22/23!, 3e-20 and 8e-19, in FP64; x^14/16! and x^14/15!, 3e-11 and 4e-10, in FP32), which are set to
+// zero where `small`: the same operations on the rest, so the short series' value bit for bit.
+template <bool kLong>
+QLG_HD void phase_series(float y, bool small, float* c, float* s) {
+  float pc = -1.0f / 720, ps = 1.0f / 120;
+  if constexpr (kLong) {
+    float hc = float(-1.0 / 87178291200.0);   // -1/14!
+    float hs = float(1.0 / 6227020800.0);   // 1/13!
+    hc = fma_t(y, hc, float(1.0 / 479001600.0));   // 1/12!
+    hs = fma_t(y, hs, float(-1.0 / 39916800.0));   // -1/11!
+    hc = fma_t(y, hc, float(-1.0 / 3628800.0));   // -1/10!
+    hs = fma_t(y, hs, float(1.0 / 362880.0));   // 1/9!
+    hc = fma_t(y, hc, float(1.0 / 40320.0));   // 1/8!
+    hs = fma_t(y, hs, float(-1.0 / 5040.0));   // -1/7!
+    pc = fma_t(y, small ? 0.0f : hc, pc);
+    ps = fma_t(y, small ? 0.0f : hs, ps);
+  }
+  *c = fma_t(y, fma_t(y, pc, 1.0f / 24), -0.5f);
+  *s = fma_t(y, fma_t(y, ps, -1.0f / 6), 1.0f);
 }
-QLG_HD void phase_series(double y, double* c, double* s) {
+template <bool kLong>
+QLG_HD void phase_series(double y, bool small, double* c, double* s) {
   double pc = -1.0 / 3628800.0, ps = 1.0 / 362880.0;   // -1/10!, 1/9!
+  if constexpr (kLong) {
+    double hc = -1.0 / 1124000727777607680000.0;   // -1/22!
+    double hs = 1.0 / 51090942171709440000.0;   // 1/21!
+    hc = fma(y, hc, 1.0 / 2432902008176640000.0);   // 1/20!
+    hs = fma(y, hs, -1.0 / 121645100408832000.0);   // -1/19!
+    hc = fma(y, hc, -1.0 / 6402373705728000.0);   // -1/18!
+    hs = fma(y, hs, 1.0 / 355687428096000.0);   // 1/17!
+    hc = fma(y, hc, 1.0 / 20922789888000.0);   // 1/16!
+    hs = fma(y, hs, -1.0 / 1307674368000.0);   // -1/15!
+    hc = fma(y, hc, -1.0 / 87178291200.0);   // -1/14!
+    hs = fma(y, hs, 1.0 / 6227020800.0);   // 1/13!
+    hc = fma(y, hc, 1.0 / 479001600.0);   // 1/12!
+    hs = fma(y, hs, -1.0 / 39916800.0);   // -1/11!
+    pc = fma(y, small ? 0.0 : hc, pc);
+    ps = fma(y, small ? 0.0 : hs, ps);
+  }
   pc = fma(y, pc, 1.0 / 40320.0);
   ps = fma(y, ps, -1.0 / 5040.0);
   pc = fma(y, pc, -1.0 / 720.0);
@@ -223,13 +221,47 @@ QLG_HD void phase_series(double y, double* c, double* s) {
   *s = fma(y, ps, 1.0);
 }
 // cos h and sin(h) / h as polynomials in y = h^2, for |h| <= 1/16 (first omitted terms
-// h^10/10! = 3e-19 and h^10/11! in FP64, h^6/6! = 8e-11 and h^6/7! in FP32).
-QLG_HD void half_angle_series(float y, float* c, float* s) {
-  *c = fma_t(y, fma_t(y, 1.0f / 24, -0.5f), 1.0f);
-  *s = fma_t(y, fma_t(y, 1.0f / 120, -1.0f / 6), 1.0f);
+// h^10/10! = 3e-19 and h^10/11! in FP64, h^6/6! = 8e-11 and h^6/7! in FP32); kLong: |h| <= pi/2
+// (h^24/24! = 8e-20 and h^22/23! = 8e-19, h^16/16! = 7e-11 and h^14/15! = 4e-10), in the same way.
+template <bool kLong>
+QLG_HD void half_angle_series(float y, bool small, float* c, float* s) {
+  float pc = 1.0f / 24, ps = 1.0f / 120;
+  if constexpr (kLong) {
+    float hc = float(-1.0 / 87178291200.0);   // -1/14!
+    hc = fma_t(y, hc, float(1.0 / 479001600.0));   // 1/12!
+    float hs = float(1.0 / 6227020800.0);   // 1/13!
+    hc = fma_t(y, hc, float(-1.0 / 3628800.0));   // -1/10!
+    hs = fma_t(y, hs, float(-1.0 / 39916800.0));   // -1/11!
+    hc = fma_t(y, hc, float(1.0 / 40320.0));   // 1/8!
+    hs = fma_t(y, hs, float(1.0 / 362880.0));   // 1/9!
+    hc = fma_t(y, hc, float(-1.0 / 720.0));   // -1/6!
+    hs = fma_t(y, hs, float(-1.0 / 5040.0));   // -1/7!
+    pc = fma_t(y, small ? 0.0f : hc, pc);
+    ps = fma_t(y, small ? 0.0f : hs, ps);
+  }
+  *c = fma_t(y, fma_t(y, pc, -0.5f), 1.0f);
+  *s = fma_t(y, fma_t(y, ps, -1.0f / 6), 1.0f);
 }
-QLG_HD void half_angle_series(double y, double* c, double* s) {
+template <bool kLong>
+QLG_HD void half_angle_series(double y, bool small, double* c, double* s) {
   double pc = 1.0 / 40320.0, ps = 1.0 / 362880.0;
+  if constexpr (kLong) {
+    double hc = -1.0 / 1124000727777607680000.0;   // -1/22!
+    hc = fma(y, hc, 1.0 / 2432902008176640000.0);   // 1/20!
+    double hs = 1.0 / 51090942171709440000.0;   // 1/21!
+    hc = fma(y, hc, -1.0 / 6402373705728000.0);   // -1/18!
+    hs = fma(y, hs, -1.0 / 121645100408832000.0);   // -1/19!
+    hc = fma(y, hc, 1.0 / 20922789888000.0);   // 1/16!
+    hs = fma(y, hs, 1.0 / 355687428096000.0);   // 1/17!
+    hc = fma(y, hc, -1.0 / 87178291200.0);   // -1/14!
+    hs = fma(y, hs, -1.0 / 1307674368000.0);   // -1/15!
+    hc = fma(y, hc, 1.0 / 479001600.0);   // 1/12!
+    hs = fma(y, hs, 1.0 / 6227020800.0);   // 1/13!
+    hc = fma(y, hc, -1.0 / 3628800.0);   // -1/10!
+    hs = fma(y, hs, -1.0 / 39916800.0);   // -1/11!
+    pc = fma(y, small ? 0.0 : hc, pc);
+    ps = fma(y, small ? 0.0 : hs, ps);
+  }
   pc = fma(y, pc, -1.0 / 720.0);
   ps = fma(y, ps, -1.0 / 5040.0);
   pc = fma(y, pc, 1.0 / 24.0);
@@ -240,11 +272,27 @@ QLG_HD void half_angle_series(double y, double* c, double* s) {
   *s = fma(y, ps, 1.0);
 }
 
-// (c, s) of the density and singlet phases x0 and x2 and (ch, sh) of the half rotation, hh = h^2, for
-// small angles.
+// x less the nearest multiple k of pi: k times its two parts, each product exact in its multiply-add; x
+// itself, exactly, where k is 0.
+QLG_HD double rint_t(double x) { return rint(x); }
+QLG_HD float rint_t(float x) { return rintf(x); }
+template <typename T>
+QLG_HD T reduce(T x, T* multiple) {
+  constexpr double hi = 3.141592653589793, lo = 1.2246467991473532e-16;   // their sum is pi to 107 bits
+  constexpr T hi_t = T(hi), lo_t = T(hi - double(hi_t) + lo);
+  const T k = rint_t(x * T(1.0 / hi));
+  *multiple = k;
+  return fma_t(-k, lo_t, fma_t(-k, hi_t, x));
+}
+template <typename T>
+QLG_HD bool is_odd(T k) { return T(2) * rint_t(T(0.5) * k) != k; }
+
+// cos x0 - 1 and sin x0 of the density phase x0; (cos x2 - 1) / x2^2 and sin(x2) / x2 of the singlet
+// phase x2; cos h and sin(h) / h of the half rotation, hh = h^2, up to their common sign, which the
+// rotation (Rot2) and its derivative do not see.
 template <typename T>
 struct Series {
-  T c0, s0, c2, s2, ch, sh;
+  T re0, im0, c2, s2, ch, sh;
 };
 template <typename T>
 QLG_HD bool small_angles(T x0, T x2, T hh) {
@@ -253,40 +301,73 @@ QLG_HD bool small_angles(T x0, T x2, T hh) {
 template <typename T>
 QLG_HD Series<T> short_series(T x0, T x2, T hh) {
   Series<T> r;
-  phase_series(x0 * x0, &r.c0, &r.s0);
-  phase_series(x2 * x2, &r.c2, &r.s2);
-  half_angle_series(hh, &r.ch, &r.sh);
+  T c, s;
+  phase_series<false>(x0 * x0, true, &c, &s);
+  r.re0 = x0 * x0 * c;
+  r.im0 = x0 * s;
+  phase_series<false>(x2 * x2, true, &r.c2, &r.s2);
+  half_angle_series<false>(hh, true, &r.ch, &r.sh);
   return r;
 }
 
-// The same for any arguments: small angles by the short series, whatever the other sites of the
-// wavefront hold (a site's result must not depend on the tile it lies in); others through their half
-// angles (cos x - 1 = -2 sin^2(x/2) without cancellation).  Not inlined: the library routines' constants
-// would otherwise be hoisted out of the substep loops of every kernel, into registers that the usual path
-// needs (the pull-back spilled 40 of them per wavefront); nor is the choice per site, which there cost 1D
-// complex64 runs 2 %.
+// The same for any arguments.  A site's result must not depend on the tile it lies in, so each angle takes
+// its form by its own size, in the same instructions for all: reduced to pi/2, then the long series, which
+// is the short one where all of the site's are small; only beyond kMostAngle the library's sine and cosine
+// (three calls of it, in wavefronts of sites on both sides, took a 2048^2 step at angles up to several
+// radians to 1322 us in complex128 and 705 us in complex64; this form 1083 and 568 us).  Not inlined: its
+// constants would otherwise be hoisted out of the substep loops of every kernel, into registers that the
+// usual path needs.
+constexpr double kMostAngle = 4096;   // k below 2^11: exact products in FP32's reduction as well
 template <typename T>
 __host__ __device__ __attribute__((noinline)) inline Series<T> general_series(T x0, T x2, T hh) {
-  auto phase = [](T x, T* c, T* s) {
-    const T h = T(0.5) * x;
-    if (fabs(h) < T(1e-4)) {
-      phase_series(x * x, c, s);
-      return;
-    }
-    T sn, cn;
-    sincos_t(h, &sn, &cn);
-    const T sc = sn * rcp_t(h);
-    *c = T(-0.5) * sc * sc;
-    *s = sc * cn;
-  };
-  if (small_angles(x0, x2, hh)) return short_series(x0, x2, hh);
+  const bool small = small_angles(x0, x2, hh);
   Series<T> r;
-  phase(x0, &r.c0, &r.s0);
-  phase(x2, &r.c2, &r.s2);
-  const T h = sqrt_t(hh);
-  T sn;
-  sincos_t(h, &sn, &r.ch);
-  r.sh = h < T(1e-4) ? fma_t(hh, T(-1.0 / 6.0), T(1)) : sn * rcp_t(h);
+  T c, s, k;
+  const T r0 = reduce(x0, &k);
+  phase_series<true>(r0 * r0, small, &c, &s);
+  r.re0 = r0 * r0 * c;
+  r.im0 = r0 * s;
+  if (!all_lanes(k == T(0))) {   // cos and sin change sign over an odd multiple
+    const bool odd = is_odd(k);
+    r.re0 = odd ? T(-2) - r.re0 : r.re0;
+    r.im0 = odd ? -r.im0 : r.im0;
+  }
+  const T r2 = reduce(x2, &k);
+  phase_series<true>(r2 * r2, small, &r.c2, &r.s2);
+  if (!all_lanes(k == T(0))) {   // the same, over x2 instead of r2
+    const bool turned = k != T(0), odd = is_odd(k);
+    const T i2 = rcp_t(turned ? x2 : T(1)), co = r2 * r2 * r.c2, si = r2 * r.s2;
+    r.c2 = turned ? (odd ? T(-2) - co : co) * i2 * i2 : r.c2;
+    r.s2 = turned ? (odd ? -si : si) * i2 : r.s2;
+  }
+  T y = hh, q = T(1);
+  if (!all_lanes(hh <= T(2.4))) {   // (pi/2)^2 = 2.467
+    const bool turned = hh > T(2.4);
+    const T ih = rsqrt_t(turned ? hh : T(1)), h0 = hh * ih;
+    const T rh = reduce(fma_t(T(0.5) * ih, fma_t(-h0, h0, hh), h0), &k);   // of sqrt(hh)
+    y = turned ? rh * rh : hh;
+    q = turned ? rh * ih : T(1);
+  }
+  half_angle_series<true>(y, small, &r.ch, &r.sh);
+  r.sh *= q;
+  constexpr T most = T(kMostAngle);
+  if (__builtin_expect(!all_lanes(fmax(fabs(x0), fabs(x2)) <= most && hh <= most * most), 0)) {
+    if (fabs(x0) > most) {
+      sincos_t(x0, &r.im0, &r.re0);
+      r.re0 -= T(1);
+    }
+    if (fabs(x2) > most) {
+      sincos_t(x2, &s, &c);
+      const T i2 = rcp_t(x2);
+      r.s2 = s * i2;
+      r.c2 = (c - T(1)) * i2 * i2;
+    }
+    if (hh > most * most) {
+      const T h = sqrt_t(hh);
+      sincos_t(h, &s, &r.ch);
+      r.sh = s * rcp_t(h);
+    }
+  }
   return r;
 }
 
@@ -425,7 +506,7 @@ QLG_HD void w_coefficients(const cx<T> (&a)[5], const cx<T> (&b)[5], const Angle
   // every lane is small (the usual case) all take short series without a branch per lane.
   const Series<T> f = __builtin_expect(all_lanes(small_angles(x0, x2, hh)), 1) ? short_series(x0, x2, hh)
                                                                                : general_series(x0, x2, hh);
-  W.mu0 = cx<T>{x0 * x0 * f.c0, -(x0 * f.s0)};
+  W.mu0 = cx<T>{f.re0, -f.im0};
   // singlet coefficient (exp(-i x2) - 1) / n = th g2/5 (x2 c - i s): no division by n, so empty or
   // denormal sites stay finite; times exp(-i x0) = 1 + mu0
   const cx<T> cs{ang.tg25 * x2 * f.c2, -(ang.tg25 * f.s2)};

@@ -101,8 +101,8 @@ QLG_HD void potential_vjp(const cx<double> (&a)[5], const cx<double> (&b)[5], cx
   const double hh = fma(Hx, Hx, fma(Hy, Hy, Hz * Hz));
   const double x0 = fma(theta * g0, n, ext), x2 = kappa * n;
 
-  // c = (cos x - 1)/x^2 and s = sin(x)/x of the density and singlet phases; cos h, sin(h)/h of the
-  // half rotation; pd = (sin(x2)/x2 - cos x2)/x2^2 (for c'(n)); pj = (1 - sinc(phi))/phi^2, phi = 2 h
+  // the phases and the half rotation (Series); pd = (sin(x2)/x2 - cos x2)/x2^2 (for c'(n));
+  // pj = (1 - sinc(phi))/phi^2, phi = 2 h
   Series<double> f;
   double pd, pj;
   auto pd_series = [](double y) {   // first omitted term y^5/518918400 (|x2| < 0.1: 2e-19)
@@ -121,7 +121,7 @@ QLG_HD void potential_vjp(const cx<double> (&a)[5], const cx<double> (&b)[5], cx
     pd = fabs(x2) <= 0.1 ? pd_series(y2) : (f.s2 - fma(y2, f.c2, 1.0)) * rcp_t(y2);
     pj = hh <= 1.0 / 256.0 ? pj_series(4.0 * hh) : (1.0 - f.sh * f.ch) * rcp_t(4.0 * hh);
   }
-  const cx<double> mu0{x0 * x0 * f.c0, -(x0 * f.s0)};
+  const cx<double> mu0{f.re0, -f.im0};
   const cx<double> cs{kappa * x2 * f.c2, -(kappa * f.s2)};        // c(n)
   Rot2<double> R;
   rot2(f.ch, f.sh * Hx, f.sh * Hy, f.sh * Hz, R);
